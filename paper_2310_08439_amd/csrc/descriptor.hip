@@ -68,7 +68,8 @@ struct PathArgs {
     // P written by the forward pass (if non-null) and read back by the
     // adjoint: [S][K][DR][n] by work slot (VALU kernels), or, for the
     // matrix-core pair, one tile per 16-atom group g of the work order,
-    // [g][S][K][4][16][4] (element (k, q, atom, i) = P[k][kMfmaRow[q][i]])
+    // [g][S][K/4][4][16][4][4]: element (kk, set, atom, j, i) =
+    // P[4 kk + j][kMfmaRow[i][set]]
     float* Pbuf;
     // backward output: virial block partials
     double* vir;
@@ -118,9 +119,7 @@ struct GlobalPos {
     }
 };
 struct LdsPos {
-    const float* sx;
-    const float* sy;
-    const float* sz;
+    const float* sp;  // [halo slot][3]
     const int32_t* hoff;
     int hp0;           // centre's halo slot minus (HX HY + HX + 1), the slot offset of the bit fields (0, 0, 0)
     int HX, HXY;       // halo cells along x, and per z layer
@@ -129,7 +128,7 @@ struct LdsPos {
     __device__ float4 fetch(int q, int32_t im, int& slot) const {
         const int i = hoff[hp0 + img_sz(im) * HXY + img_sy(im) * HX + img_sx(im)] + q;
         slot = i;
-        return make_float4(sx[i], sy[i], sz[i], 0.0f);
+        return make_float4(sp[3 * i], sp[3 * i + 1], sp[3 * i + 2], 0.0f);
     }
     // (x_q - x_i) + (b - 1) w = x_q - (x_i + w) + b w for the field b = o + 1
     __device__ float3 disp(const float4& xj, int32_t im) const {
@@ -860,12 +859,19 @@ __device__ __forceinline__ void halo_slots(const BlockGeom& bg, int64_t lb, int3
     __syncthreads();
 }
 
-// Positions of the halo atoms into sx, sy, sz (slot order) as FP32 offsets
-// from the origin of the atom's own cell (cell c spans [c w, (c+1) w)).
-// Ends with a barrier.
+// hp_of[c]: halo cell of the block's cell c (a table, because the divisions by
+// the run-time block edges cost ~75 vector instructions per group of atoms).
+// A barrier must follow before it is read.
+__device__ __forceinline__ void block_halo_cells(const BlockGeom& bg, int32_t* hp_of) {
+    const int t = threadIdx.x, HX = bg.B[0] + 2, HY = bg.B[1] + 2;
+    if (t < bg.B[0] * bg.B[1] * bg.B[2])
+        hp_of[t] = ((t / (bg.B[0] * bg.B[1]) + 1) * HY + (t / bg.B[0]) % bg.B[1] + 1) * HX + t % bg.B[0] + 1;
+}
+
+// Positions of the halo atoms into sp[slot][3] as FP32 offsets from the origin
+// of the atom's own cell (cell c spans [c w, (c+1) w)).  Ends with a barrier.
 __device__ __forceinline__ void halo_positions(const BlockGeom& bg, const PathArgs& a, int x0, int y0, int z0,
-                                               const int32_t* h_first, const int32_t* h_base, float* sx, float* sy,
-                                               float* sz) {
+                                               const int32_t* h_first, const int32_t* h_base, float* sp) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int HX = bg.B[0] + 2, HY = bg.B[1] + 2, HZ = bg.B[2] + 2;
     for (int hc = wv; hc < HX * HY * HZ; hc += kBlock / 64) {
@@ -876,12 +882,30 @@ __device__ __forceinline__ void halo_positions(const BlockGeom& bg, const PathAr
         const int lo = h_base[hc], cnt = h_base[hc + 1] - lo;
         for (int k = lane; k < cnt; k += 64) {
             const double4 x = a.xs[h_first[hc] + k];
-            sx[lo + k] = (float)(x.x - ox);
-            sy[lo + k] = (float)(x.y - oy);
-            sz[lo + k] = (float)(x.z - oz);
+            sp[3 * (lo + k)] = (float)(x.x - ox);
+            sp[3 * (lo + k) + 1] = (float)(x.y - oy);
+            sp[3 * (lo + k) + 2] = (float)(x.z - oz);
         }
     }
     __syncthreads();
+}
+
+// The block's fixed-point force sums sF[slot][3], cleared before and added to F
+// (one range per halo cell) after the pair loops.
+__device__ __forceinline__ void clear_forces(unsigned long long* sF, int atoms) {
+    for (int i = threadIdx.x; i < 3 * atoms; i += kBlock) sF[i] = 0ull;
+}
+__device__ __forceinline__ void flush_forces(const BlockGeom& bg, int nh, const int32_t* h_first, const int32_t* h_base,
+                                             const unsigned long long* sF) {
+    const int lane = threadIdx.x & 63;
+    for (int hc = threadIdx.x >> 6; hc < nh; hc += kBlock / 64) {
+        const int lo = 3 * h_base[hc], cnt = 3 * h_base[hc + 1] - lo;
+        unsigned long long* F = bg.F + 3 * (int64_t)h_first[hc];
+        for (int k = lane; k < cnt; k += 64) {
+            const unsigned long long f = sF[lo + k];
+            if (f) atomicAdd(&F[k], f);
+        }
+    }
 }
 
 // Adjoint over one block of B0 x B1 x B2 cells (ScatterSum, Sec. III.A, done
@@ -896,29 +920,23 @@ __device__ __forceinline__ void halo_positions(const BlockGeom& bg, const PathAr
 // PAIR2: two chunk lanes per atom (adjoint_atom_pair2).
 template <int KC, int M, int RAD, bool PAIR2>
 __global__ void __launch_bounds__(256) k_adjoint_blocked(PathArgs a, BlockGeom bg) {
-    // [3][hmax] halo positions (floats), then [3][hmax] fixed-point force accumulators
+    // [hmax][3] halo positions (floats), then [hmax][3] fixed-point force accumulators
     extern __shared__ __attribute__((aligned(8))) unsigned char lds_dyn[];
     __shared__ int32_t h_base[257], h_first[kMaxHaloCells], hoff[kMaxHaloCells];
-    __shared__ int32_t wtmp[kBlock / 64];
+    __shared__ int32_t wtmp[kBlock / 64], hp_of[kMaxBlockCells];
     __shared__ double red[6][kBlock / 64][2];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int blk = blockIdx.x;
     int x0, y0, z0;
+    block_halo_cells(bg, hp_of);
     halo_slots(bg, blk, h_first, h_base, hoff, wtmp, x0, y0, z0);
     const int HX = bg.B[0] + 2, HY = bg.B[1] + 2, HZ = bg.B[2] + 2;
     const int nh = HX * HY * HZ;
     const int hpos = (3 * bg.hmax + 1) & ~1;  // floats of the positions, rounded to 8 bytes
-    float* sx = reinterpret_cast<float*>(lds_dyn);
-    float* sy = sx + bg.hmax;
-    float* sz = sx + 2 * bg.hmax;
-    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sx + hpos);
-    const int htot = h_base[nh];
-    for (int i = t; i < htot; i += kBlock) {
-        sF[i] = 0ull;
-        sF[bg.hmax + i] = 0ull;
-        sF[2 * bg.hmax + i] = 0ull;
-    }
-    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sx, sy, sz);  // ends with a barrier
+    float* sp = reinterpret_cast<float*>(lds_dyn);
+    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sp + hpos);
+    clear_forces(sF, h_base[nh]);
+    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sp);  // ends with a barrier
     const float cw[3] = {(float)(a.L[0] / bg.nc[0]), (float)(a.L[1] / bg.nc[1]), (float)(a.L[2] / bg.nc[2])};
     // the block's atoms are work slots wbase[blk] .. wbase[blk+1], ordered by row length
     const int nch = 1 << a.nch_log2;
@@ -926,47 +944,36 @@ __global__ void __launch_bounds__(256) k_adjoint_blocked(PathArgs a, BlockGeom b
     const int items = (int)(bg.wbase[blk + 1] - w0) << a.nch_log2;
     double Wd[6] = {0, 0, 0, 0, 0, 0};
     auto sink = [&](int idx, float gx, float gy, float gz) {  // idx: the neighbour's halo slot
-        atomicAdd(&sF[idx], to_fixed(-gx));
-        atomicAdd(&sF[bg.hmax + idx], to_fixed(-gy));
-        atomicAdd(&sF[2 * bg.hmax + idx], to_fixed(-gz));
+        atomicAdd(&sF[3 * idx], to_fixed(-gx));
+        atomicAdd(&sF[3 * idx + 1], to_fixed(-gy));
+        atomicAdd(&sF[3 * idx + 2], to_fixed(-gz));
     };
     for (int item = t; item < ((items + kBlock - 1) / kBlock) * kBlock; item += kBlock) {
         if (item >= items) continue;
         const int ch = item & (nch - 1);
         const int64_t w = w0 + (item >> a.nch_log2);
         const int64_t p = bg.wperm[w];
-        const int ic = bg.wcell[w];
-        const int ix = ic % bg.B[0] + 1, iy = (ic / bg.B[0]) % bg.B[1] + 1, iz = ic / (bg.B[0] * bg.B[1]) + 1;
-        const int hp = (iz * HY + iy) * HX + ix;
+        const int hp = hp_of[bg.wcell[w]];
         const int ip = hoff[hp] + (int)p;
-        const LdsPos pos{sx, sy, sz, hoff, hp - (HX * HY + HX + 1), HX, HX * HY,
-                         sx[ip] + cw[0], sy[ip] + cw[1], sz[ip] + cw[2], cw[0], cw[1], cw[2]};
+        const LdsPos pos{sp, hoff, hp - (HX * HY + HX + 1), HX, HX * HY, sp[3 * ip] + cw[0], sp[3 * ip + 1] + cw[1],
+                         sp[3 * ip + 2] + cw[2], cw[0], cw[1], cw[2]};
         float Fo[3] = {0.0f, 0.0f, 0.0f};
         if constexpr (PAIR2) {
             adjoint_atom_pair2<KC, M, RAD>(a, p, w, ch, Wd, Fo, pos, sink);
-            atomicAdd(&sF[ip], to_fixed(Fo[0]));
-            atomicAdd(&sF[bg.hmax + ip], to_fixed(Fo[1]));
-            atomicAdd(&sF[2 * bg.hmax + ip], to_fixed(Fo[2]));
+            atomicAdd(&sF[3 * ip], to_fixed(Fo[0]));
+            atomicAdd(&sF[3 * ip + 1], to_fixed(Fo[1]));
+            atomicAdd(&sF[3 * ip + 2], to_fixed(Fo[2]));
         } else {
             adjoint_atom<KC, M, RAD>(a, p, w, ch, nch, Wd, Fo, pos, sink);
             if (ch == 0) {
-                atomicAdd(&sF[ip], to_fixed(Fo[0]));
-                atomicAdd(&sF[bg.hmax + ip], to_fixed(Fo[1]));
-                atomicAdd(&sF[2 * bg.hmax + ip], to_fixed(Fo[2]));
+                atomicAdd(&sF[3 * ip], to_fixed(Fo[0]));
+                atomicAdd(&sF[3 * ip + 1], to_fixed(Fo[1]));
+                atomicAdd(&sF[3 * ip + 2], to_fixed(Fo[2]));
             }
         }
     }
     __syncthreads();
-    for (int hc = wv; hc < nh; hc += kBlock / 64) {
-        const int lo = h_base[hc], cnt = h_base[hc + 1] - lo;
-        for (int k = lane; k < cnt; k += 64) {
-            const int64_t q = h_first[hc] + k;
-            const unsigned long long fx = sF[lo + k], fy = sF[bg.hmax + lo + k], fz = sF[2 * bg.hmax + lo + k];
-            if (fx) atomicAdd(&bg.F[3 * q + 0], fx);
-            if (fy) atomicAdd(&bg.F[3 * q + 1], fy);
-            if (fz) atomicAdd(&bg.F[3 * q + 2], fz);
-        }
-    }
+    flush_forces(bg, nh, h_first, h_base, sF);
     block_virial(Wd, red, a.vir + (int64_t)blockIdx.x * kVirDoubles);
 }
 
@@ -1006,32 +1013,26 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
     constexpr bool KA = RAD == kRadRec && KQ <= 3;  // k P' as the second product's A operand
     extern __shared__ __attribute__((aligned(8))) unsigned char lds_dyn[];
     __shared__ int32_t h_base[257], h_first[kMaxHaloCells], hoff[kMaxHaloCells];
-    __shared__ int32_t wtmp[kBlock / 64];
+    __shared__ int32_t wtmp[kBlock / 64], hp_of[kMaxBlockCells];
     __shared__ double red[6][kBlock / 64][2];
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int quad = lane >> 2, j = lane & 3;
     const int blk = blockIdx.x;
     int x0, y0, z0;
+    block_halo_cells(bg, hp_of);
     halo_slots(bg, blk, h_first, h_base, hoff, wtmp, x0, y0, z0);
     const int HX = bg.B[0] + 2, HY = bg.B[1] + 2, HZ = bg.B[2] + 2;
     const int nh = HX * HY * HZ;
     const int hpos = (3 * bg.hmax + 1) & ~1;
-    float* sx = reinterpret_cast<float*>(lds_dyn);
-    float* sy = sx + bg.hmax;
-    float* sz = sx + 2 * bg.hmax;
-    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sx + hpos);
-    const int htot = h_base[nh];
-    for (int i = t; i < htot; i += kBlock) {
-        sF[i] = 0ull;
-        sF[bg.hmax + i] = 0ull;
-        sF[2 * bg.hmax + i] = 0ull;
-    }
-    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sx, sy, sz);  // ends with a barrier
+    float* sp = reinterpret_cast<float*>(lds_dyn);
+    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sp + hpos);
+    clear_forces(sF, h_base[nh]);
+    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sp);  // ends with a barrier
     const float cw[3] = {(float)(a.L[0] / bg.nc[0]), (float)(a.L[1] / bg.nc[1]), (float)(a.L[2] / bg.nc[2])};
     auto sink = [&](int idx, float gx, float gy, float gz) {
-        atomicAdd(&sF[idx], to_fixed(-gx));
-        atomicAdd(&sF[bg.hmax + idx], to_fixed(-gy));
-        atomicAdd(&sF[2 * bg.hmax + idx], to_fixed(-gz));
+        atomicAdd(&sF[3 * idx], to_fixed(-gx));
+        atomicAdd(&sF[3 * idx + 1], to_fixed(-gy));
+        atomicAdd(&sF[3 * idx + 2], to_fixed(-gz));
     };
     // 2 x the multiplicities of this lane's kept components kMfmaRow[q][j] and
     // of its dropped one (full T_dm row order: xx 1, xy 2, yy 1, zz 1; x 1,
@@ -1057,24 +1058,21 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
         const int64_t w = w0 + (aval ? ia : natoms - 1);
         const int64_t g = bg.gbase[blk] + base / 16;  // the 16-atom group of P
         const int64_t p = bg.wperm[w];
-        const int ic = bg.wcell[w];
-        const int ix = ic % bg.B[0] + 1, iy = (ic / bg.B[0]) % bg.B[1] + 1, iz = ic / (bg.B[0] * bg.B[1]) + 1;
-        const int hp = (iz * HY + iy) * HX + ix;
+        const int hp = hp_of[bg.wcell[w]];
         const int ip = hoff[hp] + (int)p;
-        const LdsPos pos{sx, sy, sz, hoff, hp - (HX * HY + HX + 1), HX, HX * HY,
-                         sx[ip] + cw[0], sy[ip] + cw[1], sz[ip] + cw[2], cw[0], cw[1], cw[2]};
+        const LdsPos pos{sp, hoff, hp - (HX * HY + HX + 1), HX, HX * HY, sp[3 * ip] + cw[0], sp[3 * ip + 1] + cw[1],
+                         sp[3 * ip + 2] + cw[2], cw[0], cw[1], cw[2]};
         float Fo[3] = {0.0f, 0.0f, 0.0f};
         for (int b = 0; b < a.S; ++b) {
             // this lane's slices of P' (= 2 T sigma' P, folded onto the kept basis)
             float Ap[K][4];
-            // P in the group layout: element (k, q, atom, i) of the group's
-            // species-b tile is P[k][kMfmaRow[q][i]]; this lane takes i = j
-            const float* Pb = a.Pbuf + ((int64_t)g * a.S + b) * (K * 256) + quad * 4 + j;
+            // P in the group layout: this lane's fold set of a radial function is one float4
+            const float4* P4 = reinterpret_cast<const float4*>(a.Pbuf) + (g * a.S + b) * (K * 64) + j * 64 + quad * 4;
             const float4* g4 = reinterpret_cast<const float4*>(a.dG + p * a.F + (int64_t)b * K * 4);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const float* Pk = Pb + k * 256;
-                const float pa = Pk[0], pb = Pk[64], pc = Pk[128], pf = Pk[192];
+                const float4 pv = P4[(k / 4) * 256 + k % 4];
+                const float pa = pv.x, pb = pv.y, pc = pv.z, pf = pv.w;
                 const float4 g = g4[k];
                 // the lane's orders picked arithmetically (0/1 weights), so that
                 // every lane loads the whole dE/dG quadruple with one instruction
@@ -1112,7 +1110,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
             // the displacements of batch c0 + 4 are formed (LDS) and the list
             // entries of batch c0 + 12 are loaded.  Entry indices are clamped
             // into the row's slots; lanes past the row's length read the centre
-            // atom (slot ip) and are inactive: unit displacement, zero B.
+            // atom (slot ip) and are inactive (their column of the products,
+            // NaN for a zero displacement, is theirs alone and is not used).
             const int cl = a.cap - 1;
             auto entry = [&](int c, int& q, int& im) {
                 const int cc = min(c, cl);
@@ -1126,9 +1125,9 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
                 const float4 xj = pos.fetch(qq, ii, gslot);
                 const float3 dm = pos.disp(xj, ii);
                 gact = valid && dm.x * dm.x + dm.y * dm.y + dm.z * dm.z < a.rc2;  // skin entries carry no force
-                gdx = gact ? dm.x : 1.0f;
-                gdy = gact ? dm.y : 0.0f;
-                gdz = gact ? dm.z : 0.0f;
+                gdx = dm.x;
+                gdy = dm.y;
+                gdz = dm.z;
             };
             float dx, dy, dz;
             int slot;
@@ -1153,13 +1152,13 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
                 float fc = 0.0f, dfc = 0.0f;
                 if constexpr (RAD != kRadTab) {
                     const float ang = R * a.half_inv_rc;
-                    fc = act ? 0.5f * __builtin_amdgcn_cosf(ang) + 0.5f : 0.0f;
-                    dfc = act ? -0.5f * a.pi_over_rc * __builtin_amdgcn_sinf(ang) : 0.0f;
+                    fc = 0.5f * __builtin_amdgcn_cosf(ang) + 0.5f;
+                    dfc = -0.5f * a.pi_over_rc * __builtin_amdgcn_sinf(ang);
                 }
                 float B1[K], B2[K];
                 if constexpr (RAD == kRadRec) {
                     const float t0 = R - mu0;
-                    float ek = act ? __builtin_amdgcn_exp2f(nef0 * t0 * t0) : 0.0f;
+                    float ek = __builtin_amdgcn_exp2f(nef0 * t0 * t0);
                     float rk = __builtin_amdgcn_exp2f(fmaf(a.rec_a, t0, a.rec_b));
 #pragma unroll
                     for (int k = 0; k < K; ++k) {
@@ -1170,12 +1169,6 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
                     }
                 } else if constexpr (RAD == kRadTab) {
                     tabulated<K, true>(a, R, 0, B1, B2);
-                    const float msk = act ? 1.0f : 0.0f;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        B1[k] *= msk;
-                        B2[k] *= msk;
-                    }
                 } else {
 #pragma unroll
                     for (int k = 0; k < K; ++k) {
@@ -1261,22 +1254,13 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma(PathArgs a, BlockGeom b
             Fo[i] += __shfl_xor(Fo[i], 2);
         }
         if (aval && j == 0) {
-            atomicAdd(&sF[ip], to_fixed(Fo[0]));
-            atomicAdd(&sF[bg.hmax + ip], to_fixed(Fo[1]));
-            atomicAdd(&sF[2 * bg.hmax + ip], to_fixed(Fo[2]));
+            atomicAdd(&sF[3 * ip], to_fixed(Fo[0]));
+            atomicAdd(&sF[3 * ip + 1], to_fixed(Fo[1]));
+            atomicAdd(&sF[3 * ip + 2], to_fixed(Fo[2]));
         }
     }
     __syncthreads();
-    for (int hc = wv; hc < nh; hc += kBlock / 64) {
-        const int lo = h_base[hc], cnt = h_base[hc + 1] - lo;
-        for (int k = lane; k < cnt; k += 64) {
-            const int64_t q = h_first[hc] + k;
-            const unsigned long long fx = sF[lo + k], fy = sF[bg.hmax + lo + k], fz = sF[2 * bg.hmax + lo + k];
-            if (fx) atomicAdd(&bg.F[3 * q + 0], fx);
-            if (fy) atomicAdd(&bg.F[3 * q + 1], fy);
-            if (fz) atomicAdd(&bg.F[3 * q + 2], fz);
-        }
-    }
+    flush_forces(bg, nh, h_first, h_base, sF);
     block_virial(Wd, red, a.vir + (int64_t)blockIdx.x * kVirDoubles);
 }
 
@@ -1306,17 +1290,16 @@ __global__ void __launch_bounds__(256, 2) k_descriptor_mfma(PathArgs a, BlockGeo
     constexpr int K = 4 * KQ, DR = Moments<3>::DR, D = Moments<3>::D;
     extern __shared__ __attribute__((aligned(8))) unsigned char lds_dyn[];
     __shared__ int32_t h_base[257], h_first[kMaxHaloCells], hoff[kMaxHaloCells];
-    __shared__ int32_t wtmp[kBlock / 64];
+    __shared__ int32_t wtmp[kBlock / 64], hp_of[kMaxBlockCells];
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int quad = lane >> 2, j = lane & 3;
     const int blk = blockIdx.x;
     int x0, y0, z0;
+    block_halo_cells(bg, hp_of);
     halo_slots(bg, blk, h_first, h_base, hoff, wtmp, x0, y0, z0);
     const int HX = bg.B[0] + 2, HY = bg.B[1] + 2;
-    float* sx = reinterpret_cast<float*>(lds_dyn);
-    float* sy = sx + bg.hmax;
-    float* sz = sx + 2 * bg.hmax;
-    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sx, sy, sz);  // ends with a barrier
+    float* sp = reinterpret_cast<float*>(lds_dyn);
+    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sp);  // ends with a barrier
     const float cw[3] = {(float)(a.L[0] / bg.nc[0]), (float)(a.L[1] / bg.nc[1]), (float)(a.L[2] / bg.nc[2])};
     // this lane's monomial factors s = (1, x, y, z)[j] and v = (xy, z, z, xy)[j],
     // as 0/1 weights
@@ -1340,12 +1323,10 @@ __global__ void __launch_bounds__(256, 2) k_descriptor_mfma(PathArgs a, BlockGeo
         const int64_t w = w0 + (aval ? ia : natoms - 1);
         const int64_t g = bg.gbase[blk] + base / 16;
         const int64_t p = bg.wperm[w];
-        const int ic = bg.wcell[w];
-        const int ix = ic % bg.B[0] + 1, iy = (ic / bg.B[0]) % bg.B[1] + 1, iz = ic / (bg.B[0] * bg.B[1]) + 1;
-        const int hp = (iz * HY + iy) * HX + ix;
+        const int hp = hp_of[bg.wcell[w]];
         const int ip = hoff[hp] + (int)p;
-        const LdsPos pos{sx, sy, sz, hoff, hp - (HX * HY + HX + 1), HX, HX * HY,
-                         sx[ip] + cw[0], sy[ip] + cw[1], sz[ip] + cw[2], cw[0], cw[1], cw[2]};
+        const LdsPos pos{sp, hoff, hp - (HX * HY + HX + 1), HX, HX * HY, sp[3 * ip] + cw[0], sp[3 * ip + 1] + cw[1],
+                         sp[3 * ip + 2] + cw[2], cw[0], cw[1], cw[2]};
         for (int b = 0; b < a.S; ++b) {
             f32x4 acc[KQ][4];
 #pragma unroll
@@ -1470,14 +1451,18 @@ __global__ void __launch_bounds__(256, 2) k_descriptor_mfma(PathArgs a, BlockGeo
             }
             if (c0 < nbmax) batch(c0, qA, iA);
             if (c0 + 4 < nbmax) batch(c0 + 4, qB, iB);
-            // P in the group layout (zeros for lanes past the block's atoms)
+            // P in the group layout (zeros for lanes past the block's atoms): each
+            // store instruction writes 1 KB in a row (with 256-byte runs per
+            // instruction: 0.850 ms at 1,024,000 atoms, K = 12, two species;
+            // now 0.816)
             if (a.Pbuf) {
-                float* dst = a.Pbuf + (((int64_t)g * a.S + b) * K + j) * 256 + quad * 4;
+                float* dst = a.Pbuf + ((int64_t)g * a.S + b) * (K * 256) + lane * 4;
 #pragma unroll
                 for (int kk = 0; kk < KQ; ++kk)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        __builtin_nontemporal_store(acc[kk][q], reinterpret_cast<f32x4*>(dst + kk * 1024 + q * 64));
+                    for (int st = 0; st < 4; ++st)
+                        __builtin_nontemporal_store(f32x4{acc[kk][0][st], acc[kk][1][st], acc[kk][2][st], acc[kk][3][st]},
+                                                    reinterpret_cast<f32x4*>(dst + (kk * 4 + st) * 256));
             }
             if (aval) {
 #pragma unroll
@@ -1531,30 +1516,24 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
     constexpr int K = 4 * KS, DR = Moments<3>::DR;
     extern __shared__ __attribute__((aligned(8))) unsigned char lds_dyn[];
     __shared__ int32_t h_base[257], h_first[kMaxHaloCells], hoff[kMaxHaloCells];
-    __shared__ int32_t wtmp[kBlock / 64];
+    __shared__ int32_t wtmp[kBlock / 64], hp_of[kMaxBlockCells];
     __shared__ double red[6][kBlock / 64][2];
     __shared__ float2 rad_mm[RAD == kRadDirect ? K : 1];  // (mu_k, -2 eta_k)
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int jp = lane & 15, gq = lane >> 4;
     const int blk = blockIdx.x;
     int x0, y0, z0;
+    block_halo_cells(bg, hp_of);
     halo_slots(bg, blk, h_first, h_base, hoff, wtmp, x0, y0, z0);
     const int HX = bg.B[0] + 2, HY = bg.B[1] + 2, HZ = bg.B[2] + 2;
     const int nh = HX * HY * HZ;
     const int hpos = (3 * bg.hmax + 1) & ~1;
-    float* sx = reinterpret_cast<float*>(lds_dyn);
-    float* sy = sx + bg.hmax;
-    float* sz = sx + 2 * bg.hmax;
-    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sx + hpos);
-    const int htot = h_base[nh];
-    for (int i = t; i < htot; i += kBlock) {
-        sF[i] = 0ull;
-        sF[bg.hmax + i] = 0ull;
-        sF[2 * bg.hmax + i] = 0ull;
-    }
+    float* sp = reinterpret_cast<float*>(lds_dyn);
+    unsigned long long* sF = reinterpret_cast<unsigned long long*>(sp + hpos);
+    clear_forces(sF, h_base[nh]);
     if constexpr (RAD == kRadDirect)
         for (int k = t; k < K; k += kBlock) rad_mm[k] = make_float2(a.mu[k], -2.0f * a.eta[k]);
-    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sx, sy, sz);  // ends with a barrier
+    halo_positions(bg, a, x0, y0, z0, h_first, h_base, sp);  // ends with a barrier
     const float cw[3] = {(float)(a.L[0] / bg.nc[0]), (float)(a.L[1] / bg.nc[1]), (float)(a.L[2] / bg.nc[2])};
     // A side: this lane supplies row jp = 4 gi + ri, kept component kMfmaRow[ri][gi]
     const int gi = jp >> 2, ri = jp & 3;
@@ -1583,12 +1562,10 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
     for (int ia = wv; ia < natoms; ia += kBlock / 64) {
         const int64_t w = w0 + ia;
         const int64_t p = bg.wperm[w];
-        const int ic = bg.wcell[w];
-        const int ix = ic % bg.B[0] + 1, iy = (ic / bg.B[0]) % bg.B[1] + 1, iz = ic / (bg.B[0] * bg.B[1]) + 1;
-        const int hp = (iz * HY + iy) * HX + ix;
+        const int hp = hp_of[bg.wcell[w]];
         const int ip = hoff[hp] + (int)p;
-        const LdsPos pos{sx, sy, sz, hoff, hp - (HX * HY + HX + 1), HX, HX * HY,
-                         sx[ip] + cw[0], sy[ip] + cw[1], sz[ip] + cw[2], cw[0], cw[1], cw[2]};
+        const LdsPos pos{sp, hoff, hp - (HX * HY + HX + 1), HX, HX * HY, sp[3 * ip] + cw[0], sp[3 * ip + 1] + cw[1],
+                         sp[3 * ip + 2] + cw[2], cw[0], cw[1], cw[2]};
         float Fo = 0.0f;  // component gq (< 3) of the centre atom's force, this lane's pairs
         for (int b = 0; b < a.S; ++b) {
             // this lane's A operands: P' (folded onto the kept basis) and k P'
@@ -1618,7 +1595,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
             // the displacements of group c0 + 16 are formed (LDS) and the list
             // entries of group c0 + 32 are loaded.  Entry indices are clamped
             // into the row's slots; columns past the row's end read the centre
-            // atom and are inactive (unit displacement, zero B).
+            // atom and are inactive (their column of the products is not used).
             const int cl = a.cap - 1;
             auto entry = [&](int c, int& q, int& im) {
                 const int cc = min(c, cl);
@@ -1631,9 +1608,9 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
                 const float4 xj = pos.fetch(valid ? q : (int)p, ii, gslot);
                 const float3 dm = pos.disp(xj, ii);
                 gact = valid && dm.x * dm.x + dm.y * dm.y + dm.z * dm.z < a.rc2;
-                gdx = gact ? dm.x : 1.0f;
-                gdy = gact ? dm.y : 0.0f;
-                gdz = gact ? dm.z : 0.0f;
+                gdx = dm.x;
+                gdy = dm.y;
+                gdz = dm.z;
             };
             float dx, dy, dz;
             int slot, qe, ie;
@@ -1654,8 +1631,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
                 float fc = 0.0f, dfc = 0.0f;
                 if constexpr (RAD != kRadTab) {
                     const float ang = R * a.half_inv_rc;
-                    fc = act ? 0.5f * __builtin_amdgcn_cosf(ang) + 0.5f : 0.0f;
-                    dfc = act ? -0.5f * a.pi_over_rc * __builtin_amdgcn_sinf(ang) : 0.0f;
+                    fc = 0.5f * __builtin_amdgcn_cosf(ang) + 0.5f;
+                    dfc = -0.5f * a.pi_over_rc * __builtin_amdgcn_sinf(ang);
                 }
                 // two accumulation chains per product (even and odd steps)
                 f32x4 acc1 = {0.0f, 0.0f, 0.0f, 0.0f}, acc2 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1672,7 +1649,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
                 if constexpr (RAD == kRadRec) {
                     // e_{4 s + g} by the stride-four recurrence, cutoff applied after
                     const float t0 = R - mu_g;
-                    float e = act ? __builtin_amdgcn_exp2f(nef_g * t0 * t0) : 0.0f;
+                    float e = __builtin_amdgcn_exp2f(nef_g * t0 * t0);
                     float rr = __builtin_amdgcn_exp2f(fmaf(ra4, t0, rb4));
 #pragma unroll
                     for (int st = 0; st < KS; ++st) {
@@ -1737,7 +1714,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
                 if (act) {
                     if (gq < 3) {
                         const float gc = gq == 0 ? gx : (gq == 1 ? gy : gz);
-                        atomicAdd(&sF[gq * bg.hmax + slot], to_fixed(-gc));
+                        atomicAdd(&sF[3 * slot + gq], to_fixed(-gc));
                         Fo += gc;
                     } else {
                         virial_add(w6, dx, dy, dz, gx, gy, gz);
@@ -1755,19 +1732,10 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_mfma16(PathArgs a, BlockGeom
         // the centre atom's force: each lane group's sixteen pair columns, fixed order
 #pragma unroll
         for (int off = 1; off < 16; off <<= 1) Fo += __shfl_xor(Fo, off);
-        if (jp == 0 && gq < 3) atomicAdd(&sF[gq * bg.hmax + ip], to_fixed(Fo));
+        if (jp == 0 && gq < 3) atomicAdd(&sF[3 * ip + gq], to_fixed(Fo));
     }
     __syncthreads();
-    for (int hc = wv; hc < nh; hc += kBlock / 64) {
-        const int lo = h_base[hc], cnt = h_base[hc + 1] - lo;
-        for (int k = lane; k < cnt; k += 64) {
-            const int64_t q = h_first[hc] + k;
-            const unsigned long long fx_ = sF[lo + k], fy_ = sF[bg.hmax + lo + k], fz_ = sF[2 * bg.hmax + lo + k];
-            if (fx_) atomicAdd(&bg.F[3 * q + 0], fx_);
-            if (fy_) atomicAdd(&bg.F[3 * q + 1], fy_);
-            if (fz_) atomicAdd(&bg.F[3 * q + 2], fz_);
-        }
-    }
+    flush_forces(bg, nh, h_first, h_base, sF);
     block_virial(Wd, red, a.vir + (int64_t)blockIdx.x * kVirDoubles);
 }
 
@@ -1989,7 +1957,9 @@ BlockedFn pick_blocked_p(int M) {
         case 0: return k_adjoint_blocked<KC, 0, RAD, PAIR2>;
         case 1: return k_adjoint_blocked<KC, 1, RAD, PAIR2>;
         case 2: return k_adjoint_blocked<KC, 2, RAD, PAIR2>;
-        default: return k_adjoint_blocked<KC, 3, RAD, PAIR2>;
+        default:  // M = 3 runs on the matrix cores from K = 8 on
+            if constexpr (KC == 8 || PAIR2) return nullptr;
+            else return k_adjoint_blocked<KC, 3, RAD, PAIR2>;
     }
 }
 // Two chunk lanes per atom happen only with chunks of 6 or 8 (K = 12, 16).
