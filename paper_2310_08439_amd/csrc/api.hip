@@ -289,10 +289,9 @@ size_t eval_workspace_bytes(const tmd_model* m, int64_t n) {
 namespace {
 
 tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys,
-                                const tmd_nlist* nl, const EvalBuffers& b, double* totals7_dev, float* atom_energy,
-                                float* forces, const PruneGate* gate) {
+                                const tmd_nlist* nl, const EvalBuffers& b, double* totals7_dev, double* host_totals,
+                                float* atom_energy, float* forces, const PruneGate* gate) {
     tmd_status st;
-    if ((st = launch_refresh_positions(ctx, sys, nl)) != TMD_OK) return st;
     // A list with a skin carries ~(1 + skin/rc)^3 - 1 more entries than the
     // cutoff needs (60 % for 1 A on 6 A); the descriptor and adjoint loops
     // then run over rows pruned to the cutoff at the current positions.
@@ -300,13 +299,14 @@ tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_
     tmd_nlist pruned;
     if (nl->rlist > m->rcut * (1.0 + 1e-9)) {
         tmd_nlist* mnl = const_cast<tmd_nlist*>(nl);  // the pruned rows are scratch owned by the list
-        st = gate ? launch_prune_gated(ctx, mnl, m->rcut, *gate) : launch_prune(ctx, mnl, m->rcut);
-        if (st != TMD_OK) return st;
+        if ((st = launch_refresh_prune(ctx, sys, mnl, b.Fq, m->rcut, gate)) != TMD_OK) return st;
         pruned = *nl;  // a view: same atoms, cells and work order, pruned rows
         pruned.nbr = nl->pnbr;
         pruned.img = nl->pimg;
         pruned.cnt = nl->pcnt;
         use = &pruned;
+    } else if ((st = launch_refresh_positions(ctx, sys, nl, b.Fq)) != TMD_OK) {
+        return st;
     }
     // a BF16 MLP takes its operand as BF16 descriptors, stored in the first
     // half of the FP32 descriptor buffer
@@ -316,15 +316,16 @@ tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_
     int nvir = 0;
     if ((st = launch_adjoint(ctx, m, use, b.dG, b.P, b.Fq, b.vir, &nvir)) != TMD_OK) return st;
     return launch_finalize(ctx, nl, b.Ei, b.Fq, b.vir, nvir, atom_energy, forces, totals7_dev ? totals7_dev : b.totals,
-                           b.part);
+                           host_totals, b.part);
 }
 
 tmd_status run_energy_forces(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys, const tmd_nlist* nl,
-                             double* totals7_dev, float* atom_energy, float* forces, const PruneGate* gate = nullptr) {
+                             double* totals7_dev, double* host_totals, float* atom_energy, float* forces,
+                             const PruneGate* gate = nullptr) {
     EvalBuffers b;
     tmd_status st = eval_buffers(ctx, m, nl, &b);
     if (st != TMD_OK) return st;
-    return run_energy_forces_in(ctx, m, sys, nl, b, totals7_dev, atom_energy, forces, gate);
+    return run_energy_forces_in(ctx, m, sys, nl, b, totals7_dev, host_totals, atom_energy, forces, gate);
 }
 
 }  // namespace
@@ -349,8 +350,10 @@ tmd_status tmd_context_create(int device, void* hip_stream, tmd_context** out) {
         ctx->num_cus = cus;
     ctx->scratch = scratch_address(device);  // with `device` current
     if (hipHostMalloc((void**)&ctx->h_totals, sizeof(double) * 8, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&ctx->h_flags, sizeof(int32_t) * 64, hipHostMallocDefault) != hipSuccess) {
-        delete ctx;
+        hipHostMalloc((void**)&ctx->h_flags, sizeof(int32_t) * 64, hipHostMallocDefault) != hipSuccess ||
+        hipMalloc((void**)&ctx->d_counter, 256) != hipSuccess || hipMemset(ctx->d_counter, 0, 256) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess) {
+        tmd_context_destroy(ctx);
         return TMD_ERR_OUT_OF_MEMORY;
     }
     *out = ctx;
@@ -365,6 +368,7 @@ void tmd_context_destroy(tmd_context* ctx) {
     ctx->prof.release();
     if (ctx->h_totals) (void)hipHostFree(ctx->h_totals);
     if (ctx->h_flags) (void)hipHostFree(ctx->h_flags);
+    if (ctx->d_counter) (void)hipFree(ctx->d_counter);
     delete ctx;
 }
 
@@ -722,7 +726,7 @@ tmd_status tmd_descriptors(tmd_context* ctx, const tmd_model* m, const tmd_syste
     hipError_t e = hipSuccess;
     float* Gs = (float*)ctx->ws.get("ev.G", sizeof(float) * nl->n * m->F, &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "descriptor workspace");
-    if ((st = launch_refresh_positions(ctx, sys, nl)) != TMD_OK) return st;
+    if ((st = launch_refresh_positions(ctx, sys, nl, nullptr)) != TMD_OK) return st;
     if ((st = launch_descriptors(ctx, m, nl, Gs, nullptr)) != TMD_OK) return st;
     return launch_permute_rows(ctx, nl, Gs, m, G);
 }
@@ -736,8 +740,7 @@ tmd_status tmd_energy_forces(tmd_context* ctx, const tmd_model* m, const tmd_sys
     hipError_t e = hipSuccess;
     double* tot = (double*)ctx->ws.get("ev.totals", sizeof(double) * 8, &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "totals workspace");
-    if ((st = run_energy_forces(ctx, m, sys, nl, tot, atom_energy, forces)) != TMD_OK) return st;
-    TMD_HIP(ctx, hipMemcpyAsync(ctx->h_totals, tot, sizeof(double) * 7, hipMemcpyDeviceToHost, ctx->stream));
+    if ((st = run_energy_forces(ctx, m, sys, nl, tot, ctx->h_totals, atom_energy, forces)) != TMD_OK) return st;
     TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     *energy = ctx->h_totals[0];
     if (virial6)
@@ -751,7 +754,7 @@ tmd_status tmd_energy_forces_async(tmd_context* ctx, const tmd_model* m, const t
     tmd_status st = check_eval(ctx, m, sys, nl);
     if (st != TMD_OK) return st;
     if (!totals7 || !forces) return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "null totals or forces");
-    return run_energy_forces(ctx, m, sys, nl, totals7, atom_energy, forces);
+    return run_energy_forces(ctx, m, sys, nl, totals7, nullptr, atom_energy, forces);
 }
 
 tmd_status tmd_energy_forces_batch(tmd_context* ctx, const tmd_model* m, int32_t n_systems,
@@ -826,7 +829,7 @@ tmd_status tmd_energy_forces_batch(tmd_context* ctx, const tmd_model* m, int32_t
     // pageable source: the copy is staged before the call returns
     TMD_HIP(ctx, hipMemcpyAsync(dsegs, segs.data(), sizeof(BatchSeg) * segs.size(), hipMemcpyHostToDevice,
                                 ctx->stream));
-    if ((st = launch_batch_merge(ctx, dsegs, n_systems, &v, boxes)) != TMD_OK) return st;
+    if ((st = launch_batch_merge(ctx, dsegs, n_systems, &v, boxes, b.Fq)) != TMD_OK) return st;
     uint16_t* Gb = m->prec == TMD_BF16_MLP ? reinterpret_cast<uint16_t*>(b.G) : nullptr;
     if ((st = launch_descriptors(ctx, m, &v, b.G, b.P, Gb)) != TMD_OK) return st;
     if ((st = launch_mlp(ctx, m, species_groups(&v), m->prec, b.G, Gb, b.Ei, b.dG)) != TMD_OK) return st;
@@ -856,7 +859,7 @@ tmd_status tmd_energy_forces_noalloc(tmd_context* ctx, const tmd_model* m, const
     // per-kernel timing would create events; it is suspended for this call
     const bool prof = ctx->prof.on;
     ctx->prof.on = false;
-    st = run_energy_forces_in(ctx, m, sys, nl, b, totals7, atom_energy, forces, nullptr);
+    st = run_energy_forces_in(ctx, m, sys, nl, b, totals7, nullptr, atom_energy, forces, nullptr);
     ctx->prof.on = prof;
     return st;
 }
@@ -873,7 +876,7 @@ tmd_status energy_forces_gated(tmd_context* ctx, const tmd_model* m, const tmd_s
     tmd_status st = check_eval(ctx, m, sys, nl);
     if (st != TMD_OK) return st;
     if (!totals7 || !forces) return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "null totals or forces");
-    return run_energy_forces(ctx, m, sys, nl, totals7, atom_energy, forces, gate);
+    return run_energy_forces(ctx, m, sys, nl, totals7, nullptr, atom_energy, forces, gate);
 }
 
 }  // namespace tmd

@@ -44,9 +44,11 @@ __device__ __forceinline__ int find_segment(const BatchSeg* __restrict__ segs, i
 // Padding atoms get no rows.
 __global__ void k_batch_merge(const BatchSeg* __restrict__ segs, int nseg, int64_t N, int S, int cap,
                               double4* __restrict__ xs, double4* __restrict__ boxes, int32_t* __restrict__ nbr,
-                              int32_t* __restrict__ img, int32_t* __restrict__ cnt) {
+                              int32_t* __restrict__ img, int32_t* __restrict__ cnt,
+                              unsigned long long* __restrict__ Fq) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= N) return;
+    Fq[3 * g] = Fq[3 * g + 1] = Fq[3 * g + 2] = 0ull;
     const BatchSeg& sg = segs[find_segment(segs, nseg, g)];
     const int64_t p = g - sg.off;
     if (p >= sg.n) {
@@ -144,11 +146,12 @@ unsigned grid_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, tmd_nlist* vnl, double4* boxes) {
+tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, tmd_nlist* vnl, double4* boxes,
+                              unsigned long long* Fq) {
     {
         ProfScope ps_(ctx, "batch_merge");
         k_batch_merge<<<grid_of(vnl->n), kBlock, 0, ctx->stream>>>(segs, nseg, vnl->n, vnl->S, vnl->cap, vnl->xs, boxes,
-                                                                    vnl->nbr, vnl->img, vnl->cnt);
+                                                                    vnl->nbr, vnl->img, vnl->cnt, Fq);
         k_batch_species<<<grid_of(vnl->n), kBlock, 0, ctx->stream>>>(segs, nseg, vnl->n, vnl->S, vnl->sp_idx);
     }
     TMD_HIP(ctx, hipGetLastError());

@@ -1769,7 +1769,23 @@ __device__ __forceinline__ int block_cell(const WorkGeom& g, int x0, int y0, int
     return (cz * g.nc[1] + cy) * g.nc[0] + cx;
 }
 
-// Atoms per block: one wave per block, lanes over its cells.
+// Atoms of block q (runs of cells along x).
+__device__ __forceinline__ int block_atoms(const WorkGeom& g, int64_t q) {
+    int x0, y0, z0;
+    block_origin(g, q, x0, y0, z0);
+    const int x1 = min(x0 + g.B[0], g.nc[0]), y1 = min(y0 + g.B[1], g.nc[1]), z1 = min(z0 + g.B[2], g.nc[2]);
+    int c = 0;
+#pragma unroll 8
+    for (int r = 0; r < g.B[1] * g.B[2]; ++r) {  // (unrolled so that the rows' loads are in flight together)
+        const int y = y0 + r % g.B[1], z = z0 + r / g.B[1];
+        const int row = (min(z, z1 - 1) * g.nc[1] + min(y, y1 - 1)) * g.nc[0];
+        const int in = g.cellstart[row + x1] - g.cellstart[row + x0];
+        c += y < y1 && z < z1 ? in : 0;
+    }
+    return c;
+}
+
+// The same for many blocks: one wave per block, lanes over its cells.
 __global__ void k_wo_count(WorkGeom g, int64_t nblocks, int32_t* __restrict__ count) {
     const int lane = threadIdx.x & 63;
     const int64_t blk = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
@@ -1786,8 +1802,10 @@ __global__ void k_wo_count(WorkGeom g, int64_t nblocks, int32_t* __restrict__ co
 }
 
 // Exclusive scan of the block counts by one workgroup of 1024 threads;
-// base[nblocks] = n.
-__global__ void __launch_bounds__(1024) k_wo_scan(int64_t nblocks, const int32_t* __restrict__ count,
+// base[nblocks] = n.  Up to kScanBlocks blocks it counts them as well (one
+// launch of 2 to 5 us less); more would leave the counting to one CU.
+constexpr int64_t kScanBlocks = 1024;
+__global__ void __launch_bounds__(1024) k_wo_scan(WorkGeom g, int64_t nblocks, const int32_t* __restrict__ count,
                                                   int32_t* __restrict__ base) {
     // base[0 .. nblocks] = exclusive scan of the counts (first work slots),
     // base[nblocks + 1 ..] = exclusive scan of ceil(count / 16) (first groups)
@@ -1797,7 +1815,7 @@ __global__ void __launch_bounds__(1024) k_wo_scan(int64_t nblocks, const int32_t
     int32_t* gb = base + nblocks + 1;
     for (int64_t b0 = 0; b0 < nblocks; b0 += 1024) {
         const int64_t q = b0 + t;
-        const int32_t c = q < nblocks ? count[q] : 0;
+        const int32_t c = q < nblocks ? (count ? count[q] : block_atoms(g, q)) : 0;
         const int32_t v[2] = {c, (c + 15) >> 4};
         int32_t x[2] = {v[0], v[1]};
         for (int off = 1; off < 64; off <<= 1) {
@@ -1915,11 +1933,6 @@ __global__ void __launch_bounds__(256) k_wo_order(WorkGeom g, int cap, const int
         }
         __syncthreads();  // hist and whist are reused by the next round
     }
-}
-
-__global__ void k_zero(unsigned long long* __restrict__ p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
 }
 
 using PathFn = void (*)(PathArgs, int64_t);
@@ -2193,7 +2206,7 @@ tmd_status launch_work_order(tmd_context* ctx, tmd_nlist* nl) {
         nl->wbase_cap = 2 * (nblocks + 1);
     }
     hipError_t e = hipSuccess;
-    int32_t* count = (int32_t*)ctx->ws.get("wo.count", sizeof(int32_t) * nblocks, &e);
+    int32_t* count = nblocks > kScanBlocks ? (int32_t*)ctx->ws.get("wo.count", sizeof(int32_t) * nblocks, &e) : nullptr;
     if (e != hipSuccess) return hip_fail(ctx, e, "work order workspace");
     WorkGeom g{};
     for (int d = 0; d < 3; ++d) {
@@ -2210,9 +2223,10 @@ tmd_status launch_work_order(tmd_context* ctx, tmd_nlist* nl) {
     if (lds > kWoOrderMaxLds) return TMD_OK;
     {
         ProfScope ps_(ctx, "work_order");
-        k_wo_count<<<(unsigned)((nblocks + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, ctx->stream>>>(g, nblocks,
-                                                                                                   count);
-        k_wo_scan<<<1, 1024, 0, ctx->stream>>>(nblocks, count, nl->wbase);
+        if (count)
+            k_wo_count<<<(unsigned)((nblocks + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, ctx->stream>>>(
+                g, nblocks, count);
+        k_wo_scan<<<1, 1024, 0, ctx->stream>>>(g, nblocks, count, nl->wbase);
         k_wo_order<<<(unsigned)nblocks, kBlock, lds, ctx->stream>>>(g, nl->cap, nl->wbase, nl->wperm, nl->wcell);
     }
     TMD_HIP(ctx, hipGetLastError());
@@ -2278,9 +2292,6 @@ tmd_status launch_adjoint(tmd_context* ctx, const tmd_model* m, const tmd_nlist*
     a.dG = dG;
     a.Pbuf = Pbuf;
     a.vir = vir_partials;
-    // zeroed by a kernel rather than a memset, so that the sequence can be
-    // captured into a graph and replayed
-    k_zero<<<(unsigned)((3 * nl->n + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(Fsorted, 3 * nl->n);
     if (nl->wo_valid) {
         BlockGeom bg = wo_geom(nl);
         bg.F = Fsorted;

@@ -51,7 +51,7 @@ struct GridArgs {
 __global__ void k_bin(int64_t n, const double* __restrict__ pos, const int32_t* __restrict__ species, int S,
                       GridArgs g, double* __restrict__ wpos, int32_t* __restrict__ cell_of,
                       int32_t* __restrict__ cell_rank, int32_t* __restrict__ cellcount,
-                      int32_t* __restrict__ flags) {
+                      int32_t* __restrict__ cellsp, int64_t ncells, int32_t* __restrict__ flags) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int c[3];
@@ -65,8 +65,9 @@ __global__ void k_bin(int64_t n, const double* __restrict__ pos, const int32_t* 
     }
     if (bad) atomicOr(&flags[0], kErrNonFinite);
     int s = species[i];
-    if (s < 0 || s >= S) atomicOr(&flags[0], kErrSpecies);
     int cell = (c[2] * g.nc[1] + c[1]) * g.nc[0] + c[0];
+    if (s < 0 || s >= S) atomicOr(&flags[0], kErrSpecies);
+    else if (cellsp) atomicAdd(&cellsp[s * ncells + cell], 1);
     cell_of[i] = cell;
     // Arrival order in the cell (k_sort_gather fixes the order).  Consecutive
     // lanes in one cell (atoms in lattice or trajectory order) form a run that
@@ -162,6 +163,83 @@ __global__ void k_scan_add(int64_t ncells, const int32_t* __restrict__ tile_off,
     if (q == ncells) start[q] = tile_off[(ncells + 1023) >> 10];
 }
 
+// Up to kScanCells cells (about 230,000 atoms) are scanned by one workgroup in
+// one launch, sixteen consecutive cells per thread, species by species as
+// well: cellstart = exclusive scan of the counts, and (several species) cellsp
+// in place = first slot of the cell's species-s atoms in the species grouping.
+// It replaces six launches of 2 to 4 us each (three for the cell starts, three
+// for the grouping), which larger grids still take because one workgroup would
+// then be slower.
+constexpr int kScanCells = 16384;
+__global__ void __launch_bounds__(1024) k_scan_cells(int ncells, int S, const int32_t* __restrict__ count,
+                                                     int32_t* __restrict__ start, int32_t* __restrict__ cellsp,
+                                                     int32_t* __restrict__ flags) {
+    __shared__ int32_t wsum[16], wmax[16];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    constexpr int E = kScanCells / 1024;
+    const int per = (ncells + 1023) / 1024, q0 = t * per;  // per <= E
+    int32_t v[E];
+    // exclusive scan of v over the threads; returns the total
+    auto scan = [&](int32_t first) {
+        int32_t x = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) x += v[e];
+        const int32_t own = x;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) wsum[wv] = x;
+        __syncthreads();
+        int32_t pre = first, tot = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int32_t sw = wsum[w];
+            pre += (w < wv) ? sw : 0;
+            tot += sw;
+        }
+        __syncthreads();
+        x += pre - own;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t c = v[e];
+            v[e] = x;
+            x += c;
+        }
+        return tot;
+    };
+    int32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        v[e] = e < per && q0 + e < ncells ? count[q0 + e] : 0;
+        m = max(m, v[e]);
+    }
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    if (lane == 0) wmax[wv] = m;
+    const int32_t n = scan(0);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e < per && q0 + e < ncells) start[q0 + e] = v[e];
+    if (t == 0) {
+        start[ncells] = n;
+        for (int w = 1; w < 16; ++w) m = max(m, wmax[w]);
+        flags[4] = m;
+        if (S == 1) flags[8] = n;
+    }
+    int32_t first = 0;
+    for (int s = 0; s < S && cellsp; ++s) {
+        int32_t* c = cellsp + (int64_t)s * ncells;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = e < per && q0 + e < ncells ? c[q0 + e] : 0;
+        const int32_t tot = scan(first);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e < per && q0 + e < ncells) c[q0 + e] = v[e];
+        if (t == 0) flags[8 + s] = tot;
+        first += tot;
+    }
+}
+
 // Per-species exclusive scans over the per-block species counts; the totals
 // go to spcount[s] for the host.
 __global__ void __launch_bounds__(1024) k_species_scan(int64_t nblk, int S, const int32_t* __restrict__ blkcnt,
@@ -174,9 +252,72 @@ __global__ void __launch_bounds__(1024) k_species_scan(int64_t nblk, int S, cons
     }
 }
 
-__global__ void k_place(int64_t n, const int32_t* __restrict__ cell_of, const int32_t* __restrict__ cell_rank,
-                        const int32_t* __restrict__ start, int32_t* __restrict__ order) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline int floor_div(int a, int b) {
+    int q = a / b;
+    return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
+}
+
+// Largest atom count of a cell block of B0 x B1 x B2 cells plus its one-cell
+// periodic halo, for the three shapes h, into out[0 .. 2]: waves of the launch's
+// first h.groups workgroups stride over the blocks (lanes over a block's halo
+// cells); three atomics per workgroup.
+constexpr int kHaloMaxGroups = 256;
+struct HaloArgs {
+    int groups;  // 0: not counted
+    int3 shape[3];
+    int64_t blocks[3];
+};
+__device__ __forceinline__ void halo_max(const GridArgs& g, const HaloArgs& h, const int32_t* __restrict__ start,
+                                         int32_t* __restrict__ out) {
+    __shared__ int32_t wmax[3][kBlock / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // largest atom count of one block of shape S plus its one-cell halo
+    auto largest = [&](int3 S, int64_t nblocks) {
+        const int nb0 = (g.nc[0] + S.x - 1) / S.x, nb1 = (g.nc[1] + S.y - 1) / S.y;
+        const int HX = S.x + 2, HY = S.y + 2, nh = HX * HY * (S.z + 2);
+        int best = 0;
+        for (int64_t blk = (int64_t)blockIdx.x * (kBlock / 64) + wv; blk < nblocks;
+             blk += (int64_t)h.groups * (kBlock / 64)) {
+            const int x0 = (int)(blk % nb0) * S.x, y0 = (int)((blk / nb0) % nb1) * S.y,
+                      z0 = (int)(blk / ((int64_t)nb0 * nb1)) * S.z;
+            int c = 0;
+            for (int h = lane; h < nh; h += 64) {
+                const int x = x0 - 1 + h % HX, y = y0 - 1 + (h / HX) % HY, z = z0 - 1 + h / (HX * HY);
+                const int wx = x - floor_div(x, g.nc[0]) * g.nc[0];
+                const int wy = y - floor_div(y, g.nc[1]) * g.nc[1];
+                const int wz = z - floor_div(z, g.nc[2]) * g.nc[2];
+                const int cell = (wz * g.nc[1] + wy) * g.nc[0] + wx;
+                c += start[cell + 1] - start[cell];
+            }
+            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+            best = max(best, c);
+        }
+        return best;
+    };
+    for (int q = 0; q < 3; ++q) {
+        const int best = largest(h.shape[q], h.blocks[q]);
+        if (lane == 0) wmax[q][wv] = best;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        int m = wmax[threadIdx.x][0];
+        for (int w = 1; w < kBlock / 64; ++w) m = max(m, wmax[threadIdx.x][w]);
+        atomicMax(out + threadIdx.x, m);
+    }
+}
+
+// Atoms into their cells, in the order the bin atomics gave (k_sort_gather
+// fixes it).  The halo counts need the cell starts and nothing else, so they
+// share the launch: its first workgroups take them, the others the atoms.
+__global__ void __launch_bounds__(256) k_place(int64_t n, const int32_t* __restrict__ cell_of,
+                                               const int32_t* __restrict__ cell_rank,
+                                               const int32_t* __restrict__ start, int32_t* __restrict__ order,
+                                               GridArgs g, HaloArgs h, int32_t* __restrict__ halo_out) {
+    if ((int)blockIdx.x < h.groups) {
+        halo_max(g, h, start, halo_out);
+        return;
+    }
+    const int64_t i = (int64_t)(blockIdx.x - h.groups) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     order[start[cell_of[i]] + cell_rank[i]] = (int32_t)i;
 }
@@ -185,7 +326,10 @@ __global__ void k_place(int64_t n, const int32_t* __restrict__ cell_of, const in
 // cell's atoms (in the arbitrary order the atomic placement left) are ranked by
 // original index, which fixes a deterministic order, and each atom's wrapped
 // position, image shift, species and cell are gathered straight to its sorted
-// slot start[cell] + rank.  Fuller cells take several rounds of 16.
+// slot start[cell] + rank.  Fuller cells take several rounds of 16.  With
+// sp_idx, each atom also goes to its place in the species grouping: the cell's
+// first slot of its species (cellsp, several species) plus its rank among the
+// cell's atoms of that species.
 constexpr int kSortLanes = 16;
 __global__ void __launch_bounds__(256) k_sort_gather(int64_t ncells, const int32_t* __restrict__ start,
                                                      const int32_t* __restrict__ order, const double* __restrict__ wpos,
@@ -193,7 +337,9 @@ __global__ void __launch_bounds__(256) k_sort_gather(int64_t ncells, const int32
                                                      const int32_t* __restrict__ species, GridArgs g,
                                                      int32_t* __restrict__ perm, int32_t* __restrict__ shift,
                                                      double4* __restrict__ xs, int32_t* __restrict__ sp,
-                                                     int32_t* __restrict__ cell_sorted) {
+                                                     int32_t* __restrict__ cell_sorted, int S,
+                                                     const int32_t* __restrict__ cellsp,
+                                                     int32_t* __restrict__ sp_idx) {
     const int lane = threadIdx.x % kSortLanes;
     const int64_t cell = (int64_t)blockIdx.x * (kBlock / kSortLanes) + threadIdx.x / kSortLanes;
     if (cell >= ncells) return;  // whole group
@@ -201,11 +347,18 @@ __global__ void __launch_bounds__(256) k_sort_gather(int64_t ncells, const int32
     for (int k0 = 0; k0 < m; k0 += kSortLanes) {
         const int k = k0 + lane;
         const int32_t v = k < m ? order[lo + k] : INT32_MAX;
-        int r = 0;  // entries of the cell with a smaller original index
+        const int32_t sv = k < m ? species[v] : -1;
+        int r = 0, rs = 0;  // entries of the cell with a smaller original index, and of those the same species
         for (int j0 = 0; j0 < m; j0 += kSortLanes) {
             const int32_t vj = j0 + lane < m ? order[lo + j0 + lane] : INT32_MAX;
+            const int32_t sj = cellsp && j0 + lane < m ? species[vj] : -1;
             const int nj = min(kSortLanes, m - j0);
-            for (int t = 0; t < nj; ++t) r += __shfl(vj, t, kSortLanes) < v ? 1 : 0;
+            for (int t = 0; t < nj; ++t) {
+                const bool less = __shfl(vj, t, kSortLanes) < v;
+                const bool same = __shfl(sj, t, kSortLanes) == sv;  // (outside any branch: every lane is read)
+                r += less ? 1 : 0;
+                rs += (less & same) ? 1 : 0;
+            }
         }
         if (k < m) {
             const int64_t p = lo + r;
@@ -219,8 +372,10 @@ __global__ void __launch_bounds__(256) k_sort_gather(int64_t ncells, const int32
                 shift[3 * p + a] = (int32_t)kk;
             }
             xs[p] = make_double4(w[0], w[1], w[2], 0.0);
-            sp[p] = species[i];
+            sp[p] = sv;
             cell_sorted[p] = (int32_t)cell;
+            // (an invalid species fails the build on the host; it is not placed)
+            if (sp_idx && sv >= 0 && sv < S) sp_idx[cellsp ? cellsp[sv * ncells + cell] + rs : p] = (int32_t)p;
         }
     }
 }
@@ -328,16 +483,21 @@ __global__ void __launch_bounds__(256) k_prune(int64_t n, int S, int cap, double
     }
 }
 
-// One thread: does this evaluation need new pruned rows (see PruneGate)?
-__global__ void k_prune_gate(const unsigned long long* __restrict__ maxd2, double* __restrict__ state,
-                             int32_t* __restrict__ flag, int force, double half_margin) {
-    if (threadIdx.x != 0) return;
-    const double d = sqrt(__longlong_as_double((long long)maxd2[0]));
-    if (force || !(d + state[0] < half_margin)) {
-        flag[0] = 1;
-        state[0] = force ? 0.0 : d;  // a forced prune follows a build: no displacement yet
+// Does this evaluation need new pruned rows (see PruneGate)?  One thread.
+struct GateArgs {
+    const unsigned long long* maxd2;
+    double* state;
+    int32_t* flag;  // nullptr: no gate
+    int force;
+    double half_margin;
+};
+__device__ __forceinline__ void prune_gate(const GateArgs& g) {
+    const double d = sqrt(__longlong_as_double((long long)g.maxd2[0]));
+    if (g.force || !(d + g.state[0] < g.half_margin)) {
+        g.flag[0] = 1;
+        g.state[0] = g.force ? 0.0 : d;  // a forced prune follows a build: no displacement yet
     } else {
-        flag[0] = 0;
+        g.flag[0] = 0;
     }
 }
 
@@ -375,60 +535,19 @@ struct FillArgs {
     int32_t* img;
     int32_t* cnt;
     int32_t* flags;
+    int32_t* host;     // pinned host copy of the flags (publish_flags)
     bool narrow;       // 3x3x3 stencil: entries record their stencil offset code
 };
 
-__device__ inline int floor_div(int a, int b) {
-    int q = a / b;
-    return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
+// What the host needs after a build goes straight to pinned host memory, so
+// that no copy follows the fill: its first workgroup stores what the earlier
+// launches left in flags (errors of the input in [0], counts from [4] on), and
+// a fill that fails stores a mark in host[3], upon which the host reads flags
+// itself.
+__device__ __forceinline__ void publish_flags(const FillArgs& a) {
+    if (blockIdx.x == 0 && threadIdx.x < 16 && threadIdx.x != 3) a.host[threadIdx.x] = a.flags[threadIdx.x];
 }
-
-// Largest atom count of a cell block of B0 x B1 x B2 cells plus its one-cell
-// periodic halo into *out: waves stride over the blocks (lanes over a block's
-// halo cells); one atomic per workgroup.
-constexpr int kHaloMaxGroups = 256;
-__global__ void __launch_bounds__(256) k_halo_max(GridArgs g, int3 A, int64_t nbA, int3 B, int64_t nbB, int3 C,
-                                                  int64_t nbC, const int32_t* __restrict__ start,
-                                                  int32_t* __restrict__ out) {
-    __shared__ int32_t wmax[3][kBlock / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // largest atom count of one block of shape S plus its one-cell halo
-    auto largest = [&](int3 S, int64_t nblocks) {
-        const int nb0 = (g.nc[0] + S.x - 1) / S.x, nb1 = (g.nc[1] + S.y - 1) / S.y;
-        const int HX = S.x + 2, HY = S.y + 2, nh = HX * HY * (S.z + 2);
-        int best = 0;
-        for (int64_t blk = (int64_t)blockIdx.x * (kBlock / 64) + wv; blk < nblocks;
-             blk += (int64_t)gridDim.x * (kBlock / 64)) {
-            const int x0 = (int)(blk % nb0) * S.x, y0 = (int)((blk / nb0) % nb1) * S.y,
-                      z0 = (int)(blk / ((int64_t)nb0 * nb1)) * S.z;
-            int c = 0;
-            for (int h = lane; h < nh; h += 64) {
-                const int x = x0 - 1 + h % HX, y = y0 - 1 + (h / HX) % HY, z = z0 - 1 + h / (HX * HY);
-                const int wx = x - floor_div(x, g.nc[0]) * g.nc[0];
-                const int wy = y - floor_div(y, g.nc[1]) * g.nc[1];
-                const int wz = z - floor_div(z, g.nc[2]) * g.nc[2];
-                const int cell = (wz * g.nc[1] + wy) * g.nc[0] + wx;
-                c += start[cell + 1] - start[cell];
-            }
-            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-            best = max(best, c);
-        }
-        return best;
-    };
-    const int bestA = largest(A, nbA), bestB = largest(B, nbB), bestC = largest(C, nbC);
-    if (lane == 0) {
-        wmax[0][wv] = bestA;
-        wmax[1][wv] = bestB;
-        wmax[2][wv] = bestC;
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {  // out[0 .. 2]: shapes A, B, C
-        int m = wmax[threadIdx.x][0];
-        for (int w = 1; w < kBlock / 64; ++w) m = max(m, wmax[threadIdx.x][w]);
-        atomicMax(out + threadIdx.x, m);
-    }
-}
-
+__device__ __forceinline__ void fill_failed(const FillArgs& a) { a.host[3] = 1; }
 
 // Systems of at most this many atoms have every workgroup of k_fill stage all
 // positions in LDS (32 KB): their cells are few and crowded, so each thread
@@ -443,6 +562,7 @@ constexpr int kFillLdsAtoms = 1024;
 template <bool kLds>
 __global__ void __launch_bounds__(256) k_fill(FillArgs a) {
     __shared__ double4 xs_lds[kLds ? kFillLdsAtoms : 1];
+    publish_flags(a);
     if constexpr (kLds) {
         for (int64_t i = threadIdx.x; i < a.n; i += blockDim.x) xs_lds[i] = a.xs[i];
         __syncthreads();
@@ -527,6 +647,7 @@ __global__ void __launch_bounds__(256) k_fill(FillArgs a) {
     }
     if (mx > a.cap) atomicMax(&a.flags[1], mx);
     if (coincident) atomicOr(&a.flags[0], kErrCoincident);
+    if (mx > a.cap || coincident) fill_failed(a);
 }
 
 constexpr int kMaxCellAtoms = 64;
@@ -551,6 +672,7 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells) 
     __shared__ double s_xi[kBlock / 64][3][kMaxCellAtoms];
     __shared__ int32_t s_len[kBlock / 64][kMaxCellAtoms][SMAX];  // running row lengths
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    publish_flags(a);
     const int64_t cell = (int64_t)blockIdx.x * (kBlock / 64) + wv;
     if (cell >= ncells) return;  // whole wave
     const GridArgs& g = a.g;
@@ -558,11 +680,14 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells) 
               cz = (int)(cell / ((int64_t)g.nc[0] * g.nc[1]));
     const int a0 = __builtin_amdgcn_readfirstlane(a.cellstart[cell]);
     const int natoms = __builtin_amdgcn_readfirstlane(a.cellstart[cell + 1]) - a0;
-    if (natoms == 0) return;  // nothing to list (and a0 may equal n)
     if (natoms > kMaxCellAtoms) {  // the host reruns the build with k_fill
-        if (lane == 0) atomicOr(&a.flags[2], 1);
+        if (lane == 0) {
+            atomicOr(&a.flags[2], 1);
+            fill_failed(a);
+        }
         return;
     }
+    if (natoms == 0) return;  // nothing to list (and a0 may equal n)
     const int rx = NARROW ? 1 : g.reach[0], ry = NARROW ? 1 : g.reach[1], rz = NARROW ? 1 : g.reach[2];
     const int wx = 2 * rx + 1, wy = 2 * ry + 1, wz = 2 * rz + 1;
     const int ns = wx * wy * wz;
@@ -593,7 +718,10 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells) 
     const int total = __shfl(pre, 63);
     pre -= count;  // exclusive
     if (total > kMaxCandidates) {  // the host reruns the build with k_fill
-        if (lane == 0) atomicOr(&a.flags[2], 1);
+        if (lane == 0) {
+            atomicOr(&a.flags[2], 1);
+            fill_failed(a);
+        }
         return;
     }
     // candidate -> stencil cell table: stencil cell s owns candidates [pre_s, pre_s + count_s)
@@ -692,6 +820,7 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells) 
     }
     if (mx > a.cap) atomicMax(&a.flags[1], mx);
     if (coincident) atomicOr(&a.flags[0], kErrCoincident);
+    if (mx > a.cap || coincident) fill_failed(a);
 }
 
 // Atoms grouped by species in sorted order, without atomics: block offsets
@@ -747,16 +876,21 @@ __global__ void k_export(int64_t n, int S, int cap, const int32_t* __restrict__ 
     }
 }
 
+// Sorted positions from the caller's, and in the same launch what else an
+// evaluation needs before its kernels (each of which was a launch of a few
+// microseconds): the force accumulators cleared, and the prune decision.
 __global__ void k_refresh(int64_t n, const double* __restrict__ pos, const int32_t* __restrict__ perm,
                           const int32_t* __restrict__ shift, double L0, double L1, double L2,
-                          double4* __restrict__ xs) {
+                          double4* __restrict__ xs, unsigned long long* __restrict__ zero, GateArgs gate) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p == 0 && gate.flag) prune_gate(gate);
     if (p >= n) return;
     const int64_t i = perm[p];
     const double x = pos[3 * i] + (double)shift[3 * p] * L0;
     const double y = pos[3 * i + 1] + (double)shift[3 * p + 1] * L1;
     const double z = pos[3 * i + 2] + (double)shift[3 * p + 2] * L2;
     xs[p] = make_double4(x, y, z, 0.0);
+    if (zero) zero[3 * p] = zero[3 * p + 1] = zero[3 * p + 2] = 0ull;
 }
 
 // Sum and maximum of the row counts: grid-stride, one pair of atomics per
@@ -841,66 +975,81 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
     int32_t* cell_of = (int32_t*)ctx->ws.get("nb.cell_of", sizeof(int32_t) * n, &e);
     int32_t* cell_sorted = (int32_t*)ctx->ws.get("nb.cell_sorted", sizeof(int32_t) * n, &e);
     int32_t* order = (int32_t*)ctx->ws.get("nb.order", sizeof(int32_t) * n, &e);
-    int32_t* cellcount = (int32_t*)ctx->ws.get("nb.cellcount", sizeof(int32_t) * (ncells + 1), &e);
-    int32_t* tiles = (int32_t*)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((ncells + 1023) / 1024 + 1), &e);
+    // the flags, the cell counts and (small grids of several species) the
+    // species counts of the cells, cleared together
+    const bool small_grid = ncells <= kScanCells;
+    const int64_t nsp = small_grid && nl->S > 1 ? nl->S * ncells : 0;
+    int32_t* flags = (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + ncells + 1 + nsp), &e);
     int32_t* cell_rank = (int32_t*)ctx->ws.get("nb.cell_rank", sizeof(int32_t) * n, &e);
-    int32_t* blkcnt = (int32_t*)ctx->ws.get("nb.blkcnt", sizeof(int32_t) * kMaxSpecies * nblk, &e);
-    int32_t* blkoff = (int32_t*)ctx->ws.get("nb.blkoff", sizeof(int32_t) * kMaxSpecies * (nblk + 1), &e);
-    int32_t* flags = (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * 64, &e);
+    int32_t *tiles = nullptr, *blkcnt = nullptr, *blkoff = nullptr;
+    if (!small_grid) {
+        tiles = (int32_t*)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((ncells + 1023) / 1024 + 1), &e);
+        blkcnt = (int32_t*)ctx->ws.get("nb.blkcnt", sizeof(int32_t) * kMaxSpecies * nblk, &e);
+        blkoff = (int32_t*)ctx->ws.get("nb.blkoff", sizeof(int32_t) * kMaxSpecies * (nblk + 1), &e);
+    }
     if (e != hipSuccess) return hip_fail(ctx, e, "neighbour workspace allocation");
     hipStream_t st = ctx->stream;
+    int32_t* cellcount = flags + 64;
+    int32_t* cellsp = nsp ? cellcount + ncells + 1 : nullptr;
     int32_t* spcount = flags + 8;
-    TMD_HIP(ctx, hipMemsetAsync(cellcount, 0, sizeof(int32_t) * (ncells + 1), st));
-    TMD_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * 64, st));
+    TMD_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * (size_t)(64 + ncells + 1 + nsp), st));
+    for (int q = 0; q < 16; ++q) ctx->h_flags[q] = 0;
 
     {
         ProfScope ps_(ctx, "nb_bin");
         k_bin<<<grid_for(n), kBlock, 0, st>>>(n, sys->pos, sys->species, nl->S, g, wpos, cell_of, cell_rank,
-                                               cellcount, flags);
+                                               cellcount, cellsp, ncells, flags);
     }
     {
         ProfScope ps_(ctx, "nb_scan");
-        const int64_t ntiles = (ncells + 1023) / 1024;
-        k_scan_tiles<<<(unsigned)ntiles, 1024, 0, st>>>(ncells, cellcount, cellstart, tiles, flags + 4);
-        k_scan_tile_sums<<<1, 1024, 0, st>>>(ntiles, tiles);
-        k_scan_add<<<grid_for(ncells + 1), kBlock, 0, st>>>(ncells, tiles, cellstart);
+        if (small_grid) {
+            k_scan_cells<<<1, 1024, 0, st>>>((int)ncells, nl->S, cellcount, cellstart, cellsp, flags);
+        } else {
+            const int64_t ntiles = (ncells + 1023) / 1024;
+            k_scan_tiles<<<(unsigned)ntiles, 1024, 0, st>>>(ncells, cellcount, cellstart, tiles, flags + 4);
+            k_scan_tile_sums<<<1, 1024, 0, st>>>(ntiles, tiles);
+            k_scan_add<<<grid_for(ncells + 1), kBlock, 0, st>>>(ncells, tiles, cellstart);
+        }
     }
+    HaloArgs ha{};
     if (narrow) {
         // the block shapes the work order prefers, clamped to the grid
-        auto shape = [&](const int* B) {
-            return make_int3(std::min(B[0], g.nc[0]), std::min(B[1], g.nc[1]), std::min(B[2], g.nc[2]));
-        };
-        auto count = [&](int3 S) {
-            return (int64_t)((g.nc[0] + S.x - 1) / S.x) * ((g.nc[1] + S.y - 1) / S.y) * ((g.nc[2] + S.z - 1) / S.z);
-        };
-        const int3 A = shape(kBlockShape), B = shape(kBlockShape2), C = shape(kBlockShape3);
-        const int64_t nbA = count(A), nbB = count(B), nbC = count(C);
-        ProfScope ps_(ctx, "nb_halo_max");
-        const int64_t groups =
-            std::min<int64_t>(kHaloMaxGroups, (std::max({nbA, nbB, nbC}) + kBlock / 64 - 1) / (kBlock / 64));
-        k_halo_max<<<(unsigned)groups, kBlock, 0, st>>>(g, A, nbA, B, nbB, C, nbC, cellstart, flags + 5);
+        const int* shapes[3] = {kBlockShape, kBlockShape2, kBlockShape3};
+        int64_t most = 1;
+        for (int q = 0; q < 3; ++q) {
+            const int3 S = make_int3(std::min(shapes[q][0], g.nc[0]), std::min(shapes[q][1], g.nc[1]),
+                                     std::min(shapes[q][2], g.nc[2]));
+            ha.shape[q] = S;
+            ha.blocks[q] =
+                (int64_t)((g.nc[0] + S.x - 1) / S.x) * ((g.nc[1] + S.y - 1) / S.y) * ((g.nc[2] + S.z - 1) / S.z);
+            most = std::max(most, ha.blocks[q]);
+        }
+        ha.groups = (int)std::min<int64_t>(kHaloMaxGroups, (most + kBlock / 64 - 1) / (kBlock / 64));
     }
     {
         ProfScope ps_(ctx, "nb_place");
-        k_place<<<grid_for(n), kBlock, 0, st>>>(n, cell_of, cell_rank, cellstart, order);
+        k_place<<<(unsigned)ha.groups + grid_for(n), kBlock, 0, st>>>(n, cell_of, cell_rank, cellstart, order, g, ha,
+                                                                      flags + 5);
     }
     {
         ProfScope ps_(ctx, "nb_sort");
         k_sort_gather<<<(unsigned)((ncells + kBlock / kSortLanes - 1) / (kBlock / kSortLanes)), kBlock, 0, st>>>(
             ncells, cellstart, order, wpos, sys->pos, sys->species, g, nl->perm, nl->shift, nl->xs, nl->sp,
-            cell_sorted);
+            cell_sorted, nl->S, cellsp, small_grid ? nl->sp_idx : nullptr);
     }
-    {
-        ProfScope ps_(ctx, "nb_species_blocks");
-        k_species_blocks<<<grid_for(n), kBlock, 0, st>>>(n, nl->sp, blkcnt);
-    }
-    {
-        ProfScope ps_(ctx, "nb_species_scan");
-        k_species_scan<<<1, 1024, 0, st>>>(nblk, nl->S, blkcnt, blkoff, spcount);
-    }
-    {
-        ProfScope ps_(ctx, "nb_species");
-        k_species_place<<<grid_for(n), kBlock, 0, st>>>(n, nl->S, nl->sp, spcount, blkoff, nl->sp_idx);
+    if (!small_grid) {
+        {
+            ProfScope ps_(ctx, "nb_species_blocks");
+            k_species_blocks<<<grid_for(n), kBlock, 0, st>>>(n, nl->sp, blkcnt);
+        }
+        {
+            ProfScope ps_(ctx, "nb_species_scan");
+            k_species_scan<<<1, 1024, 0, st>>>(nblk, nl->S, blkcnt, blkoff, spcount);
+        }
+        {
+            ProfScope ps_(ctx, "nb_species");
+            k_species_place<<<grid_for(n), kBlock, 0, st>>>(n, nl->S, nl->sp, spcount, blkoff, nl->sp_idx);
+        }
     }
     FillArgs fa;
     fa.g = g;
@@ -916,6 +1065,7 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
     fa.img = nl->img;
     fa.cnt = nl->cnt;
     fa.flags = flags;
+    fa.host = ctx->h_flags;
     fa.narrow = narrow;
     const int stencil_cells = (2 * g.reach[0] + 1) * (2 * g.reach[1] + 1) * (2 * g.reach[2] + 1);
     const bool by_cell = stencil_cells <= 64;
@@ -941,8 +1091,14 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
             k_fill<false><<<grid_for(n), kBlock, 0, st>>>(fa);
     }
     TMD_HIP(ctx, hipGetLastError());
-    TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, flags, sizeof(int32_t) * 64, hipMemcpyDeviceToHost, st));
     TMD_HIP(ctx, hipStreamSynchronize(st));
+    auto read_flags = [&]() -> tmd_status {
+        TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, flags, sizeof(int32_t) * 16, hipMemcpyDeviceToHost, st));
+        TMD_HIP(ctx, hipStreamSynchronize(st));
+        return TMD_OK;
+    };
+    tmd_status rst = TMD_OK;
+    if (ctx->h_flags[3] && (rst = read_flags()) != TMD_OK) return rst;
     if (by_cell && (ctx->h_flags[2] & 1)) {
         // a cell holds more atoms than one wave can track: per-atom fill instead
         {
@@ -953,8 +1109,7 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
                 k_fill<false><<<grid_for(n), kBlock, 0, st>>>(fa);
         }
         TMD_HIP(ctx, hipGetLastError());
-        TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, flags, sizeof(int32_t) * 64, hipMemcpyDeviceToHost, st));
-        TMD_HIP(ctx, hipStreamSynchronize(st));
+        if ((rst = read_flags()) != TMD_OK) return rst;
     }
     const int32_t errs = ctx->h_flags[0];
     if (errs & kErrSpecies) return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "species index outside [0, n_species)");
@@ -1026,55 +1181,66 @@ tmd_status prune_rows(tmd_context* ctx, tmd_nlist* nl, double r, const int32_t* 
     return TMD_OK;
 }
 
-}  // namespace
-
-tmd_status reserve_pruned_rows(tmd_context* ctx, tmd_nlist* nl) { return reserve_pruned(ctx, nl); }
-
-tmd_status launch_prune(tmd_context* ctx, tmd_nlist* nl, double rcut) {
-    tmd_status st = reserve_pruned(ctx, nl);
-    if (st != TMD_OK) return st;
-    nl->pruned_margin = -1.0;
-    return prune_rows(ctx, nl, rcut * (1.0 + 1e-6), nullptr);
-}
-
-tmd_status launch_prune_gated(tmd_context* ctx, tmd_nlist* nl, double rcut, const PruneGate& g) {
-    if (!g.maxd2 || !(g.margin > 0.0)) return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "prune gate without displacements");
-    tmd_status st = reserve_pruned(ctx, nl);
-    if (st != TMD_OK) return st;
-    const int force = (nl->pruned_build_id != nl->build_id || nl->pruned_margin != g.margin) ? 1 : 0;
-    k_prune_gate<<<1, 64, 0, ctx->stream>>>(g.maxd2, nl->prune_state, nl->prune_flag, force, 0.5 * g.margin);
-    TMD_HIP(ctx, hipGetLastError());
-    nl->pruned_build_id = nl->build_id;
-    nl->pruned_margin = g.margin;
-    return prune_rows(ctx, nl, rcut + g.margin, nl->prune_flag);
-}
-
-tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl) {
+tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
+                                    unsigned long long* zero, const GateArgs& gate) {
     const int64_t n = nl->n;
     {
         ProfScope ps_(ctx, "refresh");
         k_refresh<<<grid_for(n), kBlock, 0, ctx->stream>>>(n, sys->pos, nl->perm, nl->shift, sys->box[0], sys->box[1],
-                                                            sys->box[2], nl->xs);
+                                                            sys->box[2], nl->xs, zero, gate);
     }
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;
 }
 
+}  // namespace
+
+tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
+                                    unsigned long long* zero) {
+    return launch_refresh_positions(ctx, sys, nl, zero, GateArgs{});
+}
+
+tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tmd_nlist* nl, unsigned long long* zero,
+                                double rcut, const PruneGate* gate) {
+    tmd_status st = reserve_pruned(ctx, nl);
+    if (st != TMD_OK) return st;
+    if (!gate) {
+        if ((st = launch_refresh_positions(ctx, sys, nl, zero)) != TMD_OK) return st;
+        nl->pruned_margin = -1.0;
+        return prune_rows(ctx, nl, rcut * (1.0 + 1e-6), nullptr);
+    }
+    if (!gate->maxd2 || !(gate->margin > 0.0))
+        return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "prune gate without displacements");
+    const int force = (nl->pruned_build_id != nl->build_id || nl->pruned_margin != gate->margin) ? 1 : 0;
+    const GateArgs g{gate->maxd2, nl->prune_state, nl->prune_flag, force, 0.5 * gate->margin};
+    if ((st = launch_refresh_positions(ctx, sys, nl, zero, g)) != TMD_OK) return st;
+    nl->pruned_build_id = nl->build_id;
+    nl->pruned_margin = gate->margin;
+    return prune_rows(ctx, nl, rcut + gate->margin, nl->prune_flag);
+}
+
+tmd_status reserve_pruned_rows(tmd_context* ctx, tmd_nlist* nl) { return reserve_pruned(ctx, nl); }
+
+namespace {
+// Most species counts of cells that a build of up to n atoms and S species keeps.
+int64_t flag_cells(int64_t n, int S) {
+    return S > 1 ? S * std::min<int64_t>(kScanCells, std::max<int64_t>(64, 4 * n)) : 0;
+}
+}  // namespace
+
 tmd_status reserve_nlist_workspace(tmd_context* ctx, int64_t n, int S) {
-    (void)S;
     hipError_t e = hipSuccess;
     const int64_t nblk = (n + kBlock - 1) / kBlock, cells = std::max<int64_t>(64, 4 * n) + 1;
     (void)ctx->ws.get("nb.wpos", sizeof(double) * 3 * n, &e);
     (void)ctx->ws.get("nb.cell_of", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.cell_sorted", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.order", sizeof(int32_t) * n, &e);
-    (void)ctx->ws.get("nb.cellcount", sizeof(int32_t) * cells, &e);
+    (void)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + cells + flag_cells(n, S)), &e);
     (void)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((cells + 1023) / 1024 + 1), &e);
     (void)ctx->ws.get("wo.count", sizeof(int32_t) * cells, &e);
     (void)ctx->ws.get("nb.cell_rank", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.blkcnt", sizeof(int32_t) * kMaxSpecies * nblk, &e);
     (void)ctx->ws.get("nb.blkoff", sizeof(int32_t) * kMaxSpecies * (nblk + 1), &e);
-    (void)ctx->ws.get("nb.flags", sizeof(int32_t) * 64, &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "neighbour workspace allocation");
     return TMD_OK;
 }
@@ -1082,7 +1248,8 @@ tmd_status reserve_nlist_workspace(tmd_context* ctx, int64_t n, int S) {
 size_t nlist_workspace_bytes(int64_t n) {
     const int64_t nblk = (n + kBlock - 1) / kBlock;
     const size_t cells = (size_t)std::max<int64_t>(64, 4 * n) + 1;
-    return (size_t)n * 40 + 8 * cells + 4 * (cells / 1024 + 2) + 8 * (size_t)kMaxSpecies * (nblk + 1) + 512;
+    return (size_t)n * 40 + 8 * cells + 4 * (cells / 1024 + 2) + 8 * (size_t)kMaxSpecies * (nblk + 1) +
+           4 * (size_t)flag_cells(n, kMaxSpecies) + 512;
 }
 
 tmd_status launch_nlist_stats(tmd_context* ctx, const tmd_nlist* nl, int64_t* total_pairs, int32_t* max_row) {

@@ -74,6 +74,8 @@ struct tmd_context {
     tmd::Profiler prof;
     double* h_totals = nullptr;  // pinned host [8]
     int32_t* h_flags = nullptr;  // pinned host [64]
+    // device: counts the workgroups of a launch that have finished (k_finalize); zero between launches
+    unsigned int* d_counter = nullptr;
     // device address of the library's static scratch array on this context's
     // device (tmd_energy_forces_noalloc), looked up once per device at creation
     unsigned char* scratch = nullptr;
@@ -322,7 +324,9 @@ __host__ __device__ inline void unpack_img(int32_t c, int& nx, int& ny, int& nz)
 // Launchers (each enqueues on ctx->stream) ---------------------------------
 tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, double rlist, tmd_nlist* nl,
                                   int32_t* required_capacity);
-tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl);
+// Sorted positions from the caller's; zero (nullable) [3 n] is cleared in the same launch.
+tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
+                                    unsigned long long* zero);
 // Descriptors G [n][F] (sorted order); when Pbuf is non-null the per-atom P
 // tensors (kept components) are kept there for the adjoint: p_slots(m, nl)
 // x S x K x Dr floats.  When Gb is non-null G is stored there instead, as the
@@ -357,16 +361,17 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
 constexpr double kForceFixedScale = 4294967296.0;  // 2^32
 // Virial partials: per block, 6 compensated FP64 sums (value, compensation).
 constexpr int kVirDoubles = 12;
-// Adjoint: forces accumulated into Fq [n][3] (fixed point, zeroed by the
-// launcher), virial block partials [blocks][6][2] into vir_partials (count in
+// Adjoint: forces accumulated into Fq [n][3] (fixed point, cleared by the
+// caller: launch_refresh_positions, launch_batch_merge), virial block partials [blocks][6][2] into vir_partials (count in
 // *nvir_out).
 tmd_status launch_adjoint(tmd_context* ctx, const tmd_model* m, const tmd_nlist* nl, const float* dG, float* Pbuf,
                           unsigned long long* Fq, double* vir_partials, int* nvir_out);
-// part: device scratch of finalize_part_doubles() doubles.
+// part: device scratch of finalize_part_doubles() doubles; host_totals
+// (nullable): pinned host memory that receives the seven totals as well.
 constexpr int64_t finalize_part_doubles() { return 256 * 14; }
 tmd_status launch_finalize(tmd_context* ctx, const tmd_nlist* nl, const float* Ei, const unsigned long long* Fq,
                            const double* vir_partials, int nvir, float* atom_energy, float* forces, double* totals7,
-                           double* part);
+                           double* host_totals, double* part);
 // Descriptor rows [n][F] (sorted order, padded radial functions) to the
 // caller's order and the model's own F columns.
 tmd_status launch_permute_rows(tmd_context* ctx, const tmd_nlist* nl, const float* in, const tmd_model* m, float* out);
@@ -408,11 +413,6 @@ tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n);
 // limit2 (flag is sticky: never cleared here).
 tmd_status launch_displacement_check(tmd_context* ctx, const unsigned long long* maxd2, double limit2, unsigned long long* flag);
 
-// Copy of the list's rows keeping only the entries within rcut (times 1 + 1e-6)
-// at the current positions, into nl->pnbr / pimg / pcnt (allocated on first
-// use).  Every entry the kernels would use survives, in the same order.
-tmd_status launch_prune(tmd_context* ctx, tmd_nlist* nl, double rcut);
-
 // Displacement tracking that lets pruned rows be reused: maxd2 (device) holds
 // the bits of the largest squared displacement of any atom since the list was
 // built, for the positions being evaluated.  Rows pruned to rcut + margin when
@@ -423,9 +423,14 @@ struct PruneGate {
     const unsigned long long* maxd2;
     double margin;
 };
-// launch_prune with a gate: the decision is taken on the device (no host
+// launch_refresh_positions and then a copy of the list's rows keeping only the
+// entries within rcut (times 1 + 1e-6) at those positions, into nl->pnbr /
+// pimg / pcnt (allocated on first use).  Every entry the kernels would use
+// survives, in the same order.  With a gate the rows are pruned to rcut + its
+// margin, and only when needed: the decision is taken on the device (no host
 // synchronisation); a new build always prunes.
-tmd_status launch_prune_gated(tmd_context* ctx, tmd_nlist* nl, double rcut, const PruneGate& g);
+tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tmd_nlist* nl, unsigned long long* zero,
+                                double rcut, const PruneGate* gate);
 // E+F on the stream with device-resident totals (totals7: E, W[6]); gate may
 // be null (skin lists are then pruned to the cutoff at every call).
 tmd_status energy_forces_gated(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys, const tmd_nlist* nl,
@@ -454,8 +459,10 @@ struct BatchSeg {
     int64_t dst_off[kMaxSpecies] = {0};  // first slot of its species-b atoms in the merged grouping
     float* forces = nullptr;          // output [n][3], original order
 };
-// Merged positions, per-atom boxes, rows and species grouping into vnl's arrays.
-tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, tmd_nlist* vnl, double4* boxes);
+// Merged positions, per-atom boxes, rows and species grouping into vnl's arrays;
+// the force accumulators Fq [vnl->n][3] are cleared.
+tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, tmd_nlist* vnl, double4* boxes,
+                              unsigned long long* Fq);
 // Forces to each segment's output and per-segment totals [nseg][7]; the adjoint
 // wrote one virial partial per vir_atoms combined atoms.
 tmd_status launch_batch_finalize(tmd_context* ctx, const BatchSeg* segs, int nseg, int64_t N,
