@@ -665,27 +665,39 @@ constexpr int kMaxCandidates = 27 * kMaxCellAtoms;
 // Image of cell coordinate c (in -1 .. n) when the stencil reaches one cell.
 __device__ __forceinline__ int near_image(int c, int n) { return c < 0 ? -1 : (c >= n ? 1 : 0); }
 
+//
+// A cell's atoms may be shared out over `split` waves (consecutive atoms each;
+// every wave walks all candidates): a launch of one wave per cell leaves the
+// chip idle when there are few cells, and a wave then runs its (round, atom)
+// steps one after the other.
 template <int SMAX, bool NARROW>  // a.S <= SMAX; NARROW: 3x3x3 stencil
-__global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells) {
+__global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells, int split) {
     // per wave: stencil cell of every candidate, and the cell's own positions
     __shared__ uint8_t s_cell[kBlock / 64][kMaxCandidates];
     __shared__ double s_xi[kBlock / 64][3][kMaxCellAtoms];
     __shared__ int32_t s_len[kBlock / 64][kMaxCellAtoms][SMAX];  // running row lengths
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     publish_flags(a);
-    const int64_t cell = (int64_t)blockIdx.x * (kBlock / 64) + wv;
+    const int64_t item = (int64_t)blockIdx.x * (kBlock / 64) + wv;
+    const int64_t cell = split == 1 ? item : item / split;
     if (cell >= ncells) return;  // whole wave
     const GridArgs& g = a.g;
     const int cx = (int)(cell % g.nc[0]), cy = (int)((cell / g.nc[0]) % g.nc[1]),
               cz = (int)(cell / ((int64_t)g.nc[0] * g.nc[1]));
-    const int a0 = __builtin_amdgcn_readfirstlane(a.cellstart[cell]);
-    const int natoms = __builtin_amdgcn_readfirstlane(a.cellstart[cell + 1]) - a0;
+    int a0 = __builtin_amdgcn_readfirstlane(a.cellstart[cell]);
+    int natoms = __builtin_amdgcn_readfirstlane(a.cellstart[cell + 1]) - a0;
     if (natoms > kMaxCellAtoms) {  // the host reruns the build with k_fill
         if (lane == 0) {
             atomicOr(&a.flags[2], 1);
             fill_failed(a);
         }
         return;
+    }
+    if (split > 1) {  // this wave's share of the cell's atoms
+        const int part = __builtin_amdgcn_readfirstlane((int)(item - cell * split));
+        const int per = (natoms + split - 1) / split, at = min(part * per, natoms);
+        natoms = min(per, natoms - at);
+        a0 += at;
     }
     if (natoms == 0) return;  // nothing to list (and a0 may equal n)
     const int rx = NARROW ? 1 : g.reach[0], ry = NARROW ? 1 : g.reach[1], rz = NARROW ? 1 : g.reach[2];
@@ -1071,8 +1083,14 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
     const bool by_cell = stencil_cells <= 64;
     if (by_cell) {
         ProfScope ps_(ctx, "nb_fill");
-        const unsigned grid = (unsigned)((ncells + kBlock / 64 - 1) / (kBlock / 64));
-        using FillFn = void (*)(FillArgs, int64_t);
+        // up to eight waves per SIMD, at most sixteen waves per cell (one and
+        // two, four, eight, sixteen waves per SIMD at most: 1,728 cells 48, 35,
+        // 33, 40 us; 4,096 cells of 91-entry rows 85, 85, 61, 60 us; 256 cells
+        // 32 us unsplit, 11 to 12 us split)
+        int split = 1;
+        while (split < 16 && 2 * split * ncells <= 32 * (int64_t)ctx->num_cus) split *= 2;
+        const unsigned grid = (unsigned)((ncells * split + kBlock / 64 - 1) / (kBlock / 64));
+        using FillFn = void (*)(FillArgs, int64_t, int);
         FillFn fn;
         if (nl->S == 1)
             fn = narrow ? k_fill_cells<1, true> : k_fill_cells<1, false>;
@@ -1082,7 +1100,7 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
             fn = narrow ? k_fill_cells<4, true> : k_fill_cells<4, false>;
         else
             fn = narrow ? k_fill_cells<kMaxSpecies, true> : k_fill_cells<kMaxSpecies, false>;
-        fn<<<grid, kBlock, 0, st>>>(fa, ncells);
+        fn<<<grid, kBlock, 0, st>>>(fa, ncells, split);
     } else {
         ProfScope ps_(ctx, "nb_fill");
         if (n <= kFillLdsAtoms)
