@@ -29,22 +29,46 @@ constexpr double kKeConv = 103.6427;       // amu (A/fs)^2 -> eV
 constexpr double kKb = 8.617333262e-5;     // eV/K
 constexpr double kEvA3ToGPa = 160.21766208;
 
-// v += (dt/2) a; x += dt v; and (maxd2 non-null) the largest squared
-// displacement since the last list build, as the bits of a non-negative
-// double (ordered like the values).  Grid-stride over a few workgroups per CU,
-// so that few workgroups meet at the one atomicMax.
+// One thermostat half step: state (xi, eta) in place, ke (kinetic energy)
+// rescaled; returns the velocity scale.
+__device__ __forceinline__ double nh_half(double& xi, double& eta, double& ke, const Thermostat& th) {
+    xi += 0.25 * th.dt * (2.0 * ke - th.g * th.kT) / th.Q;
+    const double s = exp(-xi * 0.5 * th.dt);
+    ke *= s * s;
+    eta += 0.5 * th.dt * xi;
+    xi += 0.25 * th.dt * (2.0 * ke - th.g * th.kT) / th.Q;
+    return s;
+}
+
+// (two scales: those of the half thermostat step that ended the step before,
+// if still pending, and of the one that begins this step)
+// v *= scale0; v *= scale1 (where non-null); v += (dt/2) a; x += dt v; and
+// (maxd2 non-null) the largest squared displacement since the last list build,
+// as the bits of a non-negative double (ordered like the values); over is set
+// when it exceeds limit2 (sticky, never cleared here).  Grid-stride over a few
+// workgroups per CU, so that few workgroups meet at the one atomicMax.
 __global__ void __launch_bounds__(256) k_kick_drift(int64_t n, double* __restrict__ x, double* __restrict__ v,
                                                     const float* __restrict__ F, const int32_t* __restrict__ sp,
                                                     const double* __restrict__ acc, double dt,
+                                                    const double* __restrict__ scale0,
+                                                    const double* __restrict__ scale1,
                                                     const double* __restrict__ xref,
-                                                    unsigned long long* __restrict__ maxd2) {
+                                                    unsigned long long* __restrict__ maxd2, double limit2,
+                                                    unsigned long long* __restrict__ over) {
     __shared__ double red[256];
     double d2 = 0.0;  // largest over this thread's atoms
+    const double s0 = scale0 ? *scale0 : 1.0, s1 = scale1 ? *scale1 : 1.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double a = acc[sp[i]];
         double di = 0.0;
         for (int c = 0; c < 3; ++c) {
-            const double vi = v[3 * i + c] + 0.5 * dt * a * (double)F[3 * i + c];
+            double v0 = v[3 * i + c];
+            {
+#pragma clang fp contract(off)  // as scalings in launches of their own would round
+                if (scale0) v0 = v0 * s0;
+                if (scale1) v0 = v0 * s1;
+            }
+            const double vi = v0 + 0.5 * dt * a * (double)F[3 * i + c];
             const double xi = x[3 * i + c] + dt * vi;
             v[3 * i + c] = vi;
             x[3 * i + c] = xi;
@@ -62,87 +86,104 @@ __global__ void __launch_bounds__(256) k_kick_drift(int64_t n, double* __restric
         if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicMax(maxd2, (unsigned long long)__double_as_longlong(red[0]));
-}
-
-// v += (dt/2) a
-__global__ void k_kick(int64_t n, double* __restrict__ v, const float* __restrict__ F,
-                       const int32_t* __restrict__ sp, const double* __restrict__ acc, double dt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double a = acc[sp[i]];
-    for (int c = 0; c < 3; ++c) v[3 * i + c] += 0.5 * dt * a * (double)F[3 * i + c];
-}
-
-// Kinetic energy tensor diagonal in two fixed-order passes: kKeBlocks strided
-// partials, then compensated sums.
-__global__ void __launch_bounds__(256) k_ke_partials(int64_t n, const double* __restrict__ v,
-                                                     const int32_t* __restrict__ sp,
-                                                     const double* __restrict__ mass, double* __restrict__ part) {
-    __shared__ double red[3][256];
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double hm = 0.5 * kKeConv * mass[sp[i]];
-        for (int c = 0; c < 3; ++c) s[c] += hm * v[3 * i + c] * v[3 * i + c];
+    if (threadIdx.x == 0) {
+        atomicMax(maxd2, (unsigned long long)__double_as_longlong(red[0]));
+        if (over && red[0] > limit2) *over = 1ull;
     }
-    for (int c = 0; c < 3; ++c) red[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 3; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) part[3 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Sum of the nb (<= 256) block partials per component: one workgroup, a fixed
-// pairwise tree of compensated (Neumaier) merges, so the result is the same
-// run to run.
-__global__ void __launch_bounds__(256) k_ke_total(const double* __restrict__ part, int nb, double* __restrict__ out4) {
+// The end of a step in one launch.  Launches bound it: kick, kinetic tensor in
+// two stages, thermostat, scaling and clears were nine of 4 to 5 us each, and
+// ten NVT steps of 54,000 atoms took 3.31 ms; with this and the scales in
+// k_kick_drift 3.25 ms, and ten-step requests of 54 to 4,000 atoms 7 % less.
+//   v += (dt/2) a (when F is given);
+//   out4 = the kinetic tensor diagonal and total, by strided sums per
+//   workgroup and, in the last workgroup to finish, a fixed pairwise tree of
+//   compensated (Neumaier) merges, so the result is the same run to run;
+//   with a thermostat (th.state), its half step that ends this step (th.second;
+//   state[0..2] = xi, eta, velocity scale, and out4 rescaled), and its half
+//   step that will begin the next one from there (state[4..6]), whose velocity
+//   scales are applied by the next kick;
+//   *clear = 0 (nullable).
+constexpr int kKeThreads = 1024;
+__global__ void __launch_bounds__(kKeThreads) k_kick_kinetic(int64_t n, double* __restrict__ v,
+                                                             const float* __restrict__ F,
+                                                             const int32_t* __restrict__ sp,
+                                                             const double* __restrict__ acc,
+                                                             const double* __restrict__ mass, double dt, double* part,
+                                                             unsigned int* counter, double* __restrict__ out4,
+                                                             Thermostat th, unsigned long long* __restrict__ clear) {
+    __shared__ double red[3][kKeThreads / 64];
     __shared__ double rs[3][256], rc[3][256];
-    const int t = threadIdx.x;
-    for (int c = 0; c < 3; ++c) {
-        rs[c][t] = t < nb ? part[3 * t + c] : 0.0;
-        rc[c][t] = 0.0;
+    __shared__ bool last;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, nb = (int)gridDim.x;
+    if (clear && blockIdx.x == 0 && t == 0) *clear = 0ull;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int64_t i = (int64_t)blockIdx.x * kKeThreads + t; i < n; i += (int64_t)nb * kKeThreads) {
+        const int b = sp[i];
+        const double hm = 0.5 * kKeConv * mass[b], a = acc[b];
+        for (int c = 0; c < 3; ++c) {
+            double vi = v[3 * i + c];
+            if (F) {
+                vi += 0.5 * dt * a * (double)F[3 * i + c];
+                v[3 * i + c] = vi;
+            }
+            s[c] += hm * vi * vi;
+        }
     }
+    for (int c = 0; c < 3; ++c) {
+        for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off);
+        if (lane == 0) red[c][wv] = s[c];
+    }
+    __syncthreads();
+    // the workgroups' sums as device-scope atomics: see k_finalize
+    if (t < 3) {
+        double r = 0.0;
+        for (int w = 0; w < kKeThreads / 64; ++w) r += red[t][w];
+        __hip_atomic_store(part + 3 * blockIdx.x + t, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (t == 0) last = atomicInc(counter, nb - 1) == (unsigned)(nb - 1);
+    __syncthreads();
+    if (!last) return;
+    if (t < 256)
+        for (int c = 0; c < 3; ++c) {
+            rs[c][t] = t < nb ? __hip_atomic_load(part + 3 * t + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+            rc[c][t] = 0.0;
+        }
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (t < w)
             for (int c = 0; c < 3; ++c) {
-                const double x = rs[c][t], y = rs[c][t + w], s = x + y;
-                const double e = fabs(x) >= fabs(y) ? (x - s) + y : (y - s) + x;
-                rs[c][t] = s;
+                const double x = rs[c][t], y = rs[c][t + w], z = x + y;
+                const double e = fabs(x) >= fabs(y) ? (x - z) + y : (y - z) + x;
+                rs[c][t] = z;
                 rc[c][t] += rc[c][t + w] + e;
             }
         __syncthreads();
     }
-    if (t == 0) {
-        double tot = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            out4[c] = rs[c][0] + rc[c][0];
-            tot += out4[c];
-        }
-        out4[3] = tot;
+    if (t != 0) return;
+    double k4[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int c = 0; c < 3; ++c) {
+        k4[c] = rs[c][0] + rc[c][0];
+        k4[3] += k4[c];
     }
-}
-
-// Thermostat half step on the device: state = (xi, eta, scale); ke4 is the
-// kinetic tensor before the scaling and is rescaled in place.
-__global__ void k_nh_half(double* __restrict__ state, double* __restrict__ ke4, double g, double kT, double Q,
-                          double dt) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double xi = state[0], eta = state[1];
-    double ke = ke4[3];
-    xi += 0.25 * dt * (2.0 * ke - g * kT) / Q;
-    const double s = exp(-xi * 0.5 * dt);
-    ke *= s * s;
-    eta += 0.5 * dt * xi;
-    xi += 0.25 * dt * (2.0 * ke - g * kT) / Q;
-    state[0] = xi;
-    state[1] = eta;
-    state[2] = s;
-    for (int c = 0; c < 3; ++c) ke4[c] *= s * s;
-    ke4[3] = ke;
+    if (th.state) {
+        double xi = th.state[th.second ? 4 : 0], eta = th.state[th.second ? 5 : 1];
+        if (th.second) {
+            const double sc = nh_half(xi, eta, k4[3], th);
+            th.state[0] = xi;
+            th.state[1] = eta;
+            th.state[2] = sc;
+            for (int c = 0; c < 3; ++c) k4[c] *= sc * sc;
+        }
+        double ke = k4[3];
+        const double sc = nh_half(xi, eta, ke, th);
+        th.state[4] = xi;
+        th.state[5] = eta;
+        th.state[6] = sc;
+    }
+    for (int c = 0; c < 4; ++c) out4[c] = k4[c];
 }
 
 __global__ void k_scale_v(int64_t n3, double* __restrict__ v, const double* __restrict__ state) {
@@ -155,9 +196,10 @@ unsigned blocks_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 }  // namespace
 
 tmd_status launch_kick_drift(tmd_context* ctx, int64_t n, double* x, double* v, const float* F, const int32_t* sp,
-                             const double* acc, double dt, const double* xref, unsigned long long* maxd2) {
+                             const double* acc, double dt, const double* scale0, const double* scale1,
+                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over) {
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks_of(n), 4 * (int64_t)ctx->num_cus));
-    k_kick_drift<<<grid, kBlock, 0, ctx->stream>>>(n, x, v, F, sp, acc, dt, xref, maxd2);
+    k_kick_drift<<<grid, kBlock, 0, ctx->stream>>>(n, x, v, F, sp, acc, dt, scale0, scale1, xref, maxd2, limit2, over);
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;
 }
@@ -167,14 +209,6 @@ __global__ void k_zero_u64(unsigned long long* __restrict__ p, int64_t n) {
     if (i < n) p[i] = 0ull;
 }
 
-// flag |= (largest squared displacement > limit2); maxd2 holds the bits of a
-// non-negative double, whose order is that of the bits.
-__global__ void k_displacement_check(const unsigned long long* __restrict__ maxd2, double limit2,
-                                     unsigned long long* __restrict__ flag) {
-    if (threadIdx.x != 0) return;
-    if (__longlong_as_double((long long)*maxd2) > limit2) *flag = 1ull;
-}
-
 tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n) {
     if (n <= 0) return TMD_OK;
     k_zero_u64<<<blocks_of(n), kBlock, 0, ctx->stream>>>(p, n);
@@ -182,24 +216,13 @@ tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n) {
     return TMD_OK;
 }
 
-tmd_status launch_displacement_check(tmd_context* ctx, const unsigned long long* maxd2, double limit2, unsigned long long* flag) {
-    k_displacement_check<<<1, 64, 0, ctx->stream>>>(maxd2, limit2, flag);
-    TMD_HIP(ctx, hipGetLastError());
-    return TMD_OK;
-}
-
-tmd_status launch_kick(tmd_context* ctx, int64_t n, double* v, const float* F, const int32_t* sp, const double* acc,
-                       double dt) {
-    k_kick<<<blocks_of(n), kBlock, 0, ctx->stream>>>(n, v, F, sp, acc, dt);
-    TMD_HIP(ctx, hipGetLastError());
-    return TMD_OK;
-}
-
-tmd_status launch_kinetic(tmd_context* ctx, int64_t n, const double* v, const int32_t* sp, const double* mass,
-                          double* part, double* out4) {
-    k_ke_partials<<<kKeBlocks, 256, 0, ctx->stream>>>(n, v, sp, mass, part);
-    static_assert(kKeBlocks <= 256, "k_ke_total sums at most 256 partials");
-    k_ke_total<<<1, 256, 0, ctx->stream>>>(part, kKeBlocks, out4);
+tmd_status launch_kick_kinetic(tmd_context* ctx, int64_t n, double* v, const float* F, const int32_t* sp,
+                               const double* acc, const double* mass, double dt, double* part, double* out4,
+                               const Thermostat& th, unsigned long long* clear) {
+    static_assert(kKeBlocks <= 256, "the last workgroup merges at most 256 partials");
+    const unsigned grid = (unsigned)std::min<int64_t>(kKeBlocks, (n + kKeThreads - 1) / kKeThreads);
+    k_kick_kinetic<<<grid, kKeThreads, 0, ctx->stream>>>(n, v, F, sp, acc, mass, dt, part, ctx->d_counter + 1, out4, th,
+                                                         clear);
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;
 }
@@ -229,7 +252,10 @@ struct tmd_md {
     double* mass = nullptr;
     double* tot7 = nullptr;     // E, virial (xx, yy, zz, xy, xz, yz)
     double* ke4 = nullptr;      // kinetic tensor diagonal + total
-    double* state = nullptr;    // xi, eta, scale
+    // Thermostat: [0..2] xi, eta and velocity scale after the half step that
+    // ends a step; [4..6] the same after the half step that begins the next.
+    double* state = nullptr;
+    bool scaled = true;         // v carries the velocity scale state[2]
     double* part = nullptr;     // kinetic partials
     unsigned long long* maxd2 = nullptr;
 };
@@ -321,20 +347,37 @@ tmd_status md_energy_forces(tmd_md* md) {
                                md->opts.skin > 0.0 ? &g : nullptr);
 }
 
-// Energy, forces and kinetic tensor at the current state.
-tmd_status md_evaluate(tmd_md* md) {
-    tmd_context* ctx = md->ctx;
-    tmd_status st = md_energy_forces(md);
-    if (st != TMD_OK) return st;
-    return launch_kinetic(ctx, md->n, md->v, md->sp, md->mass, md->part, md->ke4);
+bool md_nvt(const tmd_md* md) { return md->opts.ensemble == TMD_ENSEMBLE_NVT_NOSE_HOOVER; }
+
+// The second half kick (step) or none (the start), the kinetic tensor and the thermostat.
+tmd_status md_kinetic(tmd_md* md, bool step) {
+    Thermostat th{};
+    th.state = md_nvt(md) ? md->state : nullptr;
+    th.second = step ? 1 : 0;
+    th.g = md->g;
+    th.kT = md->kT;
+    th.Q = md->Q;
+    th.dt = md->opts.dt_fs;
+    md->scaled = !(step && th.state);
+    return launch_kick_kinetic(md->ctx, md->n, md->v, step ? md->F : nullptr, md->sp, md->acc, md->mass,
+                               md->opts.dt_fs, md->part, md->ke4, th, md->maxd2);
 }
 
-tmd_status md_thermostat(tmd_md* md) {
-    if (md->opts.ensemble != TMD_ENSEMBLE_NVT_NOSE_HOOVER) return TMD_OK;
+// Energy, forces and kinetic tensor at the start.
+tmd_status md_evaluate(tmd_md* md) {
+    tmd_status st = md_energy_forces(md);
+    if (st != TMD_OK) return st;
+    return md_kinetic(md, false);
+}
+
+// Velocities as the last step left them (its closing half thermostat step is
+// otherwise applied by the next step's kick).
+tmd_status md_settle(tmd_md* md) {
+    if (md->scaled) return TMD_OK;
     tmd_context* ctx = md->ctx;
-    k_nh_half<<<1, 64, 0, ctx->stream>>>(md->state, md->ke4, md->g, md->kT, md->Q, md->opts.dt_fs);
     k_scale_v<<<blocks_of(3 * md->n), kBlock, 0, ctx->stream>>>(3 * md->n, md->v, md->state);
     TMD_HIP(ctx, hipGetLastError());
+    md->scaled = true;
     return TMD_OK;
 }
 
@@ -385,12 +428,12 @@ tmd_status tmd_md_create(tmd_context* ctx, const tmd_model* model, const tmd_sys
     alloc((void**)&md->mass, 8 * (size_t)md->S);
     alloc((void**)&md->tot7, 8 * 8);
     alloc((void**)&md->ke4, 8 * 4);
-    alloc((void**)&md->state, 8 * 4);
+    alloc((void**)&md->state, 8 * 8);
     alloc((void**)&md->part, 8 * 3 * (size_t)kKeBlocks);
     alloc((void**)&md->maxd2, 8);
     std::vector<double> acc(md->S);
     for (int s = 0; s < md->S; ++s) acc[s] = 9.648533e-3 / masses[s];
-    const double st0[4] = {0.0, 0.0, 1.0, 0.0};
+    const double st0[8] = {0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0, 0.0};
     if (e == hipSuccess) e = hipMemcpyAsync(md->x, sys->pos, 24 * n, hipMemcpyDeviceToDevice, ctx->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(md->sp, sys->species, 4 * n, hipMemcpyDeviceToDevice, ctx->stream);
     if (e == hipSuccess)
@@ -440,13 +483,13 @@ tmd_status tmd_md_run(tmd_md* md, int64_t n_steps, int32_t thermo_every, tmd_the
     const double dt = md->opts.dt_fs, half_skin2 = 0.25 * md->opts.skin * md->opts.skin;
     const bool by_distance = md->opts.rebuild_every == 0;
     for (int64_t s = 0; s < n_steps; ++s) {
-        if ((st = md_thermostat(md)) != TMD_OK) return st;
         // the displacement since the build decides rebuilds (by_distance) and
-        // whether the pruned rows can be reused
-        TMD_HIP(ctx, hipMemsetAsync(md->maxd2, 0, 8, ctx->stream));
-        if ((st = launch_kick_drift(ctx, md->n, md->x, md->v, md->F, md->sp, md->acc, dt, md->xref, md->maxd2)) !=
-            TMD_OK)
+        // whether the pruned rows can be reused (maxd2 was cleared by the step before)
+        if ((st = launch_kick_drift(ctx, md->n, md->x, md->v, md->F, md->sp, md->acc, dt,
+                                    md->scaled ? nullptr : md->state + 2, md_nvt(md) ? md->state + 6 : nullptr,
+                                    md->xref, md->maxd2, 0.0, nullptr)) != TMD_OK)
             return st;
+        md->scaled = true;
         ++md->steps_since_build;
         bool rebuild = false;
         if (by_distance) {
@@ -460,12 +503,11 @@ tmd_status tmd_md_run(tmd_md* md, int64_t n_steps, int32_t thermo_every, tmd_the
         }
         if (rebuild && (st = md_build(md)) != TMD_OK) return st;
         if ((st = md_energy_forces(md)) != TMD_OK) return st;
-        if ((st = launch_kick(ctx, md->n, md->v, md->F, md->sp, md->acc, dt)) != TMD_OK) return st;
-        if ((st = launch_kinetic(ctx, md->n, md->v, md->sp, md->mass, md->part, md->ke4)) != TMD_OK) return st;
-        if ((st = md_thermostat(md)) != TMD_OK) return st;
+        if ((st = md_kinetic(md, true)) != TMD_OK) return st;
         ++md->step;
         if ((st = record()) != TMD_OK) return st;
     }
+    if ((st = md_settle(md)) != TMD_OK) return st;
     TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (n_thermo) *n_thermo = nt;
     return TMD_OK;
@@ -474,6 +516,8 @@ tmd_status tmd_md_run(tmd_md* md, int64_t n_steps, int32_t thermo_every, tmd_the
 tmd_status tmd_md_read(tmd_md* md, double* pos, double* vel) {
     if (!md) return TMD_ERR_INVALID_ARGUMENT;
     tmd_context* ctx = md->ctx;
+    tmd_status st = md_settle(md);  // (a run that failed part-way)
+    if (st != TMD_OK) return st;
     if (pos) TMD_HIP(ctx, hipMemcpyAsync(pos, md->x, 24 * (size_t)md->n, hipMemcpyDeviceToDevice, ctx->stream));
     if (vel) TMD_HIP(ctx, hipMemcpyAsync(vel, md->v, 24 * (size_t)md->n, hipMemcpyDeviceToDevice, ctx->stream));
     TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));

@@ -222,8 +222,10 @@ tmd_status slot_buffers(tmd_context* ctx, int n_steps, int64_t n, SlotBuffers* b
     return TMD_OK;
 }
 
-tmd_status kinetic(tmd_context* ctx, const System* sys, double* part, double* out4) {
-    return launch_kinetic(ctx, sys->n, sys->v, sys->sp, sys->mass, part, out4);
+// Second half kick of a step (dt > 0) or none, and the kinetic tensor.
+tmd_status kinetic(tmd_context* ctx, const System* sys, double dt, double* part, double* out4) {
+    return launch_kick_kinetic(ctx, sys->n, sys->v, dt > 0.0 ? sys->F : nullptr, sys->sp, sys->acc, sys->mass, dt, part,
+                               out4, Thermostat{}, nullptr);
 }
 
 // The steps of an MD request with no host synchronisation between them: each
@@ -243,17 +245,15 @@ tmd_status md_steps_device_gated(tmd_server* sv, tmd_context* ctx, System* sys, 
     int64_t queued = 0;  // atom-steps queued since the last chunk end
     int chunk = 0;
     for (int s = 1; s <= nsteps; ++s) {
-        if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, sys->xref,
-                                    b.maxd2 + s)) != TMD_OK)
+        if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, nullptr, nullptr,
+                                    sys->xref, b.maxd2 + s, half_skin2, b.flag)) != TMD_OK)
             return st;
-        if ((st = launch_displacement_check(ctx, b.maxd2 + s, half_skin2, b.flag)) != TMD_OK) return st;
         PruneGate gate;
         gate.maxd2 = b.maxd2 + s;
         gate.margin = 0.2 * sv->opts.skin;
         if ((st = energy_forces_gated(ctx, m, &view, sys->nl, b.tot + 7 * s, nullptr, sys->F, &gate)) != TMD_OK)
             return st;
-        if ((st = launch_kick(ctx, sys->n, sys->v, sys->F, sys->sp, sys->acc, dt)) != TMD_OK) return st;
-        if ((st = kinetic(ctx, sys, b.part, b.ekin + 4 * s)) != TMD_OK) return st;
+        if ((st = kinetic(ctx, sys, dt, b.part, b.ekin + 4 * s)) != TMD_OK) return st;
         queued += sys->n;
         if (queued >= kMdChunkAtomSteps && s < nsteps) {
             TMD_HIP(ctx, hipEventRecord(ev[chunk & 1], ctx->stream));
@@ -274,8 +274,8 @@ tmd_status md_steps_host_checked(tmd_server* sv, tmd_context* ctx, System* sys, 
     tmd_status st;
     for (int s = 1; s <= nsteps; ++s) {
         if ((st = launch_zero_u64(ctx, b.maxd2 + s, 1)) != TMD_OK) return st;
-        if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, sys->xref,
-                                    b.maxd2 + s)) != TMD_OK)
+        if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, nullptr, nullptr,
+                                    sys->xref, b.maxd2 + s, half_skin2, nullptr)) != TMD_OK)
             return st;
         unsigned long long bits = 0;
         TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, b.maxd2 + s, sizeof(bits), hipMemcpyDeviceToHost, ctx->stream));
@@ -296,8 +296,7 @@ tmd_status md_steps_host_checked(tmd_server* sv, tmd_context* ctx, System* sys, 
         if ((st = energy_forces_gated(ctx, m, &view, sys->nl, b.tot + 7 * s, nullptr, sys->F,
                                       sv->opts.skin > 0.0 ? &gate : nullptr)) != TMD_OK)
             return st;
-        if ((st = launch_kick(ctx, sys->n, sys->v, sys->F, sys->sp, sys->acc, dt)) != TMD_OK) return st;
-        if ((st = kinetic(ctx, sys, b.part, b.ekin + 4 * s)) != TMD_OK) return st;
+        if ((st = kinetic(ctx, sys, dt, b.part, b.ekin + 4 * s)) != TMD_OK) return st;
     }
     return TMD_OK;
 }
@@ -333,7 +332,7 @@ tmd_status run_request(tmd_server* sv, tmd_context* ctx, hipEvent_t* ev, System*
     }
     if ((st = tmd_energy_forces_async(ctx, m, &view, sys->nl, b.tot, nullptr, sys->F)) != TMD_OK) return st;
     if (md) {
-        if ((st = kinetic(ctx, sys, b.part, b.ekin)) != TMD_OK) return st;  // slot 0
+        if ((st = kinetic(ctx, sys, 0.0, b.part, b.ekin)) != TMD_OK) return st;  // slot 0
         const double dt = p.req.dt_fs;
         bool done = false;
         if (fast) {
@@ -347,7 +346,7 @@ tmd_status run_request(tmd_server* sv, tmd_context* ctx, hipEvent_t* ev, System*
                 TMD_HIP(ctx, hipMemcpyAsync(sys->v, b.v0, 24 * (size_t)sys->n, hipMemcpyDeviceToDevice, ctx->stream));
                 if ((st = tmd_energy_forces_async(ctx, m, &view, sys->nl, b.tot, nullptr, sys->F)) != TMD_OK)
                     return st;
-                if ((st = kinetic(ctx, sys, b.part, b.ekin)) != TMD_OK) return st;
+                if ((st = kinetic(ctx, sys, 0.0, b.part, b.ekin)) != TMD_OK) return st;
             }
         }
         if (!done && (st = md_steps_host_checked(sv, ctx, sys, view, b, nsteps, dt, &rebuilds)) != TMD_OK)

@@ -396,23 +396,31 @@ size_t nlist_workspace_bytes(int64_t n);
 // evaluation (a no-op once they exist).
 tmd_status reserve_pruned_rows(tmd_context* ctx, tmd_nlist* nl);
 
-// Velocity Verlet pieces (md.hip).  acc[S] = 9.648533e-3 / m_s; maxd2
-// (nullable) receives the largest squared displacement from xref as ordered
-// bits; the kinetic tensor out4 = (KE_xx, KE_yy, KE_zz, KE) in eV, FP64 fixed
-// order, with part a [3 * kKeBlocks] scratch.
-constexpr int kKeBlocks = 256;
+// Velocity Verlet pieces (md.hip).  acc[S] = 9.648533e-3 / m_s.
+// First half of a step: v *= *scale0, v *= *scale1 (each nullable), v += (dt/2) a,
+// x += dt v; maxd2 (nullable) receives the largest squared displacement from
+// xref as ordered bits, and *over (nullable) is set when it exceeds limit2
+// (sticky: never cleared here).
 tmd_status launch_kick_drift(tmd_context* ctx, int64_t n, double* x, double* v, const float* F, const int32_t* sp,
-                             const double* acc, double dt, const double* xref, unsigned long long* maxd2);
-tmd_status launch_kick(tmd_context* ctx, int64_t n, double* v, const float* F, const int32_t* sp, const double* acc,
-                       double dt);
-tmd_status launch_kinetic(tmd_context* ctx, int64_t n, const double* v, const int32_t* sp, const double* mass,
-                          double* part, double* out4);
+                             const double* acc, double dt, const double* scale0, const double* scale1,
+                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over);
+// Nose-Hoover variable of a system (state nullptr: none); second: apply the
+// half step that ends a step before the one that begins the next.
+struct Thermostat {
+    double* state;  // device [8], see tmd_md
+    int second;
+    double g, kT, Q, dt;
+};
+// Second half of a step: v += (dt/2) a (F nullable: no kick), then the kinetic
+// tensor out4 = (KE_xx, KE_yy, KE_zz, KE) in eV, FP64 fixed order, with part a
+// [3 * kKeBlocks] scratch, the thermostat's scalar steps, and *clear = 0
+// (nullable).
+constexpr int kKeBlocks = 256;
+tmd_status launch_kick_kinetic(tmd_context* ctx, int64_t n, double* v, const float* F, const int32_t* sp,
+                               const double* acc, const double* mass, double dt, double* part, double* out4,
+                               const Thermostat& th, unsigned long long* clear);
 // p[0 .. n) = 0 (a kernel, not a memset).
 tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n);
-// *flag = 1 when the squared displacement whose bits maxd2 holds exceeds
-// limit2 (flag is sticky: never cleared here).
-tmd_status launch_displacement_check(tmd_context* ctx, const unsigned long long* maxd2, double limit2, unsigned long long* flag);
-
 // Displacement tracking that lets pruned rows be reused: maxd2 (device) holds
 // the bits of the largest squared displacement of any atom since the list was
 // built, for the positions being evaluated.  Rows pruned to rcut + margin when

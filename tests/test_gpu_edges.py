@@ -8,6 +8,13 @@ the cell capacity of a wave and of its sharing over several waves).
   library sums FP32 values in FP64 with compensation, so only the final
   rounding remains (relative 2^-52; 1e-14 allows for cancellation to a
   hundredth of the summed magnitude).
+* The kinetic energy of an MD step against the exact sum over the velocities
+  read back: positive FP64 terms in strided sums of at most 8 terms, two trees
+  of depth 6 and 16, and the closing scale of a thermostat, each rounding by
+  2^-53, so 64 roundings (7e-15) bound it.  A run cut in two against one run:
+  the pending thermostat scale is applied with the same roundings, so only the
+  FP32 forces may differ where a list or a pruned row is made anew (1e-6 eV/A,
+  or 1e-9 A in three steps of 1 fs; bar 1e-8).
 """
 import math
 
@@ -96,3 +103,37 @@ def test_shared_cells(ctx, n, edge):
     scale = max(1.0, n * 4.19 * 125.0 / edge ** 3 / 50.0) * max(1.0, float(np.abs(Fr).max()))
     assert np.abs(Ea - Ear).max() <= parity.E_FP32 * scale
     assert np.abs(F - Fr).max() <= parity.FMAX_FP32 * scale
+
+
+# two atoms; edges of a 1,024-atom workgroup; every partial used (256 x 1,024) with a remainder
+@pytest.mark.parametrize("ensemble", ["nve", "nvt"])
+@pytest.mark.parametrize("n", [2, 63, 1023, 1024, 1025, 262145])
+def test_md_step_kinetic_energy(ctx, n, ensemble):
+    import torch
+    from paper_2310_08439_amd import tmd
+    print(f"[case] MD {n} atoms {ensemble}", flush=True)
+    c = max(7, int(round((n / 4) ** (1 / 3))) + 1)
+    s = inputs.make_system("fcc", 3.61, (c, c, c), 0.02, 1, seed=n, masses=[63.546])
+    pos, sp = s.pos[:n], s.species[:n]
+    v = inputs.maxwell_boltzmann(np.full(n, 63.546), 300.0, n)
+    model = tmd.Model(ctx, inputs.make_model(1, 8, 3, [16], 5.0, seed=3), tmd.FP32)
+
+    def start():
+        return tmd.MD(ctx, model, torch.tensor(pos, dtype=torch.float64, device="cuda"),
+                      torch.tensor(sp, dtype=torch.int32, device="cuda"), s.box, [63.546],
+                      torch.tensor(v, dtype=torch.float64, device="cuda"), dt_fs=1.0, temperature_K=300.0,
+                      tau_fs=100.0, skin=1.0, ensemble=tmd.ENSEMBLE_NVE if ensemble == "nve" else tmd.ENSEMBLE_NVT_NOSE_HOOVER)
+
+    one, two = start(), start()
+    last = one.run(3, thermo_every=1)[-1]
+    x1, v1 = one.state()
+    x1, v1 = x1.cpu().numpy(), v1.cpu().numpy()
+    ke = math.fsum((0.5 * 103.6427 * 63.546 * v1 * v1).ravel().tolist())
+    assert abs(last["ekin"] - ke) <= 7e-15 * ke
+    two.run(1)
+    two.run(2)
+    x2, v2 = two.state()
+    assert np.abs(x2.cpu().numpy() - x1).max() <= 1e-8
+    assert np.abs(v2.cpu().numpy() - v1).max() <= 1e-8
+    one.close()
+    two.close()
