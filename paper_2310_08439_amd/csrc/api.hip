@@ -194,6 +194,7 @@ struct EvalBuffers {
     float *G, *dG, *Ei, *P;
     unsigned long long* Fq;  // fixed-point force accumulators [n][3]
     double *vir, *totals, *part;
+    int64_t max_partials;  // room in vir
 };
 
 tmd_status eval_buffers(tmd_context* ctx, const tmd_model* m, const tmd_nlist* nl, EvalBuffers* b) {
@@ -204,7 +205,8 @@ tmd_status eval_buffers(tmd_context* ctx, const tmd_model* m, const tmd_nlist* n
     b->Ei = (float*)ctx->ws.get("ev.Ei", sizeof(float) * n, &e);
     b->Fq = (unsigned long long*)ctx->ws.get("ev.Fq", sizeof(unsigned long long) * 3 * n, &e);
     b->P = (float*)ctx->ws.get("ev.P", sizeof(float) * (size_t)p_slots(m, nl) * m->S * m->K * m->Dr, &e);
-    b->vir = (double*)ctx->ws.get("ev.vir", sizeof(double) * kVirDoubles * (size_t)adjoint_max_partials(m, nl), &e);
+    b->max_partials = adjoint_max_partials(m, nl);
+    b->vir = (double*)ctx->ws.get("ev.vir", sizeof(double) * kVirDoubles * (size_t)b->max_partials, &e);
     b->totals = (double*)ctx->ws.get("ev.totals", sizeof(double) * 8, &e);
     b->part = (double*)ctx->ws.get("ev.part", sizeof(double) * finalize_part_doubles(), &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "evaluation workspace allocation");
@@ -246,8 +248,12 @@ void scratch_buffers(unsigned char* base, const tmd_model* m, const tmd_nlist* n
     const size_t oG = take(sizeof(float) * n * m->F), odG = take(sizeof(float) * n * m->F);
     const size_t oEi = take(sizeof(float) * n), oFq = take(sizeof(unsigned long long) * 3 * n);
     const size_t oP = take(sizeof(float) * (size_t)p_slots(m, nl) * m->S * m->K * m->Dr);
-    const size_t ovir = take(sizeof(double) * kVirDoubles * (size_t)adjoint_max_partials(m, nl));
     const size_t opart = take(sizeof(double) * finalize_part_doubles());
+    const size_t ovir = off;
+    b->max_partials = adjoint_max_partials(m, nl);
+    if (off + sizeof(double) * kVirDoubles * (size_t)b->max_partials + 255 > kScratchBytes)
+        b->max_partials = adjoint_max_partials(m, nl, true);
+    take(sizeof(double) * kVirDoubles * (size_t)b->max_partials);
     *need = off;
     if (off > kScratchBytes) return;
     b->G = (float*)(base + oG);
@@ -314,7 +320,7 @@ tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_
     if ((st = launch_descriptors(ctx, m, use, b.G, b.P, Gb)) != TMD_OK) return st;
     if ((st = launch_mlp(ctx, m, species_groups(nl), m->prec, b.G, Gb, b.Ei, b.dG)) != TMD_OK) return st;
     int nvir = 0;
-    if ((st = launch_adjoint(ctx, m, use, b.dG, b.P, b.Fq, b.vir, &nvir)) != TMD_OK) return st;
+    if ((st = launch_adjoint(ctx, m, use, b.dG, b.P, b.Fq, b.vir, b.max_partials, &nvir)) != TMD_OK) return st;
     return launch_finalize(ctx, nl, b.Ei, b.Fq, b.vir, nvir, atom_energy, forces, totals7_dev ? totals7_dev : b.totals,
                            host_totals, b.part);
 }
@@ -812,12 +818,13 @@ tmd_status tmd_energy_forces_batch(tmd_context* ctx, const tmd_model* m, int32_t
             at += g.sp_off[b + 1] - g.sp_off[b];
         }
     }
-    const int nch = m->K / m->kc;  // chunk lanes per atom in the adjoint: 256 / nch atoms per virial partial
     hipError_t e = hipSuccess;
     BatchSeg* dsegs = (BatchSeg*)ctx->ws.get("batch.segs", sizeof(BatchSeg) * segs.size(), &e);
     v.xs = (double4*)ctx->ws.get("batch.xs", sizeof(double4) * N, &e);
     double4* boxes = (double4*)ctx->ws.get("batch.boxes", sizeof(double4) * N, &e);
     v.boxes = boxes;
+    int2* chunks = (int2*)ctx->ws.get("batch.chunks", sizeof(int2) * (size_t)(N / kBlock), &e);
+    v.chunks = chunks;
     v.nbr = (int32_t*)ctx->ws.get("batch.nbr", sizeof(int32_t) * (size_t)N * m->S * cap, &e);
     v.img = (int32_t*)ctx->ws.get("batch.img", sizeof(int32_t) * (size_t)N * m->S * cap, &e);
     v.cnt = (int32_t*)ctx->ws.get("batch.cnt", sizeof(int32_t) * (size_t)N * m->S, &e);
@@ -829,13 +836,13 @@ tmd_status tmd_energy_forces_batch(tmd_context* ctx, const tmd_model* m, int32_t
     // pageable source: the copy is staged before the call returns
     TMD_HIP(ctx, hipMemcpyAsync(dsegs, segs.data(), sizeof(BatchSeg) * segs.size(), hipMemcpyHostToDevice,
                                 ctx->stream));
-    if ((st = launch_batch_merge(ctx, dsegs, n_systems, &v, boxes, b.Fq)) != TMD_OK) return st;
+    if ((st = launch_batch_merge(ctx, dsegs, n_systems, m->rcut, &v, boxes, chunks, b.Fq)) != TMD_OK) return st;
     uint16_t* Gb = m->prec == TMD_BF16_MLP ? reinterpret_cast<uint16_t*>(b.G) : nullptr;
     if ((st = launch_descriptors(ctx, m, &v, b.G, b.P, Gb)) != TMD_OK) return st;
     if ((st = launch_mlp(ctx, m, species_groups(&v), m->prec, b.G, Gb, b.Ei, b.dG)) != TMD_OK) return st;
     int nvir = 0;
-    if ((st = launch_adjoint(ctx, m, &v, b.dG, b.P, b.Fq, b.vir, &nvir)) != TMD_OK) return st;
-    return launch_batch_finalize(ctx, dsegs, n_systems, N, b.Fq, b.Ei, b.vir, kBlock / nch, totals7);
+    if ((st = launch_adjoint(ctx, m, &v, b.dG, b.P, b.Fq, b.vir, b.max_partials, &nvir)) != TMD_OK) return st;
+    return launch_batch_finalize(ctx, dsegs, n_systems, N, b.Fq, b.Ei, b.vir, (int)(N / nvir), totals7);
 }
 
 tmd_status tmd_energy_forces_noalloc(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys,

@@ -245,6 +245,7 @@ struct tmd_nlist {
     int32_t* shift = nullptr;    // [n][3] wrap shift: x_wrapped = x + shift * L
     double4* xs = nullptr;       // [n]   positions used by the kernels
     const double4* boxes = nullptr;  // [n] per-atom box edges of a merged multi-system list (else box)
+    const int2* chunks = nullptr;    // [n / 256] (first atom, atoms) of the system of each 256 atoms of such a list
     int32_t* sp = nullptr;       // [n]   species
     int32_t* nbr = nullptr;      // [n][S][cap] neighbour (sorted index), row-major per atom
     int32_t* img = nullptr;      // [n][S][cap] image word (pack_img)
@@ -365,7 +366,7 @@ constexpr int kVirDoubles = 12;
 // caller: launch_refresh_positions, launch_batch_merge), virial block partials [blocks][6][2] into vir_partials (count in
 // *nvir_out).
 tmd_status launch_adjoint(tmd_context* ctx, const tmd_model* m, const tmd_nlist* nl, const float* dG, float* Pbuf,
-                          unsigned long long* Fq, double* vir_partials, int* nvir_out);
+                          unsigned long long* Fq, double* vir_partials, int64_t max_partials, int* nvir_out);
 // part: device scratch of finalize_part_doubles() doubles; host_totals
 // (nullable): pinned host memory that receives the seven totals as well.
 constexpr int64_t finalize_part_doubles() { return 256 * 14; }
@@ -469,7 +470,7 @@ struct BatchSeg {
 };
 // Merged positions, per-atom boxes, rows and species grouping into vnl's arrays;
 // the force accumulators Fq [vnl->n][3] are cleared.
-tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, tmd_nlist* vnl, double4* boxes,
+tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, double rcut, tmd_nlist* vnl, double4* boxes, int2* chunks,
                               unsigned long long* Fq);
 // Forces to each segment's output and per-segment totals [nseg][7]; the adjoint
 // wrote one virial partial per vir_atoms combined atoms.
@@ -478,6 +479,7 @@ tmd_status launch_batch_finalize(tmd_context* ctx, const BatchSeg* segs, int nse
                                  double* totals);
 
 // Upper bound on the virial partials the adjoint writes.
-int64_t adjoint_max_partials(const tmd_model* m, const tmd_nlist* nl);
+// (least: of its coarsest split, for little scratch).
+int64_t adjoint_max_partials(const tmd_model* m, const tmd_nlist* nl, bool least = false);
 
 }  // namespace tmd

@@ -8,6 +8,11 @@ the cell capacity of a wave and of its sharing over several waves).
   library sums FP32 values in FP64 with compensation, so only the final
   rounding remains (relative 2^-52; 1e-14 allows for cancellation to a
   hundredth of the summed magnitude).
+* Boxes with an edge below two list cutoffs take the kernels with 16 lanes per
+  atom: same bars, at the edges of their 32-atom workgroups, of the 16 entries
+  of a pass and of the window of force accumulators.  A merged list takes them
+  too: each system of a batch against its own evaluation, FP32 sums in another
+  order (the FP32 bars of tests/parity.py, relative to the same oracle).
 * The kinetic energy of an MD step against the exact sum over the velocities
   read back: positive FP64 terms in strided sums of at most 8 terms, two trees
   of depth 6 and 16, and the closing scale of a thermostat, each rounding by
@@ -137,3 +142,59 @@ def test_md_step_kinetic_energy(ctx, n, ensemble):
     assert np.abs(v2.cpu().numpy() - v1).max() <= 1e-8
     one.close()
     two.close()
+
+
+def _thin(nx, ny, nz, S, seed, n=None):
+    s = inputs.make_system("fcc", 3.61, (nx, ny, nz), 0.05, S, seed=seed)
+    if n is None:
+        return s
+    keep = np.sort(np.random.default_rng(seed).permutation(s.n)[:n])
+    return inputs.System(pos=s.pos[keep], species=s.species[keep], box=s.box, masses=s.masses)
+
+
+# every K the kernels take (padded from 3 and 11 too); 1, 31 to 33 and 64 atoms,
+# then systems wider than the force window on both sides of one and two windows
+@pytest.mark.parametrize("K,n,table", [(4, 1, 0.0), (8, 31, 0.0), (12, 32, 0.0), (16, 33, 0.0), (3, 64, 0.005),
+                                       (16, 64, 0.005), (11, 65, 0.0), (8, 1537, 0.0), (16, 1281, 0.0)])
+def test_thin_box(ctx, K, n, table):
+    s = _thin(1, 6, 4, 2, K + n, n) if n < 96 else _thin(1, 8, 50, 2, K + n, n)
+    spec = inputs.make_model(2, K, 3, [16], 5.0, seed=K)
+    spec.tab_dr = table
+    if table:
+        import torch
+        from paper_2310_08439_amd import tmd
+        print(f"[case] table, {s.n} atoms", flush=True)
+        E, Ea, F, W = _evaluate(ctx, spec, s)  # against the direct functions: cubic Hermite error of delta 0.005
+        spec.tab_dr = 0.0
+        E0, Ea0, F0, W0 = _evaluate(ctx, spec, s)
+        assert np.abs(F - F0).max() <= 1e-4 * max(1.0, np.abs(F0).max())
+        assert abs(E - E0) <= 1e-5 * np.abs(Ea0).sum()
+        return
+    _check(ctx, spec, s)
+
+
+@pytest.mark.parametrize("K", [4, 8, 12, 16])
+def test_merged_lists(ctx, K):
+    import torch
+    from paper_2310_08439_amd import tmd
+    spec = inputs.make_model(2, K, 3, [16], 5.0, seed=K)
+    model = tmd.Model(ctx, spec, tmd.FP32)
+    # one atom; a full padding block and one more; larger than the force window
+    systems = [_thin(4, 4, 4, 2, 1, n) for n in (1, 31, 255, 256)] + [_thin(5, 4, 4, 2, 2, 257), _thin(8, 8, 8, 2, 3)]
+    views, lists, forces = [], [], []
+    for s in systems:
+        x = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+        sp = torch.tensor(s.species, dtype=torch.int32, device="cuda")
+        nl = tmd.NeighborList(ctx, s.n, 2, tmd.default_capacity(s.n, s.box, 6.0, 2))
+        tmd.build_neighbors(ctx, x, sp, s.box, 5.0, 1.0, nl)
+        views.append((x, sp, s.box))
+        lists.append(nl)
+        forces.append(torch.empty((s.n, 3), dtype=torch.float32, device="cuda"))
+    totals = torch.empty((len(systems), 7), dtype=torch.float64, device="cuda")
+    for again in range(2):
+        print(f"[case] merged lists, K = {K}, call {again}", flush=True)
+        tmd.energy_forces_batch(ctx, model, views, lists, totals, forces)
+        t = totals.cpu().numpy()
+        for q, s in enumerate(systems):
+            E, Ea, F, W = _evaluate(ctx, spec, s)
+            parity.check_fp32(t[q, 0], Ea, forces[q].cpu().numpy().astype(np.float64), t[q, 1:], s, spec)
