@@ -521,6 +521,10 @@ struct MlpTrainArgs {
     const float* e;
     const float* params;  // [S][P]
     float* partial;       // [tiles][P]
+    // operand copies of the weights (the matrix-core kernel), as in tmd_model
+    const float *w32, *bias, *wout;
+    int64_t wstride, w_off[TMD_MAX_HIDDEN], wt_off[TMD_MAX_HIDDEN];
+    int Fpad;
 };
 
 __device__ __forceinline__ float sig(int act, float z) {
@@ -766,6 +770,238 @@ __global__ void __launch_bounds__(256) k_mlp_second(MlpTrainArgs a) {
     }
 }
 
+// The same pass on the matrix cores: sub-tiles of 16 atoms, activations in LDS
+// as [atom][width + 4] so that a lane's operands of four k-steps are one 16-byte
+// read and a result tile's four rows one 16-byte write.  Wave w owns the output
+// rows 16 (4 rt + w) of every layer in both directions, so s' and s'' zt stay in
+// its registers from the forward to the backward pass, and each element of the
+// weight gradient has one owner, which adds the sub-tiles' terms in order in the
+// tile's partial row.  Weights are read as MFMA operands from their row-major
+// copies W and W^T.
+//
+// 17,648 atoms, 32-64-64-1: 28 us (the vector kernel 101; the products take
+// 9 at the FP32 matrix rate).  Bound by the chain of layers: one sub-tile per
+// workgroup and as many workgroups as fit beat three per workgroup with the
+// gradient summed in LDS (32 against 41 us).
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+constexpr int kMlp2Tile = 16;
+__host__ __device__ inline int mlp2_cols(int F) { return (F + 15) / 16 * 16; }
+inline size_t mlp2_mfma_lds(int F, int H, int L) {
+    return sizeof(float) * ((size_t)2 * kMlp2Tile * (mlp2_cols(F) + 4) + (size_t)(2 * L + 2) * kMlp2Tile * (H + 4) +
+                            kMlp2Tile);
+}
+
+__device__ __forceinline__ f32x4 mfma4(float4 a, float4 b, f32x4 c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, c, 0, 0, 0);
+}
+
+// s, s', s'' at z.
+__device__ __forceinline__ void act3(int act, float z, float& s0, float& s1, float& s2) {
+    if (act == TMD_ACT_SQUAREPLUS) {
+        const float q = z * z + 4.0f, r = sqrtf(q);
+        s0 = 0.5f * (z + r);
+        s1 = 0.5f * (1.0f + z / r);
+        s2 = 2.0f / (q * r);
+    } else {
+        s0 = tanhf(z);
+        s1 = 1.0f - s0 * s0;
+        s2 = -2.0f * s0 * s1;
+    }
+}
+
+template <int H, int L>
+__global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    constexpr int T = kMlp2Tile, HS = H + 4, RT = (H + 63) / 64;
+    const int F = a.F, FT = mlp2_cols(F), FS = FT + 4;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, col = lane & 15, g = lane >> 4;
+    const int64_t tile = blockIdx.x;
+    int s = 0;
+    for (int q = 0; q < a.S; ++q)
+        if (tile >= a.tile_off[q] && tile < a.tile_off[q + 1]) s = q;
+    const int64_t first0 = a.sp_off[s] + (tile - a.tile_off[s]) * (int64_t)T * a.R;
+    float* X[2] = {lds, lds + T * FS};         // [T][FS] inputs and their tangents
+    float* A = lds + 2 * T * FS;               // [L][2][T][HS] activations and tangents
+    float* C = A + 2 * L * T * HS;             // [2][T][HS] cotangents of z and zt
+    float* Es = C + 2 * T * HS;                // [T] energy seeds, 0 past the last atom
+    const float* const w32 = a.w32 + s * a.wstride;
+    const float* const bias = a.bias + (int64_t)s * L * H;
+    const float* const wout = a.wout + (int64_t)s * H;
+    float* const gp = a.partial + tile * a.P;
+    const int nrt = H >= 64 ? RT : (wv < H / 16 ? 1 : 0);  // row tiles of this wave
+    for (int r = 0; r < a.R; ++r) {
+        const int64_t first = first0 + (int64_t)r * T;
+        if (first >= a.sp_off[s + 1]) break;  // the same for the whole workgroup
+        const int nt = (int)min((int64_t)T, a.sp_off[s + 1] - first);
+        if (tid < T) Es[tid] = tid < nt ? a.e[a.sp_idx[first + tid]] : 0.0f;
+        // zeros past the last atom and feature: their cotangents are exactly zero
+        {
+            const int t = tid >> 4;
+            const int64_t atom = t < nt ? a.sp_idx[first + t] : 0;
+            for (int q = tid & 15; q < FT; q += 16) {
+                const bool in = t < nt && q < F;
+                X[0][t * FS + q] = in ? a.G[atom * F + q] : 0.0f;
+                X[1][t * FS + q] = in ? a.w[atom * F + q] : 0.0f;
+            }
+        }
+        __syncthreads();
+        f32x4 d1[L][RT], d2z[L][RT];  // s'(z), s''(z) zt
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int ws = l == 0 ? a.Fpad : H, st = l == 0 ? FS : HS;
+            const float* const in0 = l == 0 ? X[0] : A + (2 * l - 2) * T * HS;
+            const float* const in1 = l == 0 ? X[1] : A + (2 * l - 1) * T * HS;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                if (rt >= nrt) continue;
+                const int o0 = 16 * (4 * rt + wv);
+                f32x4 z = *reinterpret_cast<const f32x4*>(bias + l * H + o0 + 4 * g), zt = {0.0f, 0.0f, 0.0f, 0.0f};
+                const float* const wr = w32 + a.w_off[l] + (int64_t)(o0 + col) * ws + 4 * g;
+                const float* const x0 = in0 + col * st + 4 * g;
+                const float* const x1 = in1 + col * st + 4 * g;
+                if (l == 0) {
+                    // (W has zero columns up to a multiple of 32)
+                    float4 w4 = *reinterpret_cast<const float4*>(wr);
+                    for (int k = 0; k < FT; k += 16) {
+                        const float4 wn = *reinterpret_cast<const float4*>(wr + min(k + 16, a.Fpad - 16));
+                        z = mfma4(w4, *reinterpret_cast<const float4*>(x0 + k), z);
+                        zt = mfma4(w4, *reinterpret_cast<const float4*>(x1 + k), zt);
+                        w4 = wn;
+                    }
+                } else {
+                    float4 w4[H / 16];
+#pragma unroll
+                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 16 * k);
+#pragma unroll
+                    for (int k = 0; k < H / 16; ++k) {
+                        z = mfma4(w4[k], *reinterpret_cast<const float4*>(x0 + 16 * k), z);
+                        zt = mfma4(w4[k], *reinterpret_cast<const float4*>(x1 + 16 * k), zt);
+                    }
+                }
+                f32x4 av, at;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float s0, s1, s2;
+                    act3(a.act, z[i], s0, s1, s2);
+                    av[i] = s0;
+                    at[i] = s1 * zt[i];
+                    d1[l][rt][i] = s1;
+                    d2z[l][rt][i] = s2 * zt[i];
+                }
+                *reinterpret_cast<f32x4*>(A + (2 * l) * T * HS + col * HS + o0 + 4 * g) = av;
+                *reinterpret_cast<f32x4*>(A + (2 * l + 1) * T * HS + col * HS + o0 + 4 * g) = at;
+            }
+            __syncthreads();
+        }
+        int offW[L], offb[L], off = 0;
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            offW[l] = off;
+            off += H * (l == 0 ? F : H);
+            offb[l] = off;
+            off += H;
+        }
+        auto put = [&](int k, float v) { gp[k] = r == 0 ? v : gp[k] + v; };
+        // output layer: E = w_out . a_L + b_out, q = w_out . at_L
+        for (int o = tid; o < H; o += 256) {
+            float gw = 0.0f;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                gw += Es[t] * A[(2 * L - 2) * T * HS + t * HS + o] - A[(2 * L - 1) * T * HS + t * HS + o];
+            put(off + o, gw);
+        }
+        if (tid == 255) {
+            float gb = 0.0f;
+#pragma unroll
+            for (int t = 0; t < T; ++t) gb += Es[t];
+            put(off + H, gb);
+        }
+        f32x4 ba[RT], bat[RT];  // cotangents of the layer's outputs
+        const float ecol = Es[col];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (rt >= nrt) continue;
+            const f32x4 wo = *reinterpret_cast<const f32x4*>(wout + 16 * (4 * rt + wv) + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ba[rt][i] = col < nt ? ecol * wo[i] : 0.0f;
+                bat[rt][i] = col < nt ? -wo[i] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int l = L - 1; l >= 0; --l) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                if (rt >= nrt) continue;
+                const int at = col * HS + 16 * (4 * rt + wv) + 4 * g;
+                *reinterpret_cast<f32x4*>(C + at) = d1[l][rt] * ba[rt] + d2z[l][rt] * bat[rt];
+                *reinterpret_cast<f32x4*>(C + T * HS + at) = d1[l][rt] * bat[rt];
+            }
+            __syncthreads();
+            const int wi = l == 0 ? F : H, st = l == 0 ? FS : HS;
+            const float* const in0 = l == 0 ? X[0] : A + (2 * l - 2) * T * HS;
+            const float* const in1 = l == 0 ? X[1] : A + (2 * l - 1) * T * HS;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                if (rt >= nrt) continue;
+                const int o0 = 16 * (4 * rt + wv);
+                float cz[4], czt[4];  // k = atom 4 j + g
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    cz[j] = C[(4 * j + g) * HS + o0 + col];
+                    czt[j] = C[T * HS + (4 * j + g) * HS + o0 + col];
+                }
+                for (int q0 = 0; q0 < wi; q0 += 16) {
+                    const int q = q0 + col;
+                    float* const dst = gp + offW[l] + (o0 + 4 * g) * wi + q;
+                    f32x4 gw = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (r > 0 && q < wi)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) gw[i] = dst[i * wi];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        gw = __builtin_amdgcn_mfma_f32_16x16x4f32(cz[j], in0[(4 * j + g) * st + q], gw, 0, 0, 0);
+                        gw = __builtin_amdgcn_mfma_f32_16x16x4f32(czt[j], in1[(4 * j + g) * st + q], gw, 0, 0, 0);
+                    }
+                    if (q < wi)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dst[i * wi] = gw[i];
+                }
+            }
+            for (int o = tid; o < H; o += 256) {
+                float gb = 0.0f;
+#pragma unroll
+                for (int t = 0; t < T; ++t) gb += C[t * HS + o];
+                put(offb[l] + o, gb);
+            }
+            if (l > 0) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    if (rt >= nrt) continue;
+                    const int q0 = 16 * (4 * rt + wv);
+                    const float* const wr = w32 + a.wt_off[l] + (int64_t)(q0 + col) * H + 4 * g;
+                    f32x4 sa = {0.0f, 0.0f, 0.0f, 0.0f}, sat = {0.0f, 0.0f, 0.0f, 0.0f};
+                    float4 w4[H / 16];
+#pragma unroll
+                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 16 * k);
+#pragma unroll
+                    for (int k = 0; k < H / 16; ++k) {
+                        const float* const c0 = C + col * HS + 16 * k + 4 * g;
+                        sa = mfma4(w4[k], *reinterpret_cast<const float4*>(c0), sa);
+                        sat = mfma4(w4[k], *reinterpret_cast<const float4*>(c0 + T * HS), sat);
+                    }
+                    ba[rt] = sa;
+                    bat[rt] = sat;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // Fixed-order reduction of the per-tile partials of each species, in two
 // passes so that it spreads over the chip: the tiles of species s form chunks
 // of kGradChunk consecutive tiles; pass one sums each chunk in tile order and
@@ -945,6 +1181,24 @@ void batch_free(tmd_batch* b) {
     b->tab = nullptr;
     b->cnt = nullptr;
     b->mirror = nullptr;
+}
+
+// The matrix-core form of the second-order pass takes up to three hidden layers
+// whose activations fit in LDS; the vector kernel the rest.
+bool mlp2_mfma(int F, int H, int L) { return L <= 3 && mlp2_mfma_lds(F, H, L) <= 150 * 1024; }
+using Mlp2Fn = void (*)(MlpTrainArgs);
+Mlp2Fn pick_mlp2(int H, int L) {
+    switch (H + L) {
+        case 33: return k_mlp_second_mfma<32, 1>;
+        case 34: return k_mlp_second_mfma<32, 2>;
+        case 35: return k_mlp_second_mfma<32, 3>;
+        case 65: return k_mlp_second_mfma<64, 1>;
+        case 66: return k_mlp_second_mfma<64, 2>;
+        case 67: return k_mlp_second_mfma<64, 3>;
+        case 129: return k_mlp_second_mfma<128, 1>;
+        case 130: return k_mlp_second_mfma<128, 2>;
+        default: return k_mlp_second_mfma<128, 3>;
+    }
 }
 
 // LDS bytes of k_mlp_second: activations [width][T | 1], a [H][QC + 1]
@@ -1159,7 +1413,9 @@ tmd_status tmd_batch_create(tmd_context* ctx, const tmd_model* m, int32_t n_syst
     {
         // sub-tiles per workgroup: enough that the grid fills the workgroup
         // slots the LDS allows about once
-        const size_t lds = mlp2_lds(m->F, m->H, m->L, tileT, tileQC);
+        const bool mfma = mlp2_mfma(m->F, m->H, m->L);
+        const size_t lds = mfma ? mlp2_mfma_lds(m->F, m->H, m->L) : mlp2_lds(m->F, m->H, m->L, tileT, tileQC);
+        if (mfma) b->tileT = tileT = kMlp2Tile;
         const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(160 * 1024 / lds)));
         const int64_t slots = (int64_t)ctx->num_cus * per_cu;
         int64_t sub = 0;
@@ -1271,7 +1527,17 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     t.e = b->e;
     t.params = m->params_int;
     t.partial = b->partial;
-    const size_t lds = mlp2_lds(t.F, t.H, t.L, t.T, t.QC);
+    t.w32 = m->w32;
+    t.bias = m->bias;
+    t.wout = m->wout;
+    t.wstride = m->w_species_stride;
+    for (int l = 0; l < m->L; ++l) {
+        t.w_off[l] = m->w_off[l];
+        t.wt_off[l] = m->wt_off[l];
+    }
+    t.Fpad = m->Fpad;
+    const bool mfma = mlp2_mfma(t.F, t.H, t.L);
+    const size_t lds = mfma ? mlp2_mfma_lds(t.F, t.H, t.L) : mlp2_lds(t.F, t.H, t.L, t.T, t.QC);
     // gradient in the ABI layout: reduced straight into it, or for a padded
     // model reduced in the padded layout and compacted
     float* gdst = grad ? grad : b->grad;
@@ -1285,10 +1551,9 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
         ProfScope ps_(ctx, "train_mlp2");
         // rows per thread and pass: H T / 256 (H and T powers of two), 1 to 4
         const int nr = std::max(1, std::min(4, t.H * t.T / 256));
-        using Mlp2 = void (*)(MlpTrainArgs);
-        Mlp2 kern = nullptr;
+        Mlp2Fn kern = mfma ? pick_mlp2(t.H, t.L) : nullptr;
 #define TMD_MLP2(TT) \
-    if (t.T == TT) kern = nr == 4 ? k_mlp_second<TT, 4> : nr == 2 ? k_mlp_second<TT, 2> : k_mlp_second<TT, 1>;
+    if (!mfma && t.T == TT) kern = nr == 4 ? k_mlp_second<TT, 4> : nr == 2 ? k_mlp_second<TT, 2> : k_mlp_second<TT, 1>;
         TMD_MLP2(8)
         TMD_MLP2(4)
         TMD_MLP2(2)

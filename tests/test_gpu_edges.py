@@ -13,6 +13,8 @@ the cell capacity of a wave and of its sharing over several waves).
   of a pass and of the window of force accumulators.  A merged list takes them
   too: each system of a batch against its own evaluation, FP32 sums in another
   order (the FP32 bars of tests/parity.py, relative to the same oracle).
+* The second-order pass of a training step over the network shapes it takes,
+  the bars of the training tests.
 * The kinetic energy of an MD step against the exact sum over the velocities
   read back: positive FP64 terms in strided sums of at most 8 terms, two trees
   of depth 6 and 16, and the closing scale of a thermostat, each rounding by
@@ -198,3 +200,44 @@ def test_merged_lists(ctx, K):
         for q, s in enumerate(systems):
             E, Ea, F, W = _evaluate(ctx, spec, s)
             parity.check_fp32(t[q, 0], Ea, forces[q].cpu().numpy().astype(np.float64), t[q, 1:], s, spec)
+
+
+# hidden widths 32, 64, 128 with one to three layers on the matrix cores and four
+# on the vector kernel; features that are no multiple of 16; 16 and 17, 1 and 15
+# atoms of a species (a full tile and one more, almost none and almost one)
+@pytest.mark.parametrize("K,M,hidden", [(8, 3, [20]), (6, 2, [32, 32]), (4, 1, [24] * 3), (8, 3, [64]),
+                                        (5, 3, [64, 48]), (8, 0, [64] * 3), (8, 3, [128]), (12, 3, [128, 100]),
+                                        (4, 3, [72] * 3), (8, 3, [64] * 4)])
+def test_second_order_pass_shapes(ctx, K, M, hidden):
+    import oracle
+    import torch
+    from paper_2310_08439_amd import tmd
+    print(f"[case] gradient, K = {K}, M = {M}, hidden {hidden}", flush=True)
+    sizes = [(16, 17), (1, 15)]
+    pos, sp, boxes, off = [], [], [], [0]
+    for q, (na, nb) in enumerate(sizes):
+        s = _thin(3, 3, 3, 2, 70 + q, na + nb)
+        pos.append(s.pos)
+        sp.append(np.array([0] * na + [1] * nb, dtype=np.int32))
+        boxes.append(s.box)
+        off.append(off[-1] + na + nb)
+    pos, sp, off = np.concatenate(pos), np.concatenate(sp), np.array(off, dtype=np.int64)
+    teacher = inputs.make_model(2, K, M, hidden, 5.0, seed=11)
+    student = inputs.make_model(2, K, M, hidden, 5.0, seed=12)
+    E_l, F_l = np.zeros(2), np.zeros((len(pos), 3))
+    for q in range(2):
+        a0, a1 = off[q], off[q + 1]
+        E_l[q], _, F_l[a0:a1], _ = oracle.energy_forces(teacher, pos[a0:a1], sp[a0:a1], boxes[q])
+    F_l = F_l.astype(np.float32)
+    model = tmd.Model(ctx, student)
+    bt = tmd.Batch(ctx, model, off, torch.tensor(pos, dtype=torch.float64, device="cuda"),
+                   torch.tensor(sp, device="cuda"), np.array(boxes), E_l, torch.tensor(F_l, device="cuda"))
+    grad = torch.empty(model.n_params, dtype=torch.float32, device="cuda")
+    loss = tmd.train_step(ctx, model, bt, lam=0.1, lr=0.0, grad=grad)[0]
+    lr_, _, _, gr = oracle.train_loss_grad(student, off, pos, sp, np.array(boxes), E_l, F_l, 0.1)
+    assert abs(loss - lr_) <= 1e-3 * lr_
+    g = grad.cpu().numpy().astype(np.float64)
+    assert np.abs(g - gr).max() <= 2e-3 * np.abs(gr).max()  # the bars of the training tests
+    assert np.linalg.norm(g - gr) <= 2e-3 * np.linalg.norm(gr)
+    bt.close()
+    model.close()
