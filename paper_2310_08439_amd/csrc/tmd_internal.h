@@ -383,10 +383,6 @@ tmd_status launch_compact_features(tmd_context* ctx, int64_t n, const float* in,
 tmd_status launch_export_nlist(tmd_context* ctx, const tmd_nlist* nl, int32_t* nbr, int32_t* img, int32_t* cnt);
 tmd_status launch_nlist_stats(tmd_context* ctx, const tmd_nlist* nl, int64_t* total_pairs, int32_t* max_row);
 
-// Regenerate the MLP operand copies (W, W^T in FP32 and BF16, biases, output
-// layer) of every species from the master parameters m->params32.
-tmd_status launch_unpack_params(tmd_context* ctx, tmd_model* m);
-
 // Pre-size a context's evaluation workspace for n atoms (avoids growth, and
 // the device-wide synchronisation it implies, later), and its size in bytes.
 tmd_status reserve_eval_workspace(tmd_context* ctx, const tmd_model* m, int64_t n);

@@ -57,7 +57,6 @@ struct tmd_batch {
     float4* g = nullptr;         // [N][S][cap]
     float* Fp = nullptr;         // [N][3]
     float* r = nullptr;          // [N][3]
-    float* e = nullptr;          // [N]
     float* w = nullptr;          // [N][F]
     double* sysE = nullptr;      // [B]
     double* sysF = nullptr;      // [B]
@@ -243,12 +242,16 @@ __device__ __forceinline__ void load_P(const PtArgs& a, int64_t i, int b, int ch
 }
 
 // Per-entry g = dE_i/dD_c (the adjoint chain of Sec. III.A); chunk lanes of
-// an atom are adjacent and combine their partial sums with shuffles.
+// an atom are adjacent and combine their partial sums with shuffles, and
+// kEntryLanes groups of them take the row's entries in turn (17,648 atoms, 60
+// entries each: 30 us; one group 46, with one wave on a SIMD).
+constexpr int kEntryLanes = 4, kTangentLanes = 8;
 template <int KC, int M>
 __global__ void __launch_bounds__(256) k_pt_adjoint(PtArgs a) {
     constexpr int D = Moments<M>::D;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t >> a.nch_log2;
+    const int64_t i = (t >> a.nch_log2) / kEntryLanes;
+    const int el = (int)(t >> a.nch_log2) % kEntryLanes;
     const int nch = 1 << a.nch_log2;
     const int ch = (int)(t & (nch - 1));
     if (i >= a.N) return;
@@ -281,7 +284,7 @@ __global__ void __launch_bounds__(256) k_pt_adjoint(PtArgs a) {
         }
         const int64_t row = (i * a.S + b) * a.cap;
         const int nb = a.cnt[i * a.S + b];
-        for (int c = 0; c < nb; ++c) {
+        for (int c = el; c < nb; c += kEntryLanes) {
             PairGeo p;
             float gx = 0.0f, gy = 0.0f, gz = 0.0f;
             if (pair_geo(a.tab[row + c], a.rc2, p)) {
@@ -323,12 +326,14 @@ __global__ void __launch_bounds__(256) k_pt_adjoint(PtArgs a) {
     }
 }
 
-// F_i = sum over i's entries of g_c - g_mirror(c).  Four adjacent lanes per
-// atom: lane l sums entries l, l + 4, ... of each row in order, then the
-// lanes combine in a fixed butterfly, so the result is reproducible.
+// F_i = sum over i's entries of g_c - g_mirror(c), and the residual
+// r_i = dL/dF_i = coef (F_i - Fhat_i), coef = 2 lambda / (3 N).  Four adjacent
+// lanes per atom: lane l sums entries l, l + 4, ... of each row in order, then
+// the lanes combine in a fixed butterfly, so the result is reproducible.
 constexpr int kForceLanes = 4;
 __global__ void k_pt_forces(int64_t N, int S, int cap, const int32_t* __restrict__ tcnt,
-                            const int32_t* __restrict__ mirror, const float4* __restrict__ g, float* __restrict__ F) {
+                            const int32_t* __restrict__ mirror, const float4* __restrict__ g, float* __restrict__ F,
+                            const float* __restrict__ Fl, float coef, float* __restrict__ r) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = t / kForceLanes;
     const int l = (int)(t % kForceLanes);
@@ -350,105 +355,112 @@ __global__ void k_pt_forces(int64_t N, int S, int cap, const int32_t* __restrict
         fy += __shfl_xor(fy, off);
         fz += __shfl_xor(fz, off);
     }
-    if (i < N && l == 0) {
-        F[3 * i + 0] = fx;
-        F[3 * i + 1] = fy;
-        F[3 * i + 2] = fz;
+    if (i < N && l < 3) {
+        const float f = l == 0 ? fx : (l == 1 ? fy : fz);
+        F[3 * i + l] = f;
+        r[3 * i + l] = coef * (f - Fl[3 * i + l]);
     }
 }
 
-// Per system: E_s = sum of atomic energies and sum |F - Fhat|^2, FP64, fixed
-// order (strided per thread, then a tree over the block).
-__global__ void __launch_bounds__(256) k_loss_sys(const int64_t* __restrict__ sys_off, const float* __restrict__ Ei,
-                                                  const float* __restrict__ F, const float* __restrict__ Fl,
-                                                  double* __restrict__ sysE, double* __restrict__ sysF) {
+// Workgroup s: E_s = sum of atomic energies and sum |F - Fhat|^2 of system s,
+// FP64, fixed order (strided per thread, then a tree over the block).  The last
+// workgroup to finish forms the loss terms (Neumaier over systems in order: the
+// threads form the terms of 256 systems at a time, thread 0 adds them) into
+// loss and host (pinned memory), and the per-system energy seed.
+__global__ void __launch_bounds__(256) k_loss(const int64_t* __restrict__ sys_off, const float* __restrict__ Ei,
+                                              const float* __restrict__ F, const float* __restrict__ Fl, int64_t N,
+                                              double lambda, const double* __restrict__ E_label, double* sysE,
+                                              double* sysF, unsigned int* counter, double* __restrict__ loss,
+                                              double* __restrict__ host, double* __restrict__ eseed) {
     __shared__ double se[256], sf[256];
-    const int s = blockIdx.x, t = threadIdx.x;
-    const int64_t lo = sys_off[s], hi = sys_off[s + 1];
-    double e = 0.0, f = 0.0;
-    for (int64_t i = lo + t; i < hi; i += 256) {
-        e += (double)Ei[i];
-        for (int x = 0; x < 3; ++x) {
-            const double d = (double)F[3 * i + x] - (double)Fl[3 * i + x];
-            f += d * d;
+    __shared__ bool last;
+    const int t = threadIdx.x, B = (int)gridDim.x;
+    {
+        const int s = blockIdx.x;
+        const int64_t lo = sys_off[s], hi = sys_off[s + 1];
+        double e = 0.0, f = 0.0;
+        for (int64_t i = lo + t; i < hi; i += 256) {
+            e += (double)Ei[i];
+            for (int x = 0; x < 3; ++x) {
+                const double d = (double)F[3 * i + x] - (double)Fl[3 * i + x];
+                f += d * d;
+            }
         }
-    }
-    se[t] = e;
-    sf[t] = f;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            se[t] += se[t + w];
-            sf[t] += sf[t + w];
+        se[t] = e;
+        sf[t] = f;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (t < w) {
+                se[t] += se[t + w];
+                sf[t] += sf[t + w];
+            }
+            __syncthreads();
+        }
+        if (t == 0) {
+            // device-scope stores done before the count: the last workgroup reads them from any XCD
+            __hip_atomic_store(sysE + s, se[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(sysF + s, sf[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            last = atomicInc(counter, B - 1) == (unsigned)(B - 1);
         }
         __syncthreads();
+        if (!last) return;
     }
-    if (t == 0) {
-        sysE[s] = se[0];
-        sysF[s] = sf[0];
-    }
-}
-
-// Loss terms (Neumaier over systems in order) and the per-system energy seed.
-// One workgroup of 256: the threads form the terms of 256 systems at a time,
-// thread 0 adds them in system order.
-__global__ void __launch_bounds__(256) k_loss_total(int B, int64_t N, double lambda,
-                                                    const int64_t* __restrict__ sys_off,
-                                                    const double* __restrict__ E_label, const double* __restrict__ sysE,
-                                                    const double* __restrict__ sysF, double* __restrict__ loss,
-                                                    double* __restrict__ eseed) {
-    __shared__ double te[256], tf[256];
-    const int tid = threadIdx.x;
     double le = 0.0, ce = 0.0, lf = 0.0, cf = 0.0;
     auto add = [](double& s, double& c, double x) {
-        const double t = s + x;
-        if (fabs(s) >= fabs(x)) c += (s - t) + x;
-        else c += (x - t) + s;
-        s = t;
+        const double z = s + x;
+        if (fabs(s) >= fabs(x)) c += (s - z) + x;
+        else c += (x - z) + s;
+        s = z;
     };
     for (int base = 0; base < B; base += 256) {
-        const int s = base + tid;
+        const int s = base + t;
         if (s < B) {
+            const double E = __hip_atomic_load(sysE + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const double f2 = __hip_atomic_load(sysF + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const double ns = (double)(sys_off[s + 1] - sys_off[s]);
-            const double de = (sysE[s] - E_label[s]) / ns;
-            te[tid] = de * de / (double)B;
-            tf[tid] = lambda * sysF[s] / (3.0 * (double)N);
-            eseed[s] = 2.0 / (double)B * (sysE[s] - E_label[s]) / (ns * ns);
+            const double de = (E - E_label[s]) / ns;
+            se[t] = de * de / (double)B;
+            sf[t] = lambda * f2 / (3.0 * (double)N);
+            eseed[s] = 2.0 / (double)B * (E - E_label[s]) / (ns * ns);
         }
         __syncthreads();
-        if (tid == 0)
+        if (t == 0)
             for (int k = 0; k < min(256, B - base); ++k) {
-                add(le, ce, te[k]);
-                add(lf, cf, tf[k]);
+                add(le, ce, se[k]);
+                add(lf, cf, sf[k]);
             }
         __syncthreads();
     }
-    if (tid == 0) {
-        loss[1] = le + ce;
-        loss[2] = lf + cf;
-        loss[0] = loss[1] + loss[2];
+    if (t == 0) {
+        const double l1 = le + ce, l2 = lf + cf;
+        loss[0] = host[0] = l1 + l2;
+        loss[1] = host[1] = l1;
+        loss[2] = host[2] = l2;
     }
 }
 
-// r_i = dL/dF_i = 2 lambda/(3N) (F_i - Fhat_i); e_i = seed of i's system.
-__global__ void k_residual(int64_t N, float coef, const int32_t* __restrict__ sys_of, const double* __restrict__ eseed,
-                           const float* __restrict__ F, const float* __restrict__ Fl, float* __restrict__ r,
-                           float* __restrict__ e) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    for (int x = 0; x < 3; ++x) r[3 * i + x] = coef * (F[3 * i + x] - Fl[3 * i + x]);
-    e[i] = (float)eseed[sys_of[i]];
+// The sum over aligned groups of eight lanes, in each of them (the third step
+// mirrors eight lanes, which swaps their quads, each already uniform).
+__device__ __forceinline__ float sum8(float v) {
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));
 }
 
 // Descriptor tangent along r: forward mode through pair geometry, radial
-// functions, monomials, P and S.
+// functions, monomials, P and S.  Eight lanes per (atom, chunk) take the
+// row's entries in turn (17,648 atoms, 60 entries each: 28 us; one lane and
+// half the chunk 40: the geometry repeated per chunk, one wave on a SIMD).
 template <int KC, int M>
 __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
+    constexpr int E = kTangentLanes;
     constexpr int D = Moments<M>::D;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t >> a.nch_log2;
-    const int ch = (int)(t & ((1 << a.nch_log2) - 1));
-    if (i >= a.N) return;
+    const int el = (int)(t % E);
+    const int64_t i = (t / E) >> a.nch_log2;
+    const int ch = (int)((t / E) & ((1 << a.nch_log2) - 1));
+    if (i >= a.N) return;  // whole groups
     float mu[KC], nef[KC], m2eta[KC];
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
@@ -465,12 +477,21 @@ __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
             for (int d = 0; d < D; ++d) Pt[kk][d] = 0.0f;
         const int64_t row = (i * a.S + b) * a.cap;
         const int nb = a.cnt[i * a.S + b];
-        for (int c = 0; c < nb; ++c) {
-            const float4 ent = a.tab[row + c];
+        // the next entry is fetched before this one's arithmetic and its neighbour's r after
+        float4 next = a.tab[row + min(el, max(nb - 1, 0))];
+        float jx = 0.0f, jy = 0.0f, jz = 0.0f;
+        if (el < nb) {
+            const int64_t j = __float_as_int(next.w);
+            jx = a.r[3 * j], jy = a.r[3 * j + 1], jz = a.r[3 * j + 2];
+        }
+        for (int c = el; c < nb; c += E) {
+            const float4 ent = next;
+            const float tx = jx - rix, ty = jy - riy, tz = jz - riz;
+            next = a.tab[row + min(c + E, nb - 1)];
+            const int64_t j = __float_as_int(next.w);
+            jx = a.r[3 * j], jy = a.r[3 * j + 1], jz = a.r[3 * j + 2];
             PairGeo p;
             if (!pair_geo(ent, a.rc2, p)) continue;
-            const int64_t j = __float_as_int(ent.w);
-            const float tx = a.r[3 * j] - rix, ty = a.r[3 * j + 1] - riy, tz = a.r[3 * j + 2] - riz;
             const float Rt = p.ux * tx + p.uy * ty + p.uz * tz;
             const float utx = (tx - p.ux * Rt) * p.rinv, uty = (ty - p.uy * Rt) * p.rinv,
                         utz = (tz - p.uz * Rt) * p.rinv;
@@ -490,6 +511,10 @@ __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
                 for (int d = 0; d < D; ++d) Pt[kk][d] = fmaf(dhR, Mv[d], fmaf(h, Mt[d], Pt[kk][d]));
             }
         }
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk)
+#pragma unroll
+            for (int d = 0; d < D; ++d) Pt[kk][d] = sum8(Pt[kk][d]);
         float P[KC][D];
         load_P<KC, D>(a, i, b, ch, P);
 #pragma unroll
@@ -503,7 +528,7 @@ __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
                 // m = 0: G = |P_k0|, so its tangent is sign(P_k0) times that of P_k0
                 float wv = st;
                 if (m == 0) wv = P[kk][0] > 0.0f ? Pt[kk][0] : (P[kk][0] < 0.0f ? -Pt[kk][0] : 0.0f);
-                a.w[i * a.F + (b * a.K + k) * (M + 1) + m] = wv;
+                if (el == m) a.w[i * a.F + (b * a.K + k) * (M + 1) + m] = wv;
             }
         }
     }
@@ -518,8 +543,9 @@ struct MlpTrainArgs {
     const int32_t* sp_idx;
     const float* G;
     const float* w;
-    const float* e;
-    const float* params;  // [S][P]
+    const double* eseed;    // [systems]
+    const int32_t* sys_of;  // [N]
+    const float* params;    // [S][P]
     float* partial;       // [tiles][P]
     // operand copies of the weights (the matrix-core kernel), as in tmd_model
     const float *w32, *bias, *wout;
@@ -600,7 +626,7 @@ __global__ void __launch_bounds__(256) k_mlp_second(MlpTrainArgs a) {
         // Past the tile's last atom the inputs, tangents and seeds are zero, so
         // the cotangents Cz, Czt of those columns are exactly zero and the sums
         // over the tile can run over all T columns.
-        if (tid < T) Es[tid] = tid < nt ? a.e[a.sp_idx[first + tid]] : 0.0f;
+        if (tid < T) Es[tid] = tid < nt ? (float)a.eseed[a.sys_of[a.sp_idx[first + tid]]] : 0.0f;
         for (int idx = tid; idx < F * T; idx += blockDim.x) {
             const int q = idx / T, t = idx - q * T;
             float g = 0.0f, wt = 0.0f;
@@ -836,7 +862,7 @@ __global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
         const int64_t first = first0 + (int64_t)r * T;
         if (first >= a.sp_off[s + 1]) break;  // the same for the whole workgroup
         const int nt = (int)min((int64_t)T, a.sp_off[s + 1] - first);
-        if (tid < T) Es[tid] = tid < nt ? a.e[a.sp_idx[first + tid]] : 0.0f;
+        if (tid < T) Es[tid] = tid < nt ? (float)a.eseed[a.sys_of[a.sp_idx[first + tid]]] : 0.0f;
         // zeros past the last atom and feature: their cotangents are exactly zero
         {
             const int t = tid >> 4;
@@ -1002,71 +1028,11 @@ __global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
     }
 }
 
-// Fixed-order reduction of the per-tile partials of each species, in two
-// passes so that it spreads over the chip: the tiles of species s form chunks
-// of kGradChunk consecutive tiles; pass one sums each chunk in tile order and
-// leaves the sum in the chunk's first row, pass two sums the chunks in order.
-constexpr int kGradChunk = 32;
-
-struct GradReduceArgs {
-    int S, P;
-    int64_t tile_off[kMaxSpecies + 1];   // tiles of species s: [tile_off[s], tile_off[s + 1])
-    int64_t chunk_off[kMaxSpecies + 1];  // chunks of species s: [chunk_off[s], chunk_off[s + 1])
-    float* partial;                      // [tiles][P]
-    float* grad;                         // [S][P]
-};
-
-// One thread per (chunk, parameter); workgroup x = chunk * pb + (parameter / 256)
-// with pb = ceil(P / 256).
-__global__ void __launch_bounds__(256) k_grad_chunks(GradReduceArgs a, int pb) {
-    const int64_t c = blockIdx.x / pb;
-    const int q = (int)(blockIdx.x - c * pb) * 256 + threadIdx.x;
-    if (q >= a.P) return;
-    int s = 0;
-    for (int k = 0; k < a.S; ++k)
-        if (c >= a.chunk_off[k] && c < a.chunk_off[k + 1]) s = k;
-    const int64_t lo = a.tile_off[s] + (c - a.chunk_off[s]) * kGradChunk;
-    const int64_t hi = min(lo + kGradChunk, a.tile_off[s + 1]);
-    float acc = 0.0f;
-#pragma unroll 8
-    for (int64_t tl = lo; tl < hi; ++tl) acc += a.partial[tl * a.P + q];
-    a.partial[lo * a.P + q] = acc;
-}
-
-// grad[s][q] = sum over the chunks of species s, in chunk order.
-__global__ void k_grad_reduce(GradReduceArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)a.S * a.P) return;
-    const int s = (int)(t / a.P), q = (int)(t - (int64_t)s * a.P);
-    float acc = 0.0f;
-#pragma unroll 8
-    for (int64_t lo = a.tile_off[s]; lo < a.tile_off[s + 1]; lo += kGradChunk) acc += a.partial[lo * a.P + q];
-    a.grad[t] = acc;
-}
-
-// Adam (or SGD when beta1 < 0) on the master weights.
-__global__ void k_optimizer(int64_t n, int adam, float lr, float b1, float b2, float eps, float c1, float c2,
-                            const float* __restrict__ g, float* __restrict__ theta, float* __restrict__ m,
-                            float* __restrict__ v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (!adam) {
-        theta[i] -= lr * g[i];
-        return;
-    }
-    const float mi = b1 * m[i] + (1.0f - b1) * g[i];
-    const float vi = b2 * v[i] + (1.0f - b2) * g[i] * g[i];
-    m[i] = mi;
-    v[i] = vi;
-    theta[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
 struct UnpackArgs {
     int S, L, H, Fpad;
     int64_t P, P_int, wstride;
     int64_t w_off[TMD_MAX_HIDDEN], wt_off[TMD_MAX_HIDDEN];
     ParamMap pm;
-    const float* params;
     float* params_int;  // null when the model is not padded
     float* w32;
     __hip_bfloat16* wbf;
@@ -1075,17 +1041,10 @@ struct UnpackArgs {
     float* bout;
 };
 
-// One thread per master parameter (ABI layout): write it to every operand
-// copy and to the padded master copy.  Padded entries are never written and
-// stay zero.
-__global__ void k_unpack(UnpackArgs u) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)u.S * u.P) return;
-    const int s = (int)(t / u.P);
-    const int64_t q = t - (int64_t)s * u.P;
-    const float v = u.params[t];
-    int l, o, c, kind;
-    const int64_t qi = u.pm.map(q, l, o, c, kind);
+// Parameter t of species s, at ABI index q: write it to every operand copy and
+// to the padded master copy.  Padded entries are never written and stay zero.
+__device__ __forceinline__ void unpack_param(const UnpackArgs& u, int s, int l, int o, int c, int kind, int64_t qi,
+                                             float v) {
     if (u.params_int) u.params_int[(int64_t)s * u.P_int + qi] = v;
     if (kind == 0) {
         float* ws = u.w32 + s * u.wstride;
@@ -1104,15 +1063,82 @@ __global__ void k_unpack(UnpackArgs u) {
     }
 }
 
-// Gradient of a padded model back to the ABI layout: out[s][q] = in[s][map(q)].
-__global__ void k_grad_compact(int S, int64_t P, int64_t P_int, ParamMap pm, const float* __restrict__ in,
-                               float* __restrict__ out) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)S * P) return;
-    const int s = (int)(t / P);
-    int l, o, c, kind;
-    const int64_t qi = pm.map(t - (int64_t)s * P, l, o, c, kind);
-    out[t] = in[(int64_t)s * P_int + qi];
+UnpackArgs unpack_args(tmd_model* m) {
+    UnpackArgs u{};
+    u.S = m->S;
+    u.L = m->L;
+    u.H = m->H;
+    u.Fpad = m->Fpad;
+    u.P = m->per_species;
+    u.P_int = m->per_species_int;
+    u.wstride = m->w_species_stride;
+    for (int l = 0; l < m->L; ++l) {
+        u.w_off[l] = m->w_off[l];
+        u.wt_off[l] = m->wt_off[l];
+    }
+    u.pm = param_map(m);
+    u.params_int = m->padded ? m->params_int : nullptr;
+    u.w32 = m->w32;
+    u.wbf = m->wbf;
+    u.bias = m->bias;
+    u.wout = m->wout;
+    u.bout = m->bout;
+    return u;
+}
+
+struct GradArgs {
+    int64_t tile_off[kMaxSpecies + 1];  // tiles of species s: [tile_off[s], tile_off[s + 1])
+    const float* partial;               // [tiles][P_int]
+    float* grad;                        // [S][P], the ABI layout
+    int update, adam;                   // Adam (or SGD) on the master weights
+    float lr, b1, b2, eps, c1, c2;
+    float* m;
+    float* v;
+    float* params;
+    UnpackArgs u;
+};
+
+// The gradient (ABI layout) from the tiles' partial rows in a fixed order, the
+// optimizer's step and the operand copies, one parameter at a time:
+// 32 parameters per workgroup, 32 threads each over the rows, so that reading
+// the rows is spread over the chip (1,103 rows of 6,337: 11 us; two passes
+// of summing, the update and the copies in launches of their own 19).
+__global__ void __launch_bounds__(1024) k_grad_update(GradArgs a) {
+    __shared__ float part[32][33];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int64_t t = (int64_t)blockIdx.x * 32 + x, np = (int64_t)a.u.S * a.u.P;
+    int l = 0, o = 0, c = 0, kind = 0, s = 0;
+    int64_t qi = 0;
+    float acc = 0.0f;
+    if (t < np) {
+        s = (int)(t / a.u.P);
+        qi = a.u.pm.map(t - (int64_t)s * a.u.P, l, o, c, kind);
+        const int64_t lo = a.tile_off[s], rows = a.tile_off[s + 1] - lo;
+        const int64_t r0 = rows * y / 32, r1 = rows * (y + 1) / 32;
+        const float* src = a.partial + (lo + r0) * a.u.P_int + qi;
+#pragma unroll 8
+        for (int64_t r = r0; r < r1; ++r, src += a.u.P_int) acc += *src;
+    }
+    part[y][x] = acc;
+    __syncthreads();
+    if (y != 0 || t >= np) return;
+    float g = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 32; ++k) g += part[k][x];
+    a.grad[t] = g;
+    if (!a.update) return;
+    float th = a.params[t];
+    if (!a.adam) {
+        th -= a.lr * g;
+    } else {
+        const float mi = a.b1 * a.m[t] + (1.0f - a.b1) * g;
+        const float vi = a.b2 * a.v[t] + (1.0f - a.b2) * g * g;
+        a.m[t] = mi;
+        a.v[t] = vi;
+        th -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    }
+    a.params[t] = th;
+    unpack_param(a.u, s, l, o, c, kind, qi, th);
 }
 
 using PtFn = void (*)(PtArgs);
@@ -1153,6 +1179,11 @@ int batch_kc(int K, int kc, int64_t N) {
     return kc;
 }
 
+// The tangent's chunk: two radial functions (146 registers, three waves on a
+// SIMD) where the model's chunk divides into them; four (276 registers, one
+// wave) took 44 us instead of 29 for 17,648 atoms.
+int tangent_kc(int kc) { return kc % 4 == 0 ? 2 : kc; }
+
 PtArgs pt_args(const tmd_batch* bt) {
     PtArgs a{};
     a.N = bt->N;
@@ -1174,7 +1205,7 @@ PtArgs pt_args(const tmd_batch* bt) {
 void batch_free(tmd_batch* b) {
     for (void* p : {(void*)b->sys_off, (void*)b->sys_of, (void*)b->species, (void*)b->sp_idx, (void*)b->E_label,
                     (void*)b->F_label, (void*)b->tab, (void*)b->cnt, (void*)b->mirror, (void*)b->G, (void*)b->P,
-                    (void*)b->Ei, (void*)b->dG, (void*)b->g, (void*)b->Fp, (void*)b->r, (void*)b->e, (void*)b->w,
+                    (void*)b->Ei, (void*)b->dG, (void*)b->g, (void*)b->Fp, (void*)b->r, (void*)b->w,
                     (void*)b->sysE, (void*)b->sysF, (void*)b->loss, (void*)b->partial, (void*)b->grad,
                     (void*)b->flag})
         if (p) (void)hipFree(p);
@@ -1319,7 +1350,6 @@ tmd_status tmd_batch_create(tmd_context* ctx, const tmd_model* m, int32_t n_syst
     alloc((void**)&b->dG, 4 * (size_t)N * m->F);
     alloc((void**)&b->Fp, 12 * (size_t)N);
     alloc((void**)&b->r, 12 * (size_t)N);
-    alloc((void**)&b->e, 4 * (size_t)N);
     alloc((void**)&b->w, 4 * (size_t)N * m->F);
     alloc((void**)&b->sysE, 8 * (size_t)n_systems);
     alloc((void**)&b->sysF, 8 * (size_t)n_systems);
@@ -1482,29 +1512,28 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     a.g = b->g;
     a.r = b->r;
     a.w = b->w;
-    const unsigned pt_grid = blocks_for(N * (b->K / b->kc));
     {
         ProfScope ps_(ctx, "train_adjoint");
-        pick_adjoint(b->kc, b->M)<<<pt_grid, kBlock, 0, ctx->stream>>>(a);
+        pick_adjoint(b->kc, b->M)<<<blocks_for(N * (b->K / b->kc) * kEntryLanes), kBlock, 0, ctx->stream>>>(a);
     }
     {
         ProfScope ps_(ctx, "train_forces");
-        k_pt_forces<<<blocks_for(N * kForceLanes), kBlock, 0, ctx->stream>>>(N, b->S, b->cap, b->cnt, b->mirror, b->g, b->Fp);
+        k_pt_forces<<<blocks_for(N * kForceLanes), kBlock, 0, ctx->stream>>>(N, b->S, b->cap, b->cnt, b->mirror, b->g, b->Fp,
+                                                                           b->F_label, (float)(2.0 * opts->lambda / (3.0 * (double)N)), b->r);
     }
     // 2. loss and seeds
     {
         ProfScope ps_(ctx, "train_loss");
-        double* eseed = b->loss + 4;
-        k_loss_sys<<<b->B, 256, 0, ctx->stream>>>(b->sys_off, b->Ei, b->Fp, b->F_label, b->sysE, b->sysF);
-        k_loss_total<<<1, 256, 0, ctx->stream>>>(b->B, N, opts->lambda, b->sys_off, b->E_label, b->sysE, b->sysF,
-                                                b->loss, eseed);
-        k_residual<<<blocks_for(N), kBlock, 0, ctx->stream>>>(N, (float)(2.0 * opts->lambda / (3.0 * (double)N)),
-                                                               b->sys_of, eseed, b->Fp, b->F_label, b->r, b->e);
+        k_loss<<<b->B, 256, 0, ctx->stream>>>(b->sys_off, b->Ei, b->Fp, b->F_label, N, opts->lambda, b->E_label,
+                                              b->sysE, b->sysF, ctx->d_counter, b->loss, ctx->h_totals, b->loss + 4);
     }
     // 3. descriptor tangent along r
     {
         ProfScope ps_(ctx, "train_tangent");
-        pick_tangent(b->kc, b->M)<<<pt_grid, kBlock, 0, ctx->stream>>>(a);
+        const int kc = tangent_kc(m->kc);
+        a.nch_log2 = 0;
+        while ((kc << a.nch_log2) < m->K) ++a.nch_log2;
+        pick_tangent(kc, b->M)<<<blocks_for(N * (b->K / kc) * kTangentLanes), kBlock, 0, ctx->stream>>>(a);
     }
     // 4. second-order network pass and gradient
     MlpTrainArgs t{};
@@ -1524,7 +1553,8 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     t.sp_idx = b->sp_idx;
     t.G = b->G;
     t.w = b->w;
-    t.e = b->e;
+    t.eseed = b->loss + 4;
+    t.sys_of = b->sys_of;
     t.params = m->params_int;
     t.partial = b->partial;
     t.w32 = m->w32;
@@ -1538,15 +1568,6 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     t.Fpad = m->Fpad;
     const bool mfma = mlp2_mfma(t.F, t.H, t.L);
     const size_t lds = mfma ? mlp2_mfma_lds(t.F, t.H, t.L) : mlp2_lds(t.F, t.H, t.L, t.T, t.QC);
-    // gradient in the ABI layout: reduced straight into it, or for a padded
-    // model reduced in the padded layout and compacted
-    float* gdst = grad ? grad : b->grad;
-    if (!grad && m->padded) {
-        hipError_t e = hipSuccess;
-        gdst = (float*)ctx->ws.get("train.grad_abi", sizeof(float) * (size_t)m->S * m->per_species, &e);
-        if (e != hipSuccess) return hip_fail(ctx, e, "gradient workspace");
-    }
-    float* gred = m->padded ? b->grad : gdst;
     {
         ProfScope ps_(ctx, "train_mlp2");
         // rows per thread and pass: H T / 256 (H and T powers of two), 1 to 4
@@ -1563,56 +1584,42 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
         if (b->tiles > 0) kern<<<(unsigned)b->tiles, 256, lds, ctx->stream>>>(t);
     }
     TMD_HIP(ctx, hipGetLastError());
-    {
-        GradReduceArgs g{};
-        g.S = m->S;
-        g.P = (int)m->per_species_int;
-        for (int q = 0; q <= m->S; ++q) {
-            g.tile_off[q] = b->tile_off[q];
-            g.chunk_off[q] = q == 0 ? 0
-                                    : g.chunk_off[q - 1] +
-                                          (b->tile_off[q] - b->tile_off[q - 1] + kGradChunk - 1) / kGradChunk;
-        }
-        g.partial = b->partial;
-        g.grad = gred;
-        ProfScope ps_(ctx, "train_grad_reduce");
-        const int pb = (g.P + 255) / 256;
-        if (g.chunk_off[m->S] > 0)
-            k_grad_chunks<<<(unsigned)(g.chunk_off[m->S] * pb), 256, 0, ctx->stream>>>(g, pb);
-        k_grad_reduce<<<blocks_for((int64_t)m->S * m->per_species_int), kBlock, 0, ctx->stream>>>(g);
-        if (m->padded)
-            k_grad_compact<<<blocks_for((int64_t)m->S * m->per_species), kBlock, 0, ctx->stream>>>(
-                m->S, m->per_species, m->per_species_int, param_map(m), gred, gdst);
-    }
-    TMD_HIP(ctx, hipGetLastError());
-    TMD_HIP(ctx, hipMemcpyAsync(ctx->h_totals, b->loss, sizeof(double) * 3, hipMemcpyDeviceToHost, ctx->stream));
-    // 5. update
-    if (opts->lr > 0.0) {
-        const int64_t np = (int64_t)m->S * m->per_species;
-        const bool adam = opts->optimizer == TMD_OPT_ADAM;
-        if (adam && !m->opt_m) {
+    // 5. gradient and update
+    const int64_t np = (int64_t)m->S * m->per_species;
+    GradArgs u{};
+    for (int s = 0; s <= m->S; ++s) u.tile_off[s] = b->tile_off[s];
+    u.partial = b->partial;
+    u.grad = grad ? grad : b->grad;
+    u.u = unpack_args(m);
+    u.params = m->params32;
+    u.update = opts->lr > 0.0 ? 1 : 0;
+    if (u.update) {
+        u.adam = opts->optimizer == TMD_OPT_ADAM ? 1 : 0;
+        if (u.adam && !m->opt_m) {
             TMD_HIP(ctx, hipMalloc((void**)&m->opt_m, 4 * (size_t)np));
             TMD_HIP(ctx, hipMalloc((void**)&m->opt_v, 4 * (size_t)np));
             TMD_HIP(ctx, hipMemsetAsync(m->opt_m, 0, 4 * (size_t)np, ctx->stream));
             TMD_HIP(ctx, hipMemsetAsync(m->opt_v, 0, 4 * (size_t)np, ctx->stream));
             m->opt_t = 0;
         }
-        float c1 = 1.0f, c2 = 1.0f;
-        if (adam) {
+        u.m = m->opt_m;
+        u.v = m->opt_v;
+        u.lr = (float)opts->lr;
+        u.b1 = (float)opts->beta1;
+        u.b2 = (float)opts->beta2;
+        u.eps = (float)opts->eps;
+        u.c1 = u.c2 = 1.0f;
+        if (u.adam) {
             m->opt_t += 1;
-            c1 = (float)(1.0 - std::pow(opts->beta1, (double)m->opt_t));
-            c2 = (float)(1.0 - std::pow(opts->beta2, (double)m->opt_t));
+            u.c1 = (float)(1.0 - std::pow(opts->beta1, (double)m->opt_t));
+            u.c2 = (float)(1.0 - std::pow(opts->beta2, (double)m->opt_t));
         }
-        {
-            ProfScope ps_(ctx, "train_update");
-            k_optimizer<<<blocks_for(np), kBlock, 0, ctx->stream>>>(np, adam ? 1 : 0, (float)opts->lr,
-                                                                     (float)opts->beta1, (float)opts->beta2,
-                                                                     (float)opts->eps, c1, c2, gdst, m->params32,
-                                                                     m->opt_m, m->opt_v);
-        }
-        TMD_HIP(ctx, hipGetLastError());
-        if ((st = launch_unpack_params(ctx, m)) != TMD_OK) return st;
     }
+    {
+        ProfScope ps_(ctx, "train_update");
+        k_grad_update<<<(unsigned)((np + 31) / 32), 1024, 0, ctx->stream>>>(u);
+    }
+    TMD_HIP(ctx, hipGetLastError());
     TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     for (int q = 0; q < 3; ++q) loss[q] = ctx->h_totals[q];
     return TMD_OK;
@@ -1643,33 +1650,3 @@ tmd_status tmd_batch_read(tmd_context* ctx, const tmd_batch* b, int32_t field, f
 }
 
 }  // extern "C"
-
-namespace tmd {
-
-tmd_status launch_unpack_params(tmd_context* ctx, tmd_model* m) {
-    UnpackArgs u{};
-    u.S = m->S;
-    u.L = m->L;
-    u.H = m->H;
-    u.Fpad = m->Fpad;
-    u.P = m->per_species;
-    u.P_int = m->per_species_int;
-    u.wstride = m->w_species_stride;
-    for (int l = 0; l < m->L; ++l) {
-        u.w_off[l] = m->w_off[l];
-        u.wt_off[l] = m->wt_off[l];
-    }
-    u.pm = param_map(m);
-    u.params = m->params32;
-    u.params_int = m->padded ? m->params_int : nullptr;
-    u.w32 = m->w32;
-    u.wbf = m->wbf;
-    u.bias = m->bias;
-    u.wout = m->wout;
-    u.bout = m->bout;
-    k_unpack<<<blocks_for((int64_t)m->S * m->per_species), kBlock, 0, ctx->stream>>>(u);
-    TMD_HIP(ctx, hipGetLastError());
-    return TMD_OK;
-}
-
-}  // namespace tmd
