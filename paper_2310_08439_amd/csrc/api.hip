@@ -88,15 +88,6 @@ tmd_status hip_fail(tmd_context* ctx, hipError_t e, const char* what) {
 
 namespace {
 
-uint16_t float_to_bf16_rne(float f) {
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (uint16_t)((u >> 16) | 0x40);  // NaN
-    const uint32_t lsb = (u >> 16) & 1u;
-    u += 0x7fffu + lsb;
-    return (uint16_t)(u >> 16);
-}
-
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 int choose_kc(int K) {
@@ -123,46 +114,24 @@ int padded_h(const int* hid, int L) {
     return 0;
 }
 
-// The operand copies of every species (W, W^T in FP32 and BF16 at the padded
-// sizes, biases, output layer) and the padded master copy, from ABI-layout
-// parameters; every padded entry is zero.
-tmd_status upload_params(tmd_model* m, const float* params) {
+// The master parameters, and from them on the device the operand copies of
+// every species (W, W^T in FP32 and BF16 at the padded sizes, biases, output
+// layer) and the padded master copy; clear: zero those first (every padded
+// entry stays zero).
+tmd_status upload_params(tmd_model* m, const float* params, bool clear) {
     tmd_context* ctx = m->ctx;
-    const int S = m->S, L = m->L, H = m->H, Fpad = m->Fpad;
-    const ParamMap pm = param_map(m);
-    std::vector<float> w32((size_t)S * m->w_species_stride, 0.0f);
-    std::vector<float> bias((size_t)S * L * H, 0.0f), wout((size_t)S * H, 0.0f), bout(S, 0.0f);
-    std::vector<float> pint(m->padded ? (size_t)S * m->per_species_int : 0, 0.0f);
-    for (int s = 0; s < S; ++s) {
-        const float* p = params + (size_t)s * m->per_species;
-        float* ws = w32.data() + (size_t)s * m->w_species_stride;
-        for (int64_t q = 0; q < m->per_species; ++q) {
-            int l, o, c, kind;
-            const int64_t qi = pm.map(q, l, o, c, kind);
-            const float v = p[q];
-            if (m->padded) pint[(size_t)s * m->per_species_int + qi] = v;
-            if (kind == 0) {
-                const int in_pad = (l == 0) ? Fpad : H;
-                ws[m->w_off[l] + (size_t)o * in_pad + c] = v;
-                ws[m->wt_off[l] + (size_t)c * H + o] = v;
-            } else if (kind == 1) {
-                bias[((size_t)s * L + l) * H + o] = v;
-            } else if (kind == 2) {
-                wout[(size_t)s * H + o] = v;
-            } else {
-                bout[s] = v;
-            }
-        }
+    const size_t S = (size_t)m->S, w = S * m->w_species_stride;
+    if (clear) {
+        TMD_HIP(ctx, hipMemsetAsync(m->w32, 0, w * 4, ctx->stream));
+        TMD_HIP(ctx, hipMemsetAsync(m->wbf, 0, w * 2, ctx->stream));
+        TMD_HIP(ctx, hipMemsetAsync(m->bias, 0, S * m->L * m->H * 4, ctx->stream));
+        TMD_HIP(ctx, hipMemsetAsync(m->wout, 0, S * m->H * 4, ctx->stream));
+        if (m->padded) TMD_HIP(ctx, hipMemsetAsync(m->params_int, 0, S * m->per_species_int * 4, ctx->stream));
     }
-    std::vector<uint16_t> wbf(w32.size());
-    for (size_t q = 0; q < w32.size(); ++q) wbf[q] = float_to_bf16_rne(w32[q]);
-    TMD_HIP(ctx, hipMemcpy(m->w32, w32.data(), w32.size() * 4, hipMemcpyHostToDevice));
-    TMD_HIP(ctx, hipMemcpy(m->wbf, wbf.data(), wbf.size() * 2, hipMemcpyHostToDevice));
-    TMD_HIP(ctx, hipMemcpy(m->bias, bias.data(), bias.size() * 4, hipMemcpyHostToDevice));
-    TMD_HIP(ctx, hipMemcpy(m->wout, wout.data(), wout.size() * 4, hipMemcpyHostToDevice));
-    TMD_HIP(ctx, hipMemcpy(m->bout, bout.data(), bout.size() * 4, hipMemcpyHostToDevice));
-    TMD_HIP(ctx, hipMemcpy(m->params32, params, (size_t)S * m->per_species * 4, hipMemcpyHostToDevice));
-    if (m->padded) TMD_HIP(ctx, hipMemcpy(m->params_int, pint.data(), pint.size() * 4, hipMemcpyHostToDevice));
+    TMD_HIP(ctx, hipMemcpyAsync(m->params32, params, S * m->per_species * 4, hipMemcpyHostToDevice, ctx->stream));
+    tmd_status st = launch_unpack_params(ctx, m);
+    if (st != TMD_OK) return st;
+    TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return TMD_OK;
 }
 
@@ -546,7 +515,7 @@ tmd_status tmd_model_create(tmd_context* ctx, const tmd_model_spec* spec, const 
         tmd_model_destroy(m);
         return hip_fail(ctx, e, "model allocation");
     }
-    tmd_status st = upload_params(m, params);
+    tmd_status st = upload_params(m, params, true);
     if (st != TMD_OK) {
         tmd_model_destroy(m);
         return st;
@@ -563,7 +532,7 @@ tmd_status tmd_model_set_params(tmd_model* m, const float* params) {
     const size_t bytes = (size_t)m->S * m->per_species * 4;
     if (m->opt_m) TMD_HIP(m->ctx, hipMemset(m->opt_m, 0, bytes));
     if (m->opt_v) TMD_HIP(m->ctx, hipMemset(m->opt_v, 0, bytes));
-    return upload_params(m, params);
+    return upload_params(m, params, false);
 }
 
 tmd_status tmd_model_get_params(const tmd_model* m, float* params) {

@@ -9,17 +9,16 @@
 // orientation the accumulator layout of one layer (lane = (row group, atom),
 // four consecutive rows per lane) is exactly the B-operand layout the next
 // layer needs, up to a fixed permutation of the reduction index that is
-// applied identically to the weights.  Activations therefore never leave
-// registers between layers.
+// applied identically to the weights, so where a wave holds whole layers the activations never leave
+// its registers.
 //   BF16: v_mfma_f32_16x16x32_bf16, operands rounded to BF16 (nearest-even),
 //         FP32 accumulation.  One K-step covers 32 hidden units: for lane
 //         group g the 8 operand slots hold units {4g..4g+3, 16+4g..16+4g+3}.
 //   FP32: v_mfma_f32_16x16x4_f32.  One K-step covers 4 units, lane group g
 //         holding unit 16*blk + 4g + r in step (blk, r).
-// A workgroup of 4 or 8 waves takes 128 atoms of one species; each
-// layer's weights (forward or transposed) are staged once per workgroup into
-// LDS in column chunks with padded rows, and all four waves read their MFMA
-// A operands from there.
+// Three forms: k_mlp (a layer's rows shared by four waves, weights from L2),
+// k_mlp_staged and k_mlp_resident (whole layers per wave, weights in LDS).  All
+// add a unit's products in the same order, so they agree bit for bit.
 #include "tmd_internal.h"
 
 namespace tmd {
@@ -50,35 +49,6 @@ struct MlpArgs {
     int L;
 };
 
-template <bool BF16>
-struct WT;
-template <>
-struct WT<true> {
-    using T = __hip_bfloat16;
-    // elements of row padding in LDS: rows 2 (mod 32) words apart, so that the
-    // 16 rows an A-operand read touches (8 bytes per lane) fall on distinct
-    // banks (with 8 elements, 4 words mod 32, every read was a two-way
-    // conflict: 7.8 conflict cycles per LDS instruction in the resident
-    // kernel, 0.06 with 4)
-    static constexpr int kPad = 4;
-    static constexpr int kChunk = 128;  // columns staged at a time
-};
-template <>
-struct WT<false> {
-    using T = float;
-    // measured at 1 M atoms (96-128-128-1, FP32): 1.31 ms with 4 elements of
-    // row padding (and with 44, 52 or 60), 1.03 ms with 20, 24, 28 or 36 (the
-    // staged tile is then 43-51 KB: three workgroups per CU instead of four)
-    static constexpr int kPad = 28;
-    static constexpr int kChunk = 64;
-};
-
-// LDS capacity in elements: 128 rows x (chunk + pad).
-template <bool BF16>
-constexpr int lds_elems() {
-    return 128 * (WT<BF16>::kChunk + WT<BF16>::kPad);
-}
-
 template <int ACT>
 __device__ __forceinline__ float act_f(float z) {
     constexpr int act = ACT;
@@ -107,23 +77,10 @@ __device__ __forceinline__ bf16x4 to_bf4(f32x4 v) {
     return r;
 }
 
-// Stage rows [0, nrows) x columns [c0, c0 + nc) of a row-major matrix with
-// `ld` elements per row into LDS rows of stride nc + pad.  All threads of the
-// workgroup take part; callers synchronise around it.
-template <bool BF16>
-__device__ __forceinline__ void stage(const typename WT<BF16>::T* W, int ld, int nrows, int c0, int nc,
-                                      typename WT<BF16>::T* lds) {
-    using T = typename WT<BF16>::T;
-    constexpr int V = 16 / sizeof(T);
-    const int per_row = nc / V, stride = nc + WT<BF16>::kPad;
-    for (int c = threadIdx.x; c < nrows * per_row; c += blockDim.x) {
-        const int r = c / per_row, k = (c - r * per_row) * V;
-        // rows are 8-byte aligned in LDS (not 16: see kPad)
-        const uint4 v = *reinterpret_cast<const uint4*>(W + (int64_t)r * ld + c0 + k);
-        uint2* d = reinterpret_cast<uint2*>(lds + r * stride + k);
-        d[0] = make_uint2(v.x, v.y);
-        d[1] = make_uint2(v.z, v.w);
-    }
+// n (a multiple of 8) weights to LDS by the whole workgroup; callers synchronise around it.
+__device__ __forceinline__ void copy_weights(const __hip_bfloat16* W, int n, __hip_bfloat16* lds) {
+    for (int c = threadIdx.x; c < n / 8; c += blockDim.x)
+        reinterpret_cast<uint4*>(lds)[c] = reinterpret_cast<const uint4*>(W)[c];
 }
 
 // B operand of the first layer: four consecutive features of one atom's
@@ -165,71 +122,98 @@ __device__ __forceinline__ void store_dg4(float* dG, int64_t atom, int F, int f0
         if (f0 + r < F) row[f0 + r] = v[r];
 }
 
-// Hidden layer (H x H): acc[ob][cb] += W x, x held in the accumulator layout
-// of the previous layer.  W is row-major [H][H] in global memory, staged
-// through LDS in CH-column chunks; all indices are compile-time.
-template <bool BF16, int H, int CB>
-__device__ __forceinline__ void dense_hidden(const typename WT<BF16>::T* W, typename WT<BF16>::T* lds,
-                                             const f32x4 (&x)[H / 16][CB], f32x4 (&acc)[H / 16][CB]) {
-    using T = typename WT<BF16>::T;
-    constexpr int NB = H / 16;
-    constexpr int CH = WT<BF16>::kChunk < H ? WT<BF16>::kChunk : H;
-    constexpr int stride = CH + WT<BF16>::kPad;
-    const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-#pragma unroll
-    for (int c0 = 0; c0 < H; c0 += CH) {
-        __syncthreads();
-        stage<BF16>(W, H, H, c0, CH, lds);
-        __syncthreads();
-        if constexpr (BF16) {
-#pragma unroll
-            for (int k0 = 0; k0 < CH; k0 += 32) {
-                const int blk = (c0 + k0) / 16;
-                bf16x8 bop[CB];
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) bop[cb] = cat8(to_bf4(x[blk][cb]), to_bf4(x[blk + 1][cb]));
-#pragma unroll
-                for (int ob = 0; ob < NB; ++ob) {
-                    const T* wr = lds + (16 * ob + col) * stride + k0 + 4 * grp;
-                    const bf16x8 av =
-                        cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
-                        acc[ob][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop[cb], acc[ob][cb], 0, 0, 0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k0 = 0; k0 < CH; k0 += 16) {
-                const int blk = (c0 + k0) / 16;
-#pragma unroll
-                for (int ob = 0; ob < NB; ++ob) {
-                    const f32x4 wv = *reinterpret_cast<const f32x4*>(lds + (16 * ob + col) * stride + k0 + 4 * grp);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int cb = 0; cb < CB; ++cb)
-                            acc[ob][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], x[blk][cb][r], acc[ob][cb], 0, 0, 0);
-                }
-            }
-        }
+// The operands of a matrix product Z = W X over a run of reduction blocks (16
+// values for FP32, 32 for BF16): W's rows straight from memory, X from LDS
+// (activations, [atom][H + pad]) or from the descriptor rows.
+template <bool BF16>
+struct Op;
+template <>
+struct Op<false> {
+    using A = f32x4;
+    static constexpr int kBlock = 16;  // reduction values per block
+    static constexpr int kPad = 4;     // floats of row padding of the activations
+    using X = float;
+    // W's rows 16 rb .., block k of nk
+    static __device__ __forceinline__ A load_w(const float* w, int nk, int rb, int k, int lane) {
+        return *reinterpret_cast<const f32x4*>(w + ((rb * nk + k) * 64 + lane) * 4);
     }
+    static __device__ __forceinline__ A load_x(const float* row, int k, int grp) {
+        return *reinterpret_cast<const f32x4*>(row + 16 * k + 4 * grp);
+    }
+    static __device__ __forceinline__ A load_g(const MlpArgs& a, int64_t atom, int k, int grp, bool valid) {
+        return load_g4(a.G, atom, a.F, 16 * k + 4 * grp, valid);
+    }
+    static __device__ __forceinline__ void store_x(float* row, int o0, f32x4 v) {
+        *reinterpret_cast<f32x4*>(row + o0) = v;
+    }
+    static __device__ __forceinline__ f32x4 mul(A w, A x, f32x4 c) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[r], x[r], c, 0, 0, 0);
+        return c;
+    }
+};
+template <>
+struct Op<true> {
+    using A = bf16x8;
+    static constexpr int kBlock = 32;
+    static constexpr int kPad = 4;
+    using X = __bf16;
+    static __device__ __forceinline__ A load_w(const __hip_bfloat16* w, int nk, int rb, int k, int lane) {
+        return *reinterpret_cast<const bf16x8*>(w + ((rb * nk + k) * 64 + lane) * 8);
+    }
+    static __device__ __forceinline__ A load_x(const __bf16* row, int k, int grp) {
+        const __bf16* p = row + 32 * k + 4 * grp;
+        return cat8(*reinterpret_cast<const bf16x4*>(p), *reinterpret_cast<const bf16x4*>(p + 16));
+    }
+    static __device__ __forceinline__ A load_g(const MlpArgs& a, int64_t atom, int k, int grp, bool valid) {
+        const int g0 = 32 * k + 4 * grp;
+        return cat8(load_gb4(a.Gb, atom, a.F, g0, valid), load_gb4(a.Gb, atom, a.F, g0 + 16, valid));
+    }
+    static __device__ __forceinline__ void store_x(__bf16* row, int o0, f32x4 v) {
+        *reinterpret_cast<bf16x4*>(row + o0) = to_bf4(v);
+    }
+    static __device__ __forceinline__ f32x4 mul(A w, A x, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
+    }
+};
+
+// LDS of k_mlp: two buffers of activations, one of the last layer's in FP32.
+template <bool BF16, int H, int CB>
+constexpr int mlp_lds_bytes() {
+    return 16 * CB * ((H + 4) * 4 + 2 * (H + Op<BF16>::kPad) * (int)sizeof(typename Op<BF16>::X));
 }
 
-template <bool BF16, int H, int L, int CB, int ACT, int NW>
-__global__ void __launch_bounds__(64 * NW) k_mlp(MlpArgs a) {
-    constexpr int NB = H / 16;
-    constexpr int kTile = NW * 16 * CB;
-    using T = typename WT<BF16>::T;
-    constexpr int PAD = WT<BF16>::kPad, CHUNK = WT<BF16>::kChunk;
-    __shared__ __attribute__((aligned(16))) T lds[lds_elems<BF16>()];
-    const int lane = threadIdx.x & 63;
+// One workgroup of four waves takes 16 CB atoms of one species.  Wave w owns a
+// quarter of every layer's output rows (in both directions, so s' stays in its
+// registers) and a quarter of dE/dG's; the activations pass between the waves
+// through LDS, one barrier per layer.  A wave's weight rows are nobody else's,
+// so they come straight from memory (L2), a whole layer ahead of the barrier it
+// needs.
+//
+// Bound by the chain of layers where atoms are few (32 atoms of 32-64-64: 8 us,
+// 16 with one wave per 16 atoms and weights staged in LDS), by the weights' way
+// from L2 where layers are many: 23,040 atoms of 512-128-128-128-128 in FP32
+// 134 us (staged 315; the products 69), 85,750 of 128-128-128-128 in BF16 61
+// (staged 119).  With the weights row-major instead of in operand order those
+// are 193 and 157 us.
+template <bool BF16, int H, int L, int CB, int ACT>
+__global__ void __launch_bounds__(256) k_mlp(MlpArgs a) {
+    using O = Op<BF16>;
+    using A = typename O::A;
+    using X = typename O::X;
+    constexpr int NB = H / 16, NW = NB >= 4 ? NB / 4 : 1;  // row blocks, and of one wave
+    constexpr int KB = H / O::kBlock;                      // reduction blocks of a hidden layer
+    constexpr int XS = H + O::kPad, ES = H + 4, kTile = 16 * CB;
+    constexpr int PF = 4;  // reduction blocks of the descriptor in flight
+    __shared__ __attribute__((aligned(16))) X xs[2][kTile * XS];
+    __shared__ __attribute__((aligned(16))) float last[kTile * ES];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int col = lane & 15, grp = lane >> 4;
     const int64_t tile = blockIdx.x;
     int s = 0;
     for (int q = 0; q < a.S; ++q)
         if (tile >= a.tile_off[q] && tile < a.tile_off[q + 1]) s = q;
-    const int64_t first = a.sp_off[s] + (tile - a.tile_off[s]) * kTile + (threadIdx.x >> 6) * (16 * CB);
+    const int64_t first = a.sp_off[s] + (tile - a.tile_off[s]) * kTile;
     const int64_t end = a.sp_off[s + 1];
     int64_t atom[CB];
     bool valid[CB];
@@ -239,187 +223,312 @@ __global__ void __launch_bounds__(64 * NW) k_mlp(MlpArgs a) {
         valid[cb] = r < end;
         atom[cb] = valid[cb] ? (int64_t)a.sp_idx[r] : 0;
     }
-    const T* wsp;
-    if constexpr (BF16) wsp = a.wbf + s * a.wstride;
-    else wsp = a.w32 + s * a.wstride;
+    const auto* wsp = [&] {
+        if constexpr (BF16) return a.wbf + s * a.wstride;
+        else return a.w32 + s * a.wstride;
+    }();
     const float* bias = a.bias + (int64_t)s * L * H;
+    const bool mine = wv * NW < NB;  // (H = 32: two waves own rows)
+    const int ob0 = mine ? wv * NW : 0;
 
-    f32x4 acc[NB][CB];
-    f32x4 x[NB][CB];
-    f32x4 dact[L][NB][CB];
+    f32x4 acc[NW][CB];
+    f32x4 dact[L][NW][CB];
+    A wr[NW][KB];  // this wave's rows of a hidden layer
+    auto load_layer = [&](int64_t off) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int k = 0; k < KB; ++k) wr[j][k] = O::load_w(wsp + off, KB, ob0 + j, k, lane);
+    };
+    auto dense = [&](const X* x) {
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            A xv[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) xv[cb] = O::load_x(x + (16 * cb + col) * XS, k, grp);
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[j][cb] = O::mul(wr[j][k], xv[cb], acc[j][cb]);
+        }
+    };
+    auto set_bias = [&](const float* bl) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            f32x4 init = {0, 0, 0, 0};
+            if (bl) init = *reinterpret_cast<const f32x4*>(bl + 16 * (ob0 + j) + 4 * grp);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[j][cb] = init;
+        }
+    };
+    auto activate = [&](int l) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float z = acc[j][cb][r];
+                    const float y = act_f<ACT>(z);
+                    dact[l][j][cb][r] = act_df<ACT>(z, y);
+                    acc[j][cb][r] = y;
+                }
+    };
+    auto give = [&](X* x) {
+        if (!mine) return;
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                O::store_x(x + (16 * cb + col) * XS, 16 * (ob0 + j) + 4 * grp, acc[j][cb]);
+    };
 
+    // ---- layer 1: W_1 [H][Fpad] times G^T, PF blocks ahead
+    set_bias(bias);
+    {
+        const auto* W = wsp + a.w_off[0];
+        const int nk = a.Fpad / O::kBlock;
+        A wb[PF][NW], gb[PF][CB];
+        auto fetch = [&](int q, int k) {
+            k = min(k, nk - 1);
+#pragma unroll
+            for (int j = 0; j < NW; ++j) wb[q][j] = O::load_w(W, nk, ob0 + j, k, lane);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) gb[q][cb] = O::load_g(a, atom[cb], k, grp, valid[cb]);
+        };
+#pragma unroll
+        for (int q = 0; q < PF; ++q) fetch(q, q);
+        for (int k0 = 0; k0 < nk; k0 += PF) {
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                if (k0 + q < nk) {
+#pragma unroll
+                    for (int j = 0; j < NW; ++j)
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) acc[j][cb] = O::mul(wb[q][j], gb[q][cb], acc[j][cb]);
+                }
+                if (k0 + q + PF < nk) fetch(q, k0 + q + PF);
+            }
+        }
+    }
+    int buf = 0;
+    // ---- hidden layers 2..L
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        if (l > 0) {
+            set_bias(bias + l * H);
+            dense(xs[buf]);
+            buf ^= 1;
+        }
+        activate(l);
+        if (l < L - 1) {
+            give(xs[buf]);
+            load_layer(a.w_off[l + 1]);
+            __syncthreads();
+        }
+    }
+
+    // ---- output layer: E = w_out . a_L + b_out; delta_L = w_out * act'(z_L)
+    const float* wo = a.wout + (int64_t)s * H;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+        const f32x4 wv4 = *reinterpret_cast<const f32x4*>(wo + 16 * (ob0 + j) + 4 * grp);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            if (mine) *reinterpret_cast<f32x4*>(last + (16 * cb + col) * ES + 16 * (ob0 + j) + 4 * grp) = acc[j][cb];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][cb][r] = wv4[r] * dact[L - 1][j][cb][r];
+        }
+    }
+    give(xs[buf]);
+    if (L > 1) load_layer(a.wt_off[L - 1]);
+    __syncthreads();
+    const float bo = a.bout[s];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        if ((cb & 3) != wv) continue;  // one wave per 16 atoms
+        float e = 0.0f;
+#pragma unroll
+        for (int ob = 0; ob < NB; ++ob) {
+            const f32x4 w4 = *reinterpret_cast<const f32x4*>(wo + 16 * ob + 4 * grp);
+            const f32x4 y = *reinterpret_cast<const f32x4*>(last + (16 * cb + col) * ES + 16 * ob + 4 * grp);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e = fmaf(w4[r], y[r], e);
+        }
+        e += __shfl_xor(e, 16);
+        e += __shfl_xor(e, 32);
+        if (grp == 0 && valid[cb]) a.Ei[atom[cb]] = e + bo;
+    }
+
+    // ---- backward through hidden layers: delta_{l-1} = (W_l^T delta_l) * act'(z_{l-1})
+#pragma unroll
+    for (int l = L - 1; l >= 1; --l) {
+        set_bias(nullptr);
+        dense(xs[buf]);
+        buf ^= 1;
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[j][cb][r] *= dact[l - 1][j][cb][r];
+        give(xs[buf]);
+        if (l > 1) load_layer(a.wt_off[l - 1]);
+        __syncthreads();
+    }
+
+    // ---- dE/dG^T = W_1^T delta_1: Fpad output rows, a block of 16 at a time
+    // per wave, the next block's weights in flight
+    {
+        const auto* W = wsp + a.wt_off[0];
+        const int nf = a.Fpad / 16;
+        A xv[KB][CB];
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) xv[k][cb] = O::load_x(xs[buf] + (16 * cb + col) * XS, k, grp);
+        A wb[KB];
+#pragma unroll
+        for (int k = 0; k < KB; ++k) wb[k] = O::load_w(W, KB, min(wv, nf - 1), k, lane);
+        for (int fb = wv; fb < nf; fb += 4) {
+            A wn[KB];
+#pragma unroll
+            for (int k = 0; k < KB; ++k) wn[k] = O::load_w(W, KB, min(fb + 4, nf - 1), k, lane);
+            f32x4 out[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) out[cb] = f32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < KB; ++k)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) out[cb] = O::mul(wb[k], xv[k][cb], out[cb]);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) store_dg4(a.dG, atom[cb], a.F, 16 * fb + 4 * grp, valid[cb], out[cb]);
+#pragma unroll
+            for (int k = 0; k < KB; ++k) wb[k] = wn[k];
+        }
+    }
+}
+
+// Staged form (BF16, H = 128, one or two hidden layers): eight waves take 16
+// atoms each, activations never leave a wave's registers, and each layer's
+// weights pass once per 128 atoms through LDS.  It fills the chip in one round
+// from 16,384 to 65,536 atoms, where the form above needs two or three: 54,000
+// atoms, 96-128-128-1: 21 us against 32.
+template <int L, int ACT>
+__global__ void __launch_bounds__(512) k_mlp_staged(MlpArgs a) {
+    using O = Op<true>;
+    using T = __hip_bfloat16;
+    constexpr int H = 128, NB = H / 16, KB = H / 32;
+    constexpr int kPanel = H * H;  // weights staged at a time
+    __shared__ __attribute__((aligned(16))) T lds[kPanel];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t tile = blockIdx.x;
+    int s = 0;
+    for (int q = 0; q < a.S; ++q)
+        if (tile >= a.tile_off[q] && tile < a.tile_off[q + 1]) s = q;
+    const int64_t r = a.sp_off[s] + (tile - a.tile_off[s]) * 128 + wv * 16 + col;
+    const bool valid = r < a.sp_off[s + 1];
+    const int64_t atom = valid ? (int64_t)a.sp_idx[r] : 0;
+    const T* wsp = a.wbf + s * a.wstride;
+    const float* bias = a.bias + (int64_t)s * L * H;
+    f32x4 acc[NB], x[NB], dact[L][NB];
     auto set_bias = [&](const float* bl) {
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob) {
             f32x4 init = {0, 0, 0, 0};
             if (bl) init = *reinterpret_cast<const f32x4*>(bl + 16 * ob + 4 * grp);
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = init;
+            acc[ob] = init;
         }
     };
     auto activate = [&](int l) {
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float z = acc[ob][cb][r];
-                    const float y = act_f<ACT>(z);
-                    dact[l][ob][cb][r] = act_df<ACT>(z, y);
-                    acc[ob][cb][r] = y;
-                }
-    };
-    auto keep = [&]() {
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) x[ob][cb] = acc[ob][cb];
-    };
-
-    // ---- layer 1: W_1 [H][Fpad] times G^T, weights staged in column chunks
-    set_bias(bias);
-    {
-        const T* W = wsp + a.w_off[0];
-        for (int c0 = 0; c0 < a.Fpad; c0 += CHUNK) {
-            const int nc = min(CHUNK, a.Fpad - c0);
-            const int stride = nc + PAD;
-            __syncthreads();
-            stage<BF16>(W, a.Fpad, H, c0, nc, lds);
-            __syncthreads();
-            if constexpr (BF16) {
-                for (int k0 = 0; k0 < nc; k0 += 32) {
-                    bf16x8 bop[CB];
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) {
-                        const int g0 = c0 + k0 + 4 * grp;
-                        bop[cb] = cat8(load_gb4(a.Gb, atom[cb], a.F, g0, valid[cb]),
-                                       load_gb4(a.Gb, atom[cb], a.F, g0 + 16, valid[cb]));
-                    }
-#pragma unroll
-                    for (int ob = 0; ob < NB; ++ob) {
-                        const T* wr = lds + (16 * ob + col) * stride + k0 + 4 * grp;
-                        const bf16x8 av =
-                            cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
-#pragma unroll
-                        for (int cb = 0; cb < CB; ++cb)
-                            acc[ob][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop[cb], acc[ob][cb], 0, 0, 0);
-                    }
-                }
-            } else {
-                for (int k0 = 0; k0 < nc; k0 += 16) {
-                    f32x4 bv[CB];
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) bv[cb] = load_g4(a.G, atom[cb], a.F, c0 + k0 + 4 * grp, valid[cb]);
-#pragma unroll
-                    for (int ob = 0; ob < NB; ++ob) {
-                        const f32x4 wv =
-                            *reinterpret_cast<const f32x4*>(lds + (16 * ob + col) * stride + k0 + 4 * grp);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int cb = 0; cb < CB; ++cb)
-                                acc[ob][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], bv[cb][r], acc[ob][cb], 0, 0, 0);
-                    }
-                }
+            for (int q = 0; q < 4; ++q) {
+                const float z = acc[ob][q];
+                const float y = act_f<ACT>(z);
+                dact[l][ob][q] = act_df<ACT>(z, y);
+                acc[ob][q] = y;
             }
+    };
+    auto dense = [&](const T* W) {
+#pragma unroll
+        for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
+        __syncthreads();
+        copy_weights(W, H * H, lds);
+        __syncthreads();
+    };
+    auto product = [&]() {
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            const bf16x8 bop = cat8(to_bf4(x[2 * k]), to_bf4(x[2 * k + 1]));
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(O::load_w(lds, KB, ob, k, lane), bop, acc[ob]);
+        }
+    };
+    // layer 1, up to KB blocks of 32 features at a time
+    set_bias(bias);
+    const int nk = a.Fpad / 32;
+    for (int c = 0; c < nk; c += KB) {
+        const int n = min(KB, nk - c);
+        __syncthreads();
+        for (int q = threadIdx.x; q < NB * n * 64; q += 512) {
+            const int ob = q / (n * 64), e = q - ob * (n * 64);
+            reinterpret_cast<uint4*>(lds)[q] = reinterpret_cast<const uint4*>(wsp + a.w_off[0])[(ob * nk + c) * 64 + e];
+        }
+        __syncthreads();
+        for (int k = 0; k < n; ++k) {
+            const bf16x8 bop = O::load_g(a, atom, c + k, grp, valid);
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(O::load_w(lds, n, ob, k, lane), bop, acc[ob]);
         }
     }
     activate(0);
-    // ---- hidden layers 2..L
 #pragma unroll
     for (int l = 1; l < L; ++l) {
-        keep();
+        dense(wsp + a.w_off[l]);
         set_bias(bias + l * H);
-        dense_hidden<BF16, H, CB>(wsp + a.w_off[l], lds, x, acc);
+        product();
         activate(l);
     }
-
-    // ---- output layer: E = w_out . a_L + b_out; delta_L = w_out * act'(z_L)
     const float* wo = a.wout + (int64_t)s * H;
-    float e[CB];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) e[cb] = 0.0f;
+    float e = 0.0f;
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-        const f32x4 wv = *reinterpret_cast<const f32x4*>(wo + 16 * ob + 4 * grp);
+        const f32x4 w4 = *reinterpret_cast<const f32x4*>(wo + 16 * ob + 4 * grp);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                e[cb] = fmaf(wv[r], acc[ob][cb][r], e[cb]);
-                acc[ob][cb][r] = wv[r] * dact[L - 1][ob][cb][r];
-            }
+        for (int q = 0; q < 4; ++q) {
+            e = fmaf(w4[q], acc[ob][q], e);
+            acc[ob][q] = w4[q] * dact[L - 1][ob][q];
+        }
     }
-    const float bo = a.bout[s];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        float v = e[cb];
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        if (grp == 0 && valid[cb]) a.Ei[atom[cb]] = v + bo;
-    }
-
-    // ---- backward through hidden layers: delta_{l-1} = (W_l^T delta_l) * act'(z_{l-1})
+    e += __shfl_xor(e, 16);
+    e += __shfl_xor(e, 32);
+    if (grp == 0 && valid) a.Ei[atom] = e + a.bout[s];
 #pragma unroll
     for (int l = L - 1; l >= 1; --l) {
-        keep();
+        dense(wsp + a.wt_off[l]);
         set_bias(nullptr);
-        dense_hidden<BF16, H, CB>(wsp + a.wt_off[l], lds, x, acc);
+        product();
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[ob][cb][r] *= dact[l - 1][ob][cb][r];
+            for (int q = 0; q < 4; ++q) acc[ob][q] *= dact[l - 1][ob][q];
     }
-
-    // ---- dE/dG^T = W_1^T delta_1: Fpad output rows; W_1^T [Fpad][H] is
-    // staged in panels of PR full rows.
-    constexpr int NS = NB / 2 > 0 ? NB / 2 : 1;
-    bf16x8 bop[NS][CB];
-    if constexpr (BF16) {
+    bf16x8 bop[KB];
 #pragma unroll
-        for (int s2 = 0; s2 < NB / 2; ++s2)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) bop[s2][cb] = cat8(to_bf4(acc[2 * s2][cb]), to_bf4(acc[2 * s2 + 1][cb]));
-    }
-    const T* w1t = wsp + a.wt_off[0];
-    constexpr int PR = lds_elems<BF16>() / (H + PAD) / 16 * 16;
-    for (int r0 = 0; r0 < a.Fpad; r0 += PR) {
-        const int nr = min(PR, a.Fpad - r0);
+    for (int k = 0; k < KB; ++k) bop[k] = cat8(to_bf4(acc[2 * k]), to_bf4(acc[2 * k + 1]));
+    for (int f0 = 0; f0 < a.Fpad; f0 += H) {
+        const int nf = min(H, a.Fpad - f0) / 16;
         __syncthreads();
-        stage<BF16>(w1t + (int64_t)r0 * H, H, nr, 0, H, lds);
+        copy_weights(wsp + a.wt_off[0] + (int64_t)f0 * H, nf * 16 * H, lds);
         __syncthreads();
-        for (int fb = 0; fb < nr / 16; ++fb) {
-            f32x4 out[CB];
+        for (int fb = 0; fb < nf; ++fb) {
+            f32x4 out = {0, 0, 0, 0};
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) out[cb] = f32x4{0, 0, 0, 0};
-            if constexpr (BF16) {
-#pragma unroll
-                for (int s2 = 0; s2 < NB / 2; ++s2) {
-                    const T* wr = lds + (16 * fb + col) * (H + PAD) + 32 * s2 + 4 * grp;
-                    const bf16x8 av =
-                        cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
-                        out[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop[s2][cb], out[cb], 0, 0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int blk = 0; blk < NB; ++blk) {
-                    const f32x4 wv =
-                        *reinterpret_cast<const f32x4*>(lds + (16 * fb + col) * (H + PAD) + 16 * blk + 4 * grp);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int cb = 0; cb < CB; ++cb)
-                            out[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[r], acc[blk][cb][r], out[cb], 0, 0, 0);
-                }
-            }
-            const int f0 = r0 + 16 * fb + 4 * grp;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) store_dg4(a.dG, atom[cb], a.F, f0, valid[cb], out[cb]);
+            for (int k = 0; k < KB; ++k) out = O::mul(O::load_w(lds, KB, fb, k, lane), bop[k], out);
+            store_dg4(a.dG, atom, a.F, f0 + 16 * fb + 4 * grp, valid, out);
         }
     }
 }
@@ -430,35 +539,30 @@ __global__ void __launch_bounds__(64 * NW) k_mlp(MlpArgs a) {
 // take 16-atom tiles independently, with no barrier between layers.  The
 // weights are staged once per species and workgroup instead of once per
 // 128-atom tile (at 1 M atoms that is ~30 MB of L2 traffic instead of ~0.9 GB).
-template <int H, int L>
-constexpr int resident_rows_elems(int Fpad) {
-    return H * (Fpad + WT<true>::kPad) + 2 * (L - 1) * H * (H + WT<true>::kPad) + Fpad * (H + WT<true>::kPad);
-}
-
 template <int H, int L, int ACT>
 __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
     using T = __hip_bfloat16;
-    constexpr int NB = H / 16, PAD = WT<true>::kPad;
+    constexpr int NB = H / 16, KB = H / 32;
     extern __shared__ __attribute__((aligned(16))) T sw[];
     const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4, wv = threadIdx.x >> 6;
     const int nw = blockDim.x >> 6;
-    const int s1 = a.Fpad + PAD, sh = H + PAD;
-    T* W1 = sw;                        // [H][Fpad + PAD]
-    T* Wh = W1 + H * s1;               // L-1 x [H][H + PAD]
-    T* Wt = Wh + (L - 1) * H * sh;     // L-1 x [H][H + PAD], transposed hidden layers
-    T* W1t = Wt + (L - 1) * H * sh;    // [Fpad][H + PAD]
+    // in operand order, as in memory: a read is 1 KB in a run, free of bank conflicts
+    T* W1 = sw;                        // [H][Fpad]
+    T* Wh = W1 + H * a.Fpad;           // L-1 x [H][H]
+    T* Wt = Wh + (L - 1) * H * H;      // L-1 x [H][H], transposed hidden layers
+    T* W1t = Wt + (L - 1) * H * H;     // [Fpad][H]
     for (int s = 0; s < a.S; ++s) {
         const int64_t first_atom = a.sp_off[s], end = a.sp_off[s + 1];
         const int64_t ntiles = (end - first_atom + 15) / 16;
         if (ntiles == 0) continue;  // uniform over the workgroup
         const T* wsp = a.wbf + s * a.wstride;
         __syncthreads();  // the previous species' tiles are done with the LDS copy
-        stage<true>(wsp + a.w_off[0], a.Fpad, H, 0, a.Fpad, W1);
+        copy_weights(wsp + a.w_off[0], H * a.Fpad, W1);
         for (int l = 1; l < L; ++l) {
-            stage<true>(wsp + a.w_off[l], H, H, 0, H, Wh + (l - 1) * H * sh);
-            stage<true>(wsp + a.wt_off[l], H, H, 0, H, Wt + (l - 1) * H * sh);
+            copy_weights(wsp + a.w_off[l], H * H, Wh + (l - 1) * H * H);
+            copy_weights(wsp + a.wt_off[l], H * H, Wt + (l - 1) * H * H);
         }
-        stage<true>(wsp + a.wt_off[0], H, a.Fpad, 0, H, W1t);
+        copy_weights(wsp + a.wt_off[0], H * a.Fpad, W1t);
         __syncthreads();
         const float* bias = a.bias + (int64_t)s * L * H;
         const float* wo = a.wout + (int64_t)s * H;
@@ -494,13 +598,12 @@ __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
             auto dense = [&](const T* Wm) {
 #pragma unroll
                 for (int k0 = 0; k0 < H; k0 += 32) {
+                    __asm__ volatile("" ::: "memory");  // one block's weights in flight at a time
                     const int blk = k0 / 16;
                     const bf16x8 bop = cat8(to_bf4(x[blk]), to_bf4(x[blk + 1]));
 #pragma unroll
                     for (int ob = 0; ob < NB; ++ob) {
-                        const T* wr = Wm + (16 * ob + col) * sh + k0 + 4 * grp;
-                        const bf16x8 av =
-                            cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
+                        const bf16x8 av = Op<true>::load_w(Wm, KB, ob, k0 / 32, lane);
                         acc[ob] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop, acc[ob], 0, 0, 0);
                     }
                 }
@@ -512,9 +615,7 @@ __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
                 const bf16x8 bop = cat8(load_gb4(a.Gb, atom, a.F, g0, valid), load_gb4(a.Gb, atom, a.F, g0 + 16, valid));
 #pragma unroll
                 for (int ob = 0; ob < NB; ++ob) {
-                    const T* wr = W1 + (16 * ob + col) * s1 + k0 + 4 * grp;
-                    const bf16x8 av =
-                        cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
+                    const bf16x8 av = Op<true>::load_w(W1, a.Fpad / 32, ob, k0 / 32, lane);
                     acc[ob] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop, acc[ob], 0, 0, 0);
                 }
             }
@@ -525,7 +626,7 @@ __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
 #pragma unroll
                 for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
                 set_bias(bias + l * H);
-                dense(Wh + (l - 1) * H * sh);
+                dense(Wh + (l - 1) * H * H);
                 activate(l);
             }
             // output layer and its adjoint
@@ -549,7 +650,7 @@ __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
 #pragma unroll
                 for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
                 set_bias(nullptr);
-                dense(Wt + (l - 1) * H * sh);
+                dense(Wt + (l - 1) * H * H);
 #pragma unroll
                 for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
@@ -564,9 +665,7 @@ __global__ void __launch_bounds__(1024) k_mlp_resident(MlpArgs a) {
                 f32x4 out = {0, 0, 0, 0};
 #pragma unroll
                 for (int s2 = 0; s2 < NB / 2; ++s2) {
-                    const T* wr = W1t + (16 * fb + col) * sh + 32 * s2 + 4 * grp;
-                    const bf16x8 av =
-                        cat8(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16));
+                    const bf16x8 av = Op<true>::load_w(W1t, KB, fb, s2, lane);
                     out = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bop[s2], out, 0, 0, 0);
                 }
                 store_dg4(a.dG, atom, a.F, 16 * fb + 4 * grp, valid, out);
@@ -584,10 +683,7 @@ ResidentFn pick_resident(int H, int L) {
     if (H == 64 && L == 3) return k_mlp_resident<64, 3, ACT>;
     return nullptr;
 }
-int resident_lds_bytes(int H, int L, int Fpad) {
-    const int pad = 4;
-    return 2 * (H * (Fpad + pad) + 2 * (L - 1) * H * (H + pad) + Fpad * (H + pad));
-}
+int resident_lds_bytes(int H, int L, int Fpad) { return 2 * (2 * H * Fpad + 2 * (L - 1) * H * H); }
 constexpr int kMaxResidentLds = 150 * 1024;
 
 using MlpFn = void (*)(MlpArgs);
@@ -597,35 +693,28 @@ using MlpFn = void (*)(MlpArgs);
 // activations and derivatives fit in far fewer registers (4 waves per SIMD
 // for two hidden layers), with 8 waves per workgroup so that each staged
 // weight panel is still shared by 128 atoms.
-struct MlpShape {
-    MlpFn fn;
-    int cb, waves;
-};
-
-template <bool BF16, int H, int ACT>
-MlpShape pick_L(int L) {
-    constexpr int C = (H == 128) ? 1 : 2;
-    constexpr int W = (H == 128) ? 8 : 4;  // deeper H = 128 nets: 4 waves, up to 512 registers
+template <bool BF16, int H, int ACT, int CB>
+MlpFn pick_L(int L) {
     switch (L) {
-        case 1: return {k_mlp<BF16, H, 1, C, ACT, W>, C, W};
-        case 2: return {k_mlp<BF16, H, 2, C, ACT, W>, C, W};
-        case 3: return {k_mlp<BF16, H, 3, C, ACT, 4>, C, 4};
-        default: return {k_mlp<BF16, H, 4, C, ACT, 4>, C, 4};
+        case 1: return k_mlp<BF16, H, 1, CB, ACT>;
+        case 2: return k_mlp<BF16, H, 2, CB, ACT>;
+        case 3: return k_mlp<BF16, H, 3, CB, ACT>;
+        default: return k_mlp<BF16, H, 4, CB, ACT>;
     }
 }
 
-template <bool BF16, int ACT>
-MlpShape pick_H(int H, int L) {
+template <bool BF16, int ACT, int CB>
+MlpFn pick_H(int H, int L) {
     switch (H) {
-        case 32: return pick_L<BF16, 32, ACT>(L);
-        case 64: return pick_L<BF16, 64, ACT>(L);
-        default: return pick_L<BF16, 128, ACT>(L);
+        case 32: return pick_L<BF16, 32, ACT, CB>(L);
+        case 64: return pick_L<BF16, 64, ACT, CB>(L);
+        default: return pick_L<BF16, 128, ACT, CB>(L);
     }
 }
 
-template <bool BF16>
-MlpShape pick_act(int act, int H, int L) {
-    return act == TMD_ACT_SQUAREPLUS ? pick_H<BF16, TMD_ACT_SQUAREPLUS>(H, L) : pick_H<BF16, TMD_ACT_TANH>(H, L);
+template <bool BF16, int CB>
+MlpFn pick_act(int act, int H, int L) {
+    return act == TMD_ACT_SQUAREPLUS ? pick_H<BF16, TMD_ACT_SQUAREPLUS, CB>(H, L) : pick_H<BF16, TMD_ACT_TANH, CB>(H, L);
 }
 
 }  // namespace
@@ -648,9 +737,26 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     a.Fpad = m->Fpad;
     a.act = m->act;
     a.L = m->L;
-    const MlpShape sh = (prec == TMD_BF16_MLP) ? pick_act<true>(m->act, m->H, m->L)
-                                               : pick_act<false>(m->act, m->H, m->L);
-    const int kTileAtoms = sh.waves * 16 * sh.cb;
+    // 16 atoms per workgroup up to about one round of workgroups (four on a CU),
+    // 32 from 24,576 on: 23,040 atoms of 512-128-128-128-128 in FP32 took 134
+    // with 16, 146 with 32, 32,000 of 32-64-64 19.8 and 18.0, 98,646 of
+    // 96-128-128 148 and 137 us.  BF16 with one or two layers of 128: the
+    // staged form from 16,384 on (30,000 atoms: 18 against 21 and 23 us with 32
+    // and 16 atoms; 4,096: 15 against 9).
+    const int64_t N = g.off[m->S];
+    const bool wide = N >= 24 * 1024;
+    const bool bf16 = prec == TMD_BF16_MLP;
+    MlpFn staged = nullptr;
+    if (N >= 16 * 1024 && bf16 && m->H == 128 && m->L <= 2) {
+        const bool sp = m->act == TMD_ACT_SQUAREPLUS;
+        staged = m->L == 1 ? (sp ? k_mlp_staged<1, TMD_ACT_SQUAREPLUS> : k_mlp_staged<1, TMD_ACT_TANH>)
+                           : (sp ? k_mlp_staged<2, TMD_ACT_SQUAREPLUS> : k_mlp_staged<2, TMD_ACT_TANH>);
+    }
+    const MlpFn fn = staged ? staged
+                     : bf16
+                         ? (wide ? pick_act<true, 2>(m->act, m->H, m->L) : pick_act<true, 1>(m->act, m->H, m->L))
+                         : (wide ? pick_act<false, 2>(m->act, m->H, m->L) : pick_act<false, 1>(m->act, m->H, m->L));
+    const int kTileAtoms = staged ? 128 : wide ? 32 : 16;
     int64_t tiles = 0;
     for (int s = 0; s < m->S; ++s) {
         a.sp_off[s] = g.off[s];
@@ -677,7 +783,7 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     if (tiles == 0) return TMD_OK;
     const int rlds = resident_lds_bytes(m->H, m->L, m->Fpad);
     ResidentFn rfn = nullptr;
-    if (prec == TMD_BF16_MLP && rlds <= kMaxResidentLds && g.off[m->S] >= (int64_t)16 * 16 * ctx->num_cus)
+    if (prec == TMD_BF16_MLP && rlds <= kMaxResidentLds && N >= (int64_t)16 * 16 * ctx->num_cus)
         rfn = m->act == TMD_ACT_SQUAREPLUS ? pick_resident<TMD_ACT_SQUAREPLUS>(m->H, m->L)
                                            : pick_resident<TMD_ACT_TANH>(m->H, m->L);
     if (rfn) {
@@ -687,7 +793,7 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
         rfn<<<(unsigned)ctx->num_cus, 1024, rlds, ctx->stream>>>(a);
     } else {
         ProfScope ps_(ctx, "mlp");
-        sh.fn<<<(unsigned)tiles, sh.waves * 64, 0, ctx->stream>>>(a);
+        fn<<<(unsigned)tiles, staged ? 512 : 256, 0, ctx->stream>>>(a);
     }
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;

@@ -144,7 +144,8 @@ struct tmd_model {
     int tab_n = 0;
     double tab_delta = 0.0;
     // Per species, per layer l = 0..L-1: forward W_l [H][in_pad] and transposed
-    // W_l^T [in_pad][H] (in_pad = Fpad for l = 0, H otherwise), FP32 and BF16 copies.
+    // W_l^T [in_pad][H] (in_pad = Fpad for l = 0, H otherwise), FP32 and BF16
+    // copies in the order of MFMA operands (w32_at, wbf_at).
     float* w32 = nullptr;
     __hip_bfloat16* wbf = nullptr;
     int64_t w_species_stride = 0;         // elements per species in w32 / wbf
@@ -168,6 +169,17 @@ namespace tmd {
 // the output weights [width] and bias; the padded one at the padded sizes.
 // Returns the offset inside the species block and, for a weight, its row o
 // and padded column c (layer l; -1 for the output layer and biases).
+// Element (r, c) of a weight matrix with cols columns in the order its MFMA
+// operand reads it: 16 rows by 16 (FP32) or 32 (BF16) columns are 1 KB, lane
+// (c % 16 / 4, r % 16) holding its 16 bytes in one piece, so that a wave's load
+// is one contiguous run.
+__host__ __device__ inline int64_t w32_at(int64_t r, int64_t c, int64_t cols) {
+    return ((r / 16 * (cols / 16) + c / 16) * 64 + c % 16 / 4 * 16 + r % 16) * 4 + c % 4;
+}
+__host__ __device__ inline int64_t wbf_at(int64_t r, int64_t c, int64_t cols) {
+    return ((r / 16 * (cols / 32) + c / 32) * 64 + c % 16 / 4 * 16 + r % 16) * 8 + c % 32 / 16 * 4 + c % 4;
+}
+
 struct ParamMap {
     int L, H, F, Fabi, K, Kabi, M1;
     int hid[TMD_MAX_HIDDEN];
@@ -382,6 +394,10 @@ tmd_status launch_compact_features(tmd_context* ctx, int64_t n, const float* in,
                                    int M1, float* out);
 tmd_status launch_export_nlist(tmd_context* ctx, const tmd_nlist* nl, int32_t* nbr, int32_t* img, int32_t* cnt);
 tmd_status launch_nlist_stats(tmd_context* ctx, const tmd_nlist* nl, int64_t* total_pairs, int32_t* max_row);
+
+// The MLP operand copies (W, W^T in FP32 and BF16, biases, output layer) of
+// every species and the padded master copy from the master parameters m->params32.
+tmd_status launch_unpack_params(tmd_context* ctx, tmd_model* m);
 
 // Pre-size a context's evaluation workspace for n atoms (avoids growth, and
 // the device-wide synchronisation it implies, later), and its size in bytes.

@@ -802,8 +802,8 @@ __global__ void __launch_bounds__(256) k_mlp_second(MlpTrainArgs a) {
 // rows 16 (4 rt + w) of every layer in both directions, so s' and s'' zt stay in
 // its registers from the forward to the backward pass, and each element of the
 // weight gradient has one owner, which adds the sub-tiles' terms in order in the
-// tile's partial row.  Weights are read as MFMA operands from their row-major
-// copies W and W^T.
+// tile's partial row.  Weights are read as MFMA operands from the copies of W
+// and W^T in that order.
 //
 // 17,648 atoms, 32-64-64-1: 28 us (the vector kernel 101; the products take
 // 9 at the FP32 matrix rate).  Bound by the chain of layers: one sub-tile per
@@ -885,14 +885,14 @@ __global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
                 if (rt >= nrt) continue;
                 const int o0 = 16 * (4 * rt + wv);
                 f32x4 z = *reinterpret_cast<const f32x4*>(bias + l * H + o0 + 4 * g), zt = {0.0f, 0.0f, 0.0f, 0.0f};
-                const float* const wr = w32 + a.w_off[l] + (int64_t)(o0 + col) * ws + 4 * g;
+                const float* const wr = w32 + a.w_off[l] + (int64_t)o0 * ws + 4 * lane;  // 1 KB per 16 columns
                 const float* const x0 = in0 + col * st + 4 * g;
                 const float* const x1 = in1 + col * st + 4 * g;
                 if (l == 0) {
                     // (W has zero columns up to a multiple of 32)
                     float4 w4 = *reinterpret_cast<const float4*>(wr);
                     for (int k = 0; k < FT; k += 16) {
-                        const float4 wn = *reinterpret_cast<const float4*>(wr + min(k + 16, a.Fpad - 16));
+                        const float4 wn = *reinterpret_cast<const float4*>(wr + 16 * min(k + 16, a.Fpad - 16));
                         z = mfma4(w4, *reinterpret_cast<const float4*>(x0 + k), z);
                         zt = mfma4(w4, *reinterpret_cast<const float4*>(x1 + k), zt);
                         w4 = wn;
@@ -900,7 +900,7 @@ __global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
                 } else {
                     float4 w4[H / 16];
 #pragma unroll
-                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 16 * k);
+                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 256 * k);
 #pragma unroll
                     for (int k = 0; k < H / 16; ++k) {
                         z = mfma4(w4[k], *reinterpret_cast<const float4*>(x0 + 16 * k), z);
@@ -1008,11 +1008,11 @@ __global__ void __launch_bounds__(256) k_mlp_second_mfma(MlpTrainArgs a) {
                 for (int rt = 0; rt < RT; ++rt) {
                     if (rt >= nrt) continue;
                     const int q0 = 16 * (4 * rt + wv);
-                    const float* const wr = w32 + a.wt_off[l] + (int64_t)(q0 + col) * H + 4 * g;
+                    const float* const wr = w32 + a.wt_off[l] + (int64_t)q0 * H + 4 * lane;
                     f32x4 sa = {0.0f, 0.0f, 0.0f, 0.0f}, sat = {0.0f, 0.0f, 0.0f, 0.0f};
                     float4 w4[H / 16];
 #pragma unroll
-                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 16 * k);
+                    for (int k = 0; k < H / 16; ++k) w4[k] = *reinterpret_cast<const float4*>(wr + 256 * k);
 #pragma unroll
                     for (int k = 0; k < H / 16; ++k) {
                         const float* const c0 = C + col * HS + 16 * k + 4 * g;
@@ -1050,10 +1050,10 @@ __device__ __forceinline__ void unpack_param(const UnpackArgs& u, int s, int l, 
         float* ws = u.w32 + s * u.wstride;
         __hip_bfloat16* wb = u.wbf + s * u.wstride;
         const int in_pad = (l == 0) ? u.Fpad : u.H;
-        ws[u.w_off[l] + (int64_t)o * in_pad + c] = v;
-        ws[u.wt_off[l] + (int64_t)c * u.H + o] = v;
-        wb[u.w_off[l] + (int64_t)o * in_pad + c] = __float2bfloat16(v);
-        wb[u.wt_off[l] + (int64_t)c * u.H + o] = __float2bfloat16(v);
+        ws[u.w_off[l] + w32_at(o, c, in_pad)] = v;
+        ws[u.wt_off[l] + w32_at(c, o, u.H)] = v;
+        wb[u.w_off[l] + wbf_at(o, c, in_pad)] = __float2bfloat16(v);
+        wb[u.wt_off[l] + wbf_at(c, o, u.H)] = __float2bfloat16(v);
     } else if (kind == 1) {
         u.bias[((int64_t)s * u.L + l) * u.H + o] = v;
     } else if (kind == 2) {
@@ -1084,6 +1084,16 @@ UnpackArgs unpack_args(tmd_model* m) {
     u.wout = m->wout;
     u.bout = m->bout;
     return u;
+}
+
+// One thread per master parameter (ABI layout).
+__global__ void k_unpack(UnpackArgs u, const float* __restrict__ params) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)u.S * u.P) return;
+    const int s = (int)(t / u.P);
+    int l, o, c, kind;
+    const int64_t qi = u.pm.map(t - (int64_t)s * u.P, l, o, c, kind);
+    unpack_param(u, s, l, o, c, kind, qi, params[t]);
 }
 
 struct GradArgs {
@@ -1650,3 +1660,13 @@ tmd_status tmd_batch_read(tmd_context* ctx, const tmd_batch* b, int32_t field, f
 }
 
 }  // extern "C"
+
+namespace tmd {
+
+tmd_status launch_unpack_params(tmd_context* ctx, tmd_model* m) {
+    k_unpack<<<blocks_for((int64_t)m->S * m->per_species), kBlock, 0, ctx->stream>>>(unpack_args(m), m->params32);
+    TMD_HIP(ctx, hipGetLastError());
+    return TMD_OK;
+}
+
+}  // namespace tmd

@@ -13,6 +13,8 @@ the cell capacity of a wave and of its sharing over several waves).
   of a pass and of the window of force accumulators.  A merged list takes them
   too: each system of a batch against its own evaluation, FP32 sums in another
   order (the FP32 bars of tests/parity.py, relative to the same oracle).
+* The network's kernels over the widths, depths and atom counts that choose
+  between them: the FP32 and BF16 bars of tests/parity.py.
 * The second-order pass of a training step over the network shapes it takes,
   the bars of the training tests.
 * The kinetic energy of an MD step against the exact sum over the velocities
@@ -241,3 +243,47 @@ def test_second_order_pass_shapes(ctx, K, M, hidden):
     assert np.linalg.norm(g - gr) <= 2e-3 * np.linalg.norm(gr)
     bt.close()
     model.close()
+
+
+# every width and depth of the network on few atoms: 1, 15, 16, 17 and 33 of a
+# species (16 atoms per workgroup)
+@pytest.mark.parametrize("hidden", [[32], [20, 32], [64, 64], [50] * 3, [64] * 4, [128], [128, 96], [128] * 3, [100] * 4])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_network_shapes(ctx, hidden, bf16):
+    import torch
+    from paper_2310_08439_amd import tmd
+    for na, nb in ((1, 16), (15, 17), (33, 0)):
+        s = _thin(3, 3, 3, 2, na, na + nb)
+        s = inputs.System(pos=s.pos, species=np.array([0] * na + [1] * nb, dtype=np.int32), box=s.box, masses=s.masses)
+        spec = inputs.make_model(2, 8, 3, hidden, 5.0, seed=len(hidden) + hidden[0])
+        print(f"[case] network {hidden}, bf16 {bf16}, {na} + {nb} atoms", flush=True)
+        pos = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+        ev = tmd.Evaluator(spec, s.n, s.box, precision=tmd.BF16_MLP if bf16 else tmd.FP32, ctx=ctx)
+        E, Ea, F, W = ev.energy_forces(pos, torch.tensor(s.species, device="cuda"), s.box)
+        Ea, F = Ea.cpu().numpy().astype(np.float64), F.cpu().numpy().astype(np.float64)
+        if not bf16:
+            parity.check_fp32(E, Ea, F, W, s, spec)
+            continue
+        # too few atoms for the statistics of the BF16 bars: the largest deviation from the BF16 form
+        import oracle
+        _, Ea16, F16, _ = oracle.energy_forces(spec, s.pos, s.species, s.box, bf16=True)
+        assert np.abs(Ea - Ea16).max() <= parity.BF16_MAX_EI
+        _, _, F64, _ = oracle.energy_forces(spec, s.pos, s.species, s.box)
+        rms = lambda v: math.sqrt(np.mean(v * v))
+        assert rms(F - F64) <= max(parity.F_BF16, rms(F16 - F64) + parity.F_FP32)
+
+
+# 27,431 atoms: 32 atoms per workgroup, and in BF16 with 128 units weights staged in LDS
+@pytest.mark.parametrize("hidden", [[32, 32], [64, 64], [128], [128, 128], [128] * 3])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_network_shapes_many_atoms(ctx, hidden, bf16):
+    import torch
+    from paper_2310_08439_amd import tmd
+    s = _thin(19, 19, 19, 2, 5, 27431)
+    spec = inputs.make_model(2, 12, 3, hidden, 5.0, seed=97)
+    print(f"[case] network {hidden}, bf16 {bf16}, {s.n} atoms", flush=True)
+    pos = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+    ev = tmd.Evaluator(spec, s.n, s.box, precision=tmd.BF16_MLP if bf16 else tmd.FP32, ctx=ctx)
+    _, Ea, F, _ = ev.energy_forces(pos, torch.tensor(s.species, dtype=torch.int32, device="cuda"), s.box)
+    parity.check_sampled(Ea.cpu().numpy().astype(np.float64), F.cpu().numpy().astype(np.float64), s, spec, bf16,
+                         n_sample=300)
