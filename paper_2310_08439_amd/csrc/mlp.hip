@@ -21,6 +21,8 @@
 // add a unit's products in the same order, so they agree bit for bit.
 #include "tmd_internal.h"
 
+#include <type_traits>
+
 namespace tmd {
 namespace {
 
@@ -409,18 +411,25 @@ __global__ void __launch_bounds__(256) k_mlp(MlpArgs a) {
     }
 }
 
-// Staged form (BF16, H = 128, one or two hidden layers): eight waves take 16
-// atoms each, activations never leave a wave's registers, and each layer's
-// weights pass once per 128 atoms through LDS.  It fills the chip in one round
+// Staged form (H = 128, one or two hidden layers): eight waves take 16 atoms
+// each, activations never leave a wave's registers, and each layer's weights
+// pass once per 128 atoms through LDS, 32 KB at a time.  It fills the chip in one round
 // from 16,384 to 65,536 atoms, where the form above needs two or three: 54,000
 // atoms, 96-128-128-1: 21 us against 32.
-template <int L, int ACT>
-__global__ void __launch_bounds__(512) k_mlp_staged(MlpArgs a) {
-    using O = Op<true>;
-    using T = __hip_bfloat16;
-    constexpr int H = 128, NB = H / 16, KB = H / 32;
-    constexpr int kPanel = H * H;  // weights staged at a time
-    __shared__ __attribute__((aligned(16))) T lds[kPanel];
+// (128 registers: two workgroups on a CU; with 136 the FP32 form took 1,094 us
+// for 877,952 atoms.)
+template <bool BF16, int L, int ACT>
+__global__ void __launch_bounds__(512, L == 1 || ACT == TMD_ACT_TANH ? 4 : 2) k_mlp_staged(MlpArgs a) {
+    using O = Op<BF16>;
+    using A = typename O::A;
+    using T = std::conditional_t<BF16, __hip_bfloat16, float>;
+    constexpr int H = 128, NB = H / 16, KB = H / O::kBlock;
+    constexpr int PB = 4;          // reduction blocks of 1 KB per row block in a panel
+    constexpr int RB = 32 / KB;    // row blocks of W_1^T in a panel
+    // BF16: a panel in operand order.  FP32: rows padded by 28 floats (pads of
+    // 20 to 36 are alike, 4 or 44 and more a quarter slower).
+    constexpr int PS = 16 * PB + 28, FS = H + 28;
+    __shared__ __attribute__((aligned(16))) T lds[BF16 ? 16 * 1024 : H * PS];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int col = lane & 15, grp = lane >> 4;
     const int64_t tile = blockIdx.x;
@@ -430,7 +439,9 @@ __global__ void __launch_bounds__(512) k_mlp_staged(MlpArgs a) {
     const int64_t r = a.sp_off[s] + (tile - a.tile_off[s]) * 128 + wv * 16 + col;
     const bool valid = r < a.sp_off[s + 1];
     const int64_t atom = valid ? (int64_t)a.sp_idx[r] : 0;
-    const T* wsp = a.wbf + s * a.wstride;
+    const T* wsp;
+    if constexpr (BF16) wsp = a.wbf + s * a.wstride;
+    else wsp = a.w32 + s * a.wstride;
     const float* bias = a.bias + (int64_t)s * L * H;
     f32x4 acc[NB], x[NB], dact[L][NB];
     auto set_bias = [&](const float* bl) {
@@ -452,44 +463,56 @@ __global__ void __launch_bounds__(512) k_mlp_staged(MlpArgs a) {
                 acc[ob][q] = y;
             }
     };
-    auto dense = [&](const T* W) {
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
-        __syncthreads();
-        copy_weights(W, H * H, lds);
-        __syncthreads();
-    };
-    auto product = [&]() {
-#pragma unroll
-        for (int k = 0; k < KB; ++k) {
-            const bf16x8 bop = cat8(to_bf4(x[2 * k]), to_bf4(x[2 * k + 1]));
-#pragma unroll
-            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(O::load_w(lds, KB, ob, k, lane), bop, acc[ob]);
-        }
-    };
-    // layer 1, up to KB blocks of 32 features at a time
-    set_bias(bias);
-    const int nk = a.Fpad / 32;
-    for (int c = 0; c < nk; c += KB) {
-        const int n = min(KB, nk - c);
+    // blocks c .. c + n - 1 of every row block of a matrix with nk blocks a row
+    auto panel = [&](const T* W, int nk, int c, int n) {
         __syncthreads();
         for (int q = threadIdx.x; q < NB * n * 64; q += 512) {
             const int ob = q / (n * 64), e = q - ob * (n * 64);
-            reinterpret_cast<uint4*>(lds)[q] = reinterpret_cast<const uint4*>(wsp + a.w_off[0])[(ob * nk + c) * 64 + e];
+            const uint4 v = reinterpret_cast<const uint4*>(W)[(ob * nk + c) * 64 + e];
+            if constexpr (BF16) reinterpret_cast<uint4*>(lds)[q] = v;
+            else *reinterpret_cast<uint4*>(lds + (16 * ob + (e & 15)) * PS + 4 * (e >> 4)) = v;
         }
         __syncthreads();
-        for (int k = 0; k < n; ++k) {
-            const bf16x8 bop = O::load_g(a, atom, c + k, grp, valid);
+    };
+    auto from_panel = [&](int n, int ob, int k) {
+        if constexpr (BF16) return O::load_w(lds, n, ob, k, lane);
+        else return *reinterpret_cast<const f32x4*>(lds + (16 * ob + col) * PS + 16 * k + 4 * grp);
+    };
+    auto operand = [&](const f32x4 (&v)[NB], int k) {
+        if constexpr (BF16) return cat8(to_bf4(v[2 * k]), to_bf4(v[2 * k + 1]));
+        else return v[k];
+    };
+    auto dense = [&](const T* W, const float* bl) {
 #pragma unroll
-            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(O::load_w(lds, n, ob, k, lane), bop, acc[ob]);
+        for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
+        set_bias(bl);
+#pragma unroll
+        for (int c = 0; c < KB; c += PB) {
+            panel(W, KB, c, PB);
+#pragma unroll
+            for (int k = 0; k < PB; ++k) {
+                const A xv = operand(x, c + k);
+#pragma unroll
+                for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(from_panel(PB, ob, k), xv, acc[ob]);
+            }
+        }
+    };
+    // layer 1
+    set_bias(bias);
+    const int nk = a.Fpad / O::kBlock;
+    for (int c = 0; c < nk; c += PB) {
+        const int n = min(PB, nk - c);
+        panel(wsp + a.w_off[0], nk, c, n);
+        for (int k = 0; k < n; ++k) {
+            const A xv = O::load_g(a, atom, c + k, grp, valid);
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(from_panel(n, ob, k), xv, acc[ob]);
         }
     }
     activate(0);
 #pragma unroll
     for (int l = 1; l < L; ++l) {
-        dense(wsp + a.w_off[l]);
-        set_bias(bias + l * H);
-        product();
+        dense(wsp + a.w_off[l], bias + l * H);
         activate(l);
     }
     const float* wo = a.wout + (int64_t)s * H;
@@ -508,27 +531,34 @@ __global__ void __launch_bounds__(512) k_mlp_staged(MlpArgs a) {
     if (grp == 0 && valid) a.Ei[atom] = e + a.bout[s];
 #pragma unroll
     for (int l = L - 1; l >= 1; --l) {
-        dense(wsp + a.wt_off[l]);
-        set_bias(nullptr);
-        product();
+        dense(wsp + a.wt_off[l], nullptr);
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[ob][q] *= dact[l - 1][ob][q];
     }
-    bf16x8 bop[KB];
+    A xv[KB];
 #pragma unroll
-    for (int k = 0; k < KB; ++k) bop[k] = cat8(to_bf4(acc[2 * k]), to_bf4(acc[2 * k + 1]));
-    for (int f0 = 0; f0 < a.Fpad; f0 += H) {
-        const int nf = min(H, a.Fpad - f0) / 16;
+    for (int k = 0; k < KB; ++k) xv[k] = operand(acc, k);
+    for (int f0 = 0; f0 < a.Fpad / 16; f0 += RB) {
+        const int nf = min(RB, a.Fpad / 16 - f0);
         __syncthreads();
-        copy_weights(wsp + a.wt_off[0] + (int64_t)f0 * H, nf * 16 * H, lds);
+        for (int q = threadIdx.x; q < nf * KB * 64; q += 512) {
+            const uint4 v = reinterpret_cast<const uint4*>(wsp + a.wt_off[0])[f0 * KB * 64 + q];
+            if constexpr (BF16) reinterpret_cast<uint4*>(lds)[q] = v;
+            else *reinterpret_cast<uint4*>(lds + (q / (KB * 64) * 16 + (q & 15)) * FS + 4 * (q % (KB * 64) >> 4)) = v;
+        }
         __syncthreads();
         for (int fb = 0; fb < nf; ++fb) {
             f32x4 out = {0, 0, 0, 0};
 #pragma unroll
-            for (int k = 0; k < KB; ++k) out = O::mul(O::load_w(lds, KB, fb, k, lane), bop[k], out);
-            store_dg4(a.dG, atom, a.F, f0 + 16 * fb + 4 * grp, valid, out);
+            for (int k = 0; k < KB; ++k) {
+                A w;
+                if constexpr (BF16) w = O::load_w(lds, KB, fb, k, lane);
+                else w = *reinterpret_cast<const f32x4*>(lds + (16 * fb + col) * FS + 16 * k + 4 * grp);
+                out = O::mul(w, xv[k], out);
+            }
+            store_dg4(a.dG, atom, a.F, 16 * (f0 + fb) + 4 * grp, valid, out);
         }
     }
 }
@@ -717,6 +747,13 @@ MlpFn pick_act(int act, int H, int L) {
     return act == TMD_ACT_SQUAREPLUS ? pick_H<BF16, TMD_ACT_SQUAREPLUS, CB>(H, L) : pick_H<BF16, TMD_ACT_TANH, CB>(H, L);
 }
 
+template <bool BF16>
+MlpFn pick_staged(int act, int L) {
+    if (act == TMD_ACT_SQUAREPLUS)
+        return L == 1 ? k_mlp_staged<BF16, 1, TMD_ACT_SQUAREPLUS> : k_mlp_staged<BF16, 2, TMD_ACT_SQUAREPLUS>;
+    return L == 1 ? k_mlp_staged<BF16, 1, TMD_ACT_TANH> : k_mlp_staged<BF16, 2, TMD_ACT_TANH>;
+}
+
 }  // namespace
 
 SpeciesGroups species_groups(const tmd_nlist* nl) {
@@ -740,18 +777,16 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     // 16 atoms per workgroup up to about one round of workgroups (four on a CU),
     // 32 from 24,576 on: 23,040 atoms of 512-128-128-128-128 in FP32 took 134
     // with 16, 146 with 32, 32,000 of 32-64-64 19.8 and 18.0, 98,646 of
-    // 96-128-128 148 and 137 us.  BF16 with one or two layers of 128: the
-    // staged form from 16,384 on (30,000 atoms: 18 against 21 and 23 us with 32
-    // and 16 atoms; 4,096: 15 against 9).
+    // 96-128-128 148 and 137 us.  One or two layers of 128: in BF16 the staged
+    // form from 16,384 on (30,000 atoms: 18 against 21 and 23 us with 32 and 16
+    // atoms; 4,096: 15 against 9), in FP32 from 65,536 on (98,642 atoms: 139
+    // against 139, 877,952: 892 against 1,090).
     const int64_t N = g.off[m->S];
     const bool wide = N >= 24 * 1024;
     const bool bf16 = prec == TMD_BF16_MLP;
     MlpFn staged = nullptr;
-    if (N >= 16 * 1024 && bf16 && m->H == 128 && m->L <= 2) {
-        const bool sp = m->act == TMD_ACT_SQUAREPLUS;
-        staged = m->L == 1 ? (sp ? k_mlp_staged<1, TMD_ACT_SQUAREPLUS> : k_mlp_staged<1, TMD_ACT_TANH>)
-                           : (sp ? k_mlp_staged<2, TMD_ACT_SQUAREPLUS> : k_mlp_staged<2, TMD_ACT_TANH>);
-    }
+    if (N >= (bf16 ? 16 * 1024 : 64 * 1024) && m->H == 128 && m->L <= 2)
+        staged = bf16 ? pick_staged<true>(m->act, m->L) : pick_staged<false>(m->act, m->L);
     const MlpFn fn = staged ? staged
                      : bf16
                          ? (wide ? pick_act<true, 2>(m->act, m->H, m->L) : pick_act<true, 1>(m->act, m->H, m->L))
