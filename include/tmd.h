@@ -426,7 +426,12 @@ typedef struct tmd_server tmd_server;
  * served together: a slot that takes one also takes the other such requests
  * queued on idle systems (the first queued request of each system, up to 64
  * systems and max_atoms atoms) and evaluates them with one
- * tmd_energy_forces_batch call (0: off). */
+ * tmd_energy_forces_batch call (0: off).  With M = 3 and 4, 8, 12 or 16 radial
+ * functions (after padding) a lone request on such a system takes that call
+ * too, so that what it returns does not depend, to the bit, on which others
+ * were queued; otherwise a lone one is evaluated as by tmd_energy_forces, with
+ * the same energy bit for bit, and forces and virial in another order of FP32
+ * sums. */
 typedef struct {
     int64_t hbm_budget_bytes;
     int32_t max_slots;

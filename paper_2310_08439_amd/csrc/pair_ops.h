@@ -53,11 +53,10 @@ struct PathArgs {
 // Arguments of a model and list (outputs unset); descriptor.hip.
 PathArgs make_args(const tmd_model* m, const tmd_nlist* nl);
 
-// Kernels with many lanes per atom (rows.hip), for lists without a work order:
-// whether they take a model; atoms per adjoint workgroup (a power of two, at
-// most 256) for at most max_partials workgroups; the launches (a's outputs
+// Kernels with many lanes per atom (rows.hip), for lists without a work order
+// of the models that row_kernels names: atoms per adjoint workgroup (a power of
+// two, at most 256) for at most max_partials workgroups; the launches (a's outputs
 // set; segs: the segment of each 256 atoms of a merged list, or null).
-bool row_kernels(const tmd_model* m);
 int adjoint_rows_atoms(int64_t n, int64_t max_partials);
 tmd_status launch_descriptor_rows(tmd_context* ctx, const tmd_model* m, const PathArgs& a);
 tmd_status launch_adjoint_rows(tmd_context* ctx, const tmd_model* m, const PathArgs& a, const int2* segs, int atoms,

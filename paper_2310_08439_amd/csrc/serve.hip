@@ -435,6 +435,12 @@ tmd_status run_batch(tmd_server* sv, tmd_context* ctx, const std::vector<System*
 constexpr int kServeBatchSystems = 64;
 constexpr int64_t kServeBatchAtoms = 65536;
 
+// Whether energy-and-force requests on a system may be evaluated together with others.
+bool batchable(const tmd_server* sv, const System* sys) {
+    return sys->n <= sv->opts.batch_atoms &&
+           (sys->n + kBlock - 1) / kBlock * kBlock <= std::min<int64_t>(sv->opts.max_atoms, kServeBatchAtoms);
+}
+
 // With `first` (an energy-and-force request on a small system with a resident
 // list) admitted, also take the other such requests from the queue: the first
 // queued request of each idle system.  Caller holds sv->mu.
@@ -578,8 +584,7 @@ void worker_main(tmd_server* sv, int slot) {
                 continue;
             }
             sv->running.insert(p.ticket);
-            if (sv->opts.batch_atoms > 0 && p.req.kind == TMD_REQ_ENERGY_FORCES && sys->nl &&
-                sys->n <= sv->opts.batch_atoms) {
+            if (p.req.kind == TMD_REQ_ENERGY_FORCES && sys->nl && batchable(sv, sys)) {
                 std::vector<Pending> reqs;
                 std::vector<System*> systems;
                 reqs.push_back(std::move(p));
@@ -613,7 +618,25 @@ void worker_main(tmd_server* sv, int slot) {
                 sys->nl_valid = false;
             }
         }
-        if (st == TMD_OK) st = run_request(sv, ctx, sv->events.data() + 2 * slot, sys, p, &f);
+        if (st == TMD_OK) {
+            // A request that could have been batched but is alone takes the
+            // merged evaluation too where that one runs other descriptor
+            // kernels than the single one (row_kernels): their FP32 roundings
+            // differ, which a BF16 network magnifies to 1e-4 of the forces, and
+            // the result would depend on what else was queued.  (54 to 3,456
+            // atoms, K = 12: 52 to 69 us against 70 to 80.)  Of other models
+            // the two have the descriptors, so the energies, bit for bit in
+            // common, and the single one is faster (K = 32: 99 to 134 against
+            // 147 to 160 us).
+            if (p.req.kind == TMD_REQ_ENERGY_FORCES && batchable(sv, sys) && row_kernels(sv->model)) {
+                std::vector<Finished> one(1);
+                std::swap(one[0], f);
+                st = run_batch(sv, ctx, {sys}, one);
+                std::swap(one[0], f);
+            } else {
+                st = run_request(sv, ctx, sv->events.data() + 2 * slot, sys, p, &f);
+            }
+        }
         f.res.status = st;
         f.res.t_done = now_s(sv->t0);
         {

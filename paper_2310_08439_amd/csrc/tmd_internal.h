@@ -490,6 +490,10 @@ tmd_status launch_batch_finalize(tmd_context* ctx, const BatchSeg* segs, int nse
                                  const unsigned long long* Fq, const float* Ei, const double* vir, int vir_atoms,
                                  double* totals);
 
+// Whether lists without a work order (merged ones among them) of a model take
+// the kernels with 16 lanes per atom (rows.hip).
+bool row_kernels(const tmd_model* m);
+
 // Upper bound on the virial partials the adjoint writes.
 // (least: of its coarsest split, for little scratch).
 int64_t adjoint_max_partials(const tmd_model* m, const tmd_nlist* nl, bool least = false);

@@ -361,3 +361,40 @@ def test_serve_batches_small_energy_force_requests(tmd, ctx):
     print(f"  batch sizes seen: {sorted(set(sizes))}", flush=True)
     assert max(sizes) > 1
     srv.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_serve_batched_request_same_alone_and_merged(tmd, ctx, bf16):
+    """A request that may be batched gives the same bits alone as merged with
+    others, in BF16 too, where another FP32 rounding of the descriptors would
+    flip operands of the network; also when its list was evicted or not built
+    yet, and for a system just too large to be batched (always alone)."""
+    _note(f"serve EF alone vs merged, bf16 {bf16}")
+    spec = inputs.make_model(2, 12, 3, [128, 128], 6.0, seed=102)
+    model = tmd.Model(ctx, spec, precision=tmd.BF16_MLP if bf16 else tmd.FP32)
+    systems = [inputs.make_system("bcc", 3.16, (c, c, c), 0.08, 2, seed=110 + c, masses=[183.84, 95.95])
+               for c in (3, 6, 8, 9, 10)]  # 54 to 2,000 atoms; up to 1,458 are batched
+    srv = tmd.Server(model, max_slots=1, max_atoms=8192, skin=1.0, batch_atoms=1458)
+    ids = [srv.add_system(s.pos, s.species, s.box, s.masses) for s in systems]
+
+    def get(t):
+        r = srv.wait(t, 60.0)
+        assert r is not None and r["status"] == 0
+        return r["energy"], np.array(r["virial"]), srv.fetch(t, r)["forces"], r["batch_size"]
+
+    alone = [get(srv.submit(i)) for i in ids]
+    assert [a[3] for a in alone] == [1] * len(ids)
+    # a larger system whose MD run keeps the one slot busy while the burst queues
+    big = inputs.make_system("bcc", 3.16, (12, 12, 12), 0.08, 2, seed=120, masses=[183.84, 95.95])
+    big_id = srv.add_system(big.pos, big.species, big.box, big.masses)
+    v0 = inputs.maxwell_boltzmann(np.asarray(big.masses)[big.species], 300.0, seed=121)
+    busy = srv.submit(big_id, tmd.REQ_MD, 100, 1.0, v0)
+    tickets = [srv.submit(i) for i in ids]
+    assert srv.wait(busy, 60.0)["status"] == 0
+    merged = [get(t) for t in tickets]
+    assert [m[3] for m in merged] == [4, 4, 4, 4, 1]
+    for a, m in zip(alone, merged):
+        assert a[0] == m[0]
+        assert np.array_equal(a[1], m[1])
+        assert np.array_equal(a[2], m[2])
+    srv.close()
