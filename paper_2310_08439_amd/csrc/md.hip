@@ -332,11 +332,13 @@ tmd_status md_thermo(tmd_md* md, tmd_thermo* out) {
 
 // Skin lists are pruned to the cutoff plus a fifth of the skin and reused
 // while the displacements since the build allow (PruneGate); maxd2 holds the
-// largest squared displacement since the build for the current positions.
+// largest squared displacement since the build for the current positions
+// (since the build before, when the list was just built).
 PruneGate md_gate(const tmd_md* md) {
     PruneGate g;
     g.maxd2 = md->maxd2;
     g.margin = 0.2 * md->opts.skin;
+    g.at_build = md->steps_since_build == 0;
     return g;
 }
 

@@ -489,13 +489,14 @@ struct GateArgs {
     double* state;
     int32_t* flag;  // nullptr: no gate
     int force;
+    int at_build;  // the list was built at these positions (maxd2 still refers to the build before)
     double half_margin;
 };
 __device__ __forceinline__ void prune_gate(const GateArgs& g) {
-    const double d = sqrt(__longlong_as_double((long long)g.maxd2[0]));
+    const double d = g.at_build ? 0.0 : sqrt(__longlong_as_double((long long)g.maxd2[0]));
     if (g.force || !(d + g.state[0] < g.half_margin)) {
         g.flag[0] = 1;
-        g.state[0] = g.force ? 0.0 : d;  // a forced prune follows a build: no displacement yet
+        g.state[0] = d;
     } else {
         g.flag[0] = 0;
     }
@@ -1230,7 +1231,7 @@ tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tm
     if (!gate->maxd2 || !(gate->margin > 0.0))
         return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "prune gate without displacements");
     const int force = (nl->pruned_build_id != nl->build_id || nl->pruned_margin != gate->margin) ? 1 : 0;
-    const GateArgs g{gate->maxd2, nl->prune_state, nl->prune_flag, force, 0.5 * gate->margin};
+    const GateArgs g{gate->maxd2, nl->prune_state, nl->prune_flag, force, gate->at_build ? 1 : 0, 0.5 * gate->margin};
     if ((st = launch_refresh_positions(ctx, sys, nl, zero, g)) != TMD_OK) return st;
     nl->pruned_build_id = nl->build_id;
     nl->pruned_margin = gate->margin;

@@ -283,14 +283,15 @@ tmd_status md_steps_host_checked(tmd_server* sv, tmd_context* ctx, System* sys, 
         std::memcpy(&bits, ctx->h_flags, sizeof(bits));
         double d2;
         std::memcpy(&d2, &bits, sizeof(d2));
-        if (!(d2 <= half_skin2)) {
-            sys->nl_valid = false;
-            if ((st = build_list(sv, ctx, sys, rebuilds)) != TMD_OK) return st;
-        }
-        // b.maxd2[s] now holds this system's displacement since its build: the
+        // b.maxd2[s] holds this system's displacement since its build: the
         // pruned rows are reused while it allows (the request's first
         // evaluation pruned to the cutoff, so the first step here prunes)
         PruneGate gate;
+        if (!(d2 <= half_skin2)) {
+            sys->nl_valid = false;
+            if ((st = build_list(sv, ctx, sys, rebuilds)) != TMD_OK) return st;
+            gate.at_build = true;
+        }
         gate.maxd2 = b.maxd2 + s;
         gate.margin = 0.2 * sv->opts.skin;
         if ((st = energy_forces_gated(ctx, m, &view, sys->nl, b.tot + 7 * s, nullptr, sys->F,

@@ -439,10 +439,15 @@ tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n);
 // built, for the positions being evaluated.  Rows pruned to rcut + margin when
 // the largest displacement since the build was d_p keep every pair within
 // rcut while d + d_p < margin / 2 (each of a pair's atoms moved by at most
-// d + d_p since the prune), so they are rebuilt only when that fails.
+// d + d_p since the prune), so they are rebuilt only when that fails.  A prune
+// is also forced by a new build, by another margin and after an evaluation
+// without a gate; the last two may find the atoms anywhere within the skin, so
+// d_p is what maxd2 says, except at the very positions of a build (at_build),
+// where it is 0 and maxd2 need not have been cleared.
 struct PruneGate {
-    const unsigned long long* maxd2;
-    double margin;
+    const unsigned long long* maxd2 = nullptr;
+    double margin = 0.0;
+    bool at_build = false;
 };
 // launch_refresh_positions and then a copy of the list's rows keeping only the
 // entries within rcut (times 1 + 1e-6) at those positions, into nl->pnbr /

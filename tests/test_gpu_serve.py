@@ -398,3 +398,34 @@ def test_serve_batched_request_same_alone_and_merged(tmd, ctx, bf16):
         assert np.array_equal(a[1], m[1])
         assert np.array_equal(a[2], m[2])
     srv.close()
+
+
+def test_serve_pruned_rows_after_an_earlier_requests_displacement(tmd, ctx):
+    """Pruned rows are reused while no atom can have moved by a tenth of the
+    skin since the prune: a request on a list that an earlier one left its
+    atoms 0.09 skin away from prunes at displaced positions, and the atoms then
+    cross to -0.09 skin.  Two sublattices move against each other, so that the
+    pairs of one shell are 0.16 A beyond their distance at the build, past the
+    pruned rows' reach, when the rows are pruned and 0.07 A inside the cutoff
+    at the end (missing, they are 1e-4 eV of an atom's energy)."""
+    _note("serve pruned rows after an earlier displacement")
+    a = 3.2
+    pos, box = inputs.lattice("bcc", a, (6, 6, 6))
+    shell = a * math.sqrt(11.0) / 2.0
+    spec = inputs.make_model(1, 8, 3, [32, 32], shell - 0.095, seed=103)
+    sign = np.where(np.arange(len(pos)) % 2 == 0, 1.0, -1.0)[:, None] * np.array([[1.0, 0.0, 0.0]])
+    sp, masses = np.zeros(len(pos), dtype=np.int32), np.array([CU_MASS])
+    model = tmd.Model(ctx, spec)
+    srv = tmd.Server(model, max_slots=1, max_atoms=1024, skin=1.0)
+    sid = srv.add_system(pos, sp, box, masses)
+    x = pos
+    for v, steps in ((0.09 * sign, 1), (-0.0225 * sign, 8)):
+        t = srv.submit(sid, tmd.REQ_MD, n_steps=steps, dt_fs=1.0, velocities=v)
+        r = srv.wait(t, 60.0)
+        assert r["status"] == 0 and r["rebuilds"] == 0
+        out = srv.fetch(t, r)
+        x, _, epot, _ = oracle.nve(spec, x, v, sp, masses, box, 1.0, steps)
+        print(f"  max |dE|/N={np.abs(out['epot'] - epot).max() / len(pos):.3e}", flush=True)
+        assert np.abs(out["epot"] - epot).max() / len(pos) <= 1e-5
+        np.testing.assert_allclose(out["pos"], x, rtol=0, atol=1e-6)
+    srv.close()
