@@ -110,7 +110,10 @@ typedef struct {
  * (a hipStream_t; NULL for the legacy default stream). */
 tmd_status tmd_context_create(int device, void* hip_stream, tmd_context** out);
 void tmd_context_destroy(tmd_context* ctx);
-/* Re-target the context at another stream of the same device. */
+/* Re-target the context at another stream of the same device.  The calls that
+ * follow use the same workspace as the ones before: work still running on the
+ * old stream has to be ordered before them by the caller (an event, or a
+ * synchronisation). */
 tmd_status tmd_context_set_stream(tmd_context* ctx, void* hip_stream);
 /* Message of the last failed call on ctx ("" if none).  Valid until the next call. */
 const char* tmd_last_error(const tmd_context* ctx);

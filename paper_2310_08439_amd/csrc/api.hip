@@ -274,13 +274,14 @@ tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_
     tmd_nlist pruned;
     if (nl->rlist > m->rcut * (1.0 + 1e-9)) {
         tmd_nlist* mnl = const_cast<tmd_nlist*>(nl);  // the pruned rows are scratch owned by the list
-        if ((st = launch_refresh_prune(ctx, sys, mnl, b.Fq, m->rcut, gate)) != TMD_OK) return st;
+        if ((st = launch_refresh_prune(ctx, sys, mnl, b.Fq, finalize_counter(b.part), m->rcut, gate)) != TMD_OK)
+            return st;
         pruned = *nl;  // a view: same atoms, cells and work order, pruned rows
         pruned.nbr = nl->pnbr;
         pruned.img = nl->pimg;
         pruned.cnt = nl->pcnt;
         use = &pruned;
-    } else if ((st = launch_refresh_positions(ctx, sys, nl, b.Fq)) != TMD_OK) {
+    } else if ((st = launch_refresh_positions(ctx, sys, nl, b.Fq, finalize_counter(b.part))) != TMD_OK) {
         return st;
     }
     // a BF16 MLP takes its operand as BF16 descriptors, stored in the first
@@ -701,7 +702,7 @@ tmd_status tmd_descriptors(tmd_context* ctx, const tmd_model* m, const tmd_syste
     hipError_t e = hipSuccess;
     float* Gs = (float*)ctx->ws.get("ev.G", sizeof(float) * nl->n * m->F, &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "descriptor workspace");
-    if ((st = launch_refresh_positions(ctx, sys, nl, nullptr)) != TMD_OK) return st;
+    if ((st = launch_refresh_positions(ctx, sys, nl, nullptr, nullptr)) != TMD_OK) return st;
     if ((st = launch_descriptors(ctx, m, nl, Gs, nullptr)) != TMD_OK) return st;
     return launch_permute_rows(ctx, nl, Gs, m, G);
 }

@@ -26,7 +26,6 @@ __device__ __forceinline__ Comp comp_merge(Comp a, Comp b) {
     return a;
 }
 
-constexpr int kPartBlocks = 256;
 // Atoms per summing workgroup: eight per thread, so that up to 2,048 atoms are
 // summed by one workgroup without a second stage.
 constexpr int64_t kPartAtoms = 2048;
@@ -49,8 +48,8 @@ __device__ __forceinline__ Comp wave_merge(Comp a) {
 // after them take the forces (fixed point, 32 fractional bits: F = q 2^-32,
 // exact in FP64, then rounded to FP32) and atomic energies back to the caller's
 // atom order.  As three launches and a copy of the totals these steps took
-// 17 us of a small system's evaluation, most of it launch and drain; the
-// counter wraps to zero by itself, so it needs no clearing.
+// 17 us of a small system's evaluation, most of it launch and drain.  The
+// counter is zero at the start (k_refresh).
 __global__ void __launch_bounds__(256) k_finalize(int64_t n, const int32_t* __restrict__ perm,
                                                   const float* __restrict__ Ei,
                                                   const unsigned long long* __restrict__ Fq,
@@ -153,13 +152,12 @@ __global__ void k_permute_rows(int64_t n, int Fabi, int F, int Kabi, int K, int 
 tmd_status launch_finalize(tmd_context* ctx, const tmd_nlist* nl, const float* Ei, const unsigned long long* Fs,
                            const double* vir_partials, int nvir, float* atom_energy, float* forces, double* totals7,
                            double* host_totals, double* part) {
-    static_assert(finalize_part_doubles() == kPartBlocks * 14, "partials of the two-stage reduction");
     const int64_t n = nl->n;
-    const int nb = (int)std::min<int64_t>(kPartBlocks, (n + kPartAtoms - 1) / kPartAtoms);
+    const int nb = (int)std::min<int64_t>(kMaxPartials, (n + kPartAtoms - 1) / kPartAtoms);
     {
         ProfScope ps_(ctx, "finalize");
         k_finalize<<<(unsigned)(nb + (n + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-            n, nl->perm, Ei, Fs, atom_energy, forces, nb, nvir, vir_partials, part, ctx->d_counter, totals7,
+            n, nl->perm, Ei, Fs, atom_energy, forces, nb, nvir, vir_partials, part, finalize_counter(part), totals7,
             host_totals);
     }
     TMD_HIP(ctx, hipGetLastError());

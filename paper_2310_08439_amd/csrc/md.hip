@@ -221,7 +221,7 @@ tmd_status launch_kick_kinetic(tmd_context* ctx, int64_t n, double* v, const flo
                                const Thermostat& th, unsigned long long* clear) {
     static_assert(kKeBlocks <= 256, "the last workgroup merges at most 256 partials");
     const unsigned grid = (unsigned)std::min<int64_t>(kKeBlocks, (n + kKeThreads - 1) / kKeThreads);
-    k_kick_kinetic<<<grid, kKeThreads, 0, ctx->stream>>>(n, v, F, sp, acc, mass, dt, part, ctx->d_counter + 1, out4, th,
+    k_kick_kinetic<<<grid, kKeThreads, 0, ctx->stream>>>(n, v, F, sp, acc, mass, dt, part, ctx->d_counter, out4, th,
                                                          clear);
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;

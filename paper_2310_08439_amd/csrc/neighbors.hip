@@ -891,12 +891,15 @@ __global__ void k_export(int64_t n, int S, int cap, const int32_t* __restrict__ 
 
 // Sorted positions from the caller's, and in the same launch what else an
 // evaluation needs before its kernels (each of which was a launch of a few
-// microseconds): the force accumulators cleared, and the prune decision.
+// microseconds): the force accumulators and k_finalize's counter cleared, and
+// the prune decision.
 __global__ void k_refresh(int64_t n, const double* __restrict__ pos, const int32_t* __restrict__ perm,
                           const int32_t* __restrict__ shift, double L0, double L1, double L2,
-                          double4* __restrict__ xs, unsigned long long* __restrict__ zero, GateArgs gate) {
+                          double4* __restrict__ xs, unsigned long long* __restrict__ zero,
+                          unsigned int* __restrict__ counter, GateArgs gate) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p == 0 && gate.flag) prune_gate(gate);
+    if (p == 0 && counter) *counter = 0u;
     if (p >= n) return;
     const int64_t i = perm[p];
     const double x = pos[3 * i] + (double)shift[3 * p] * L0;
@@ -1201,12 +1204,12 @@ tmd_status prune_rows(tmd_context* ctx, tmd_nlist* nl, double r, const int32_t* 
 }
 
 tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
-                                    unsigned long long* zero, const GateArgs& gate) {
+                                    unsigned long long* zero, unsigned int* counter, const GateArgs& gate) {
     const int64_t n = nl->n;
     {
         ProfScope ps_(ctx, "refresh");
         k_refresh<<<grid_for(n), kBlock, 0, ctx->stream>>>(n, sys->pos, nl->perm, nl->shift, sys->box[0], sys->box[1],
-                                                            sys->box[2], nl->xs, zero, gate);
+                                                            sys->box[2], nl->xs, zero, counter, gate);
     }
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;
@@ -1215,16 +1218,16 @@ tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys
 }  // namespace
 
 tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
-                                    unsigned long long* zero) {
-    return launch_refresh_positions(ctx, sys, nl, zero, GateArgs{});
+                                    unsigned long long* zero, unsigned int* counter) {
+    return launch_refresh_positions(ctx, sys, nl, zero, counter, GateArgs{});
 }
 
 tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tmd_nlist* nl, unsigned long long* zero,
-                                double rcut, const PruneGate* gate) {
+                                unsigned int* counter, double rcut, const PruneGate* gate) {
     tmd_status st = reserve_pruned(ctx, nl);
     if (st != TMD_OK) return st;
     if (!gate) {
-        if ((st = launch_refresh_positions(ctx, sys, nl, zero)) != TMD_OK) return st;
+        if ((st = launch_refresh_positions(ctx, sys, nl, zero, counter)) != TMD_OK) return st;
         nl->pruned_margin = -1.0;
         return prune_rows(ctx, nl, rcut * (1.0 + 1e-6), nullptr);
     }
@@ -1232,7 +1235,7 @@ tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tm
         return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "prune gate without displacements");
     const int force = (nl->pruned_build_id != nl->build_id || nl->pruned_margin != gate->margin) ? 1 : 0;
     const GateArgs g{gate->maxd2, nl->prune_state, nl->prune_flag, force, gate->at_build ? 1 : 0, 0.5 * gate->margin};
-    if ((st = launch_refresh_positions(ctx, sys, nl, zero, g)) != TMD_OK) return st;
+    if ((st = launch_refresh_positions(ctx, sys, nl, zero, counter, g)) != TMD_OK) return st;
     nl->pruned_build_id = nl->build_id;
     nl->pruned_margin = gate->margin;
     return prune_rows(ctx, nl, rcut + gate->margin, nl->prune_flag);

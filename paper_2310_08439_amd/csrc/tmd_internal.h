@@ -74,7 +74,8 @@ struct tmd_context {
     tmd::Profiler prof;
     double* h_totals = nullptr;  // pinned host [8]
     int32_t* h_flags = nullptr;  // pinned host [64]
-    // device: counts the workgroups of a launch that have finished (k_finalize); zero between launches
+    // device: counts the workgroups of a k_kick_kinetic that have finished; zero
+    // between launches (every call that makes them waits for the last)
     unsigned int* d_counter = nullptr;
     // device address of the library's static scratch array on this context's
     // device (tmd_energy_forces_noalloc), looked up once per device at creation
@@ -337,9 +338,10 @@ __host__ __device__ inline void unpack_img(int32_t c, int& nx, int& ny, int& nz)
 // Launchers (each enqueues on ctx->stream) ---------------------------------
 tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, double rlist, tmd_nlist* nl,
                                   int32_t* required_capacity);
-// Sorted positions from the caller's; zero (nullable) [3 n] is cleared in the same launch.
+// Sorted positions from the caller's; zero (nullable) [3 n] and *counter
+// (nullable) are cleared in the same launch.
 tmd_status launch_refresh_positions(tmd_context* ctx, const tmd_system_view* sys, const tmd_nlist* nl,
-                                    unsigned long long* zero);
+                                    unsigned long long* zero, unsigned int* counter);
 // Descriptors G [n][F] (sorted order); when Pbuf is non-null the per-atom P
 // tensors (kept components) are kept there for the adjoint: p_slots(m, nl)
 // x S x K x Dr floats.  When Gb is non-null G is stored there instead, as the
@@ -379,9 +381,16 @@ constexpr int kVirDoubles = 12;
 // *nvir_out).
 tmd_status launch_adjoint(tmd_context* ctx, const tmd_model* m, const tmd_nlist* nl, const float* dG, float* Pbuf,
                           unsigned long long* Fq, double* vir_partials, int64_t max_partials, int* nvir_out);
-// part: device scratch of finalize_part_doubles() doubles; host_totals
-// (nullable): pinned host memory that receives the seven totals as well.
-constexpr int64_t finalize_part_doubles() { return 256 * 14; }
+// part: device scratch of finalize_part_doubles() doubles, up to 255 workgroups'
+// sums and their counter (finalize_counter(part)), which must be zero before
+// (launch_refresh_positions); host_totals (nullable): pinned host memory that
+// receives the seven totals as well.  The counter lies with the sums it counts,
+// so that evaluations that share no buffers (the static scratch of
+// tmd_energy_forces_noalloc and a context's workspace) share no counter, and
+// what was captured with the static scratch does not refer to its context.
+constexpr int kMaxPartials = 255;
+constexpr int64_t finalize_part_doubles() { return (kMaxPartials + 1) * 14; }
+inline unsigned int* finalize_counter(double* part) { return reinterpret_cast<unsigned int*>(part + kMaxPartials * 14); }
 tmd_status launch_finalize(tmd_context* ctx, const tmd_nlist* nl, const float* Ei, const unsigned long long* Fq,
                            const double* vir_partials, int nvir, float* atom_energy, float* forces, double* totals7,
                            double* host_totals, double* part);
@@ -456,7 +465,7 @@ struct PruneGate {
 // margin, and only when needed: the decision is taken on the device (no host
 // synchronisation); a new build always prunes.
 tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tmd_nlist* nl, unsigned long long* zero,
-                                double rcut, const PruneGate* gate);
+                                unsigned int* counter, double rcut, const PruneGate* gate);
 // E+F on the stream with device-resident totals (totals7: E, W[6]); gate may
 // be null (skin lists are then pruned to the cutoff at every call).
 tmd_status energy_forces_gated(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys, const tmd_nlist* nl,

@@ -63,7 +63,7 @@ struct tmd_batch {
     double* loss = nullptr;      // [4]
     float* partial = nullptr;    // [tiles][P_int]
     float* grad = nullptr;       // [S][P_int], the gradient in the padded layout
-    int32_t* flag = nullptr;     // [1] set when an entry has no mirror
+    int32_t* flag = nullptr;     // [2] set when an entry has no mirror; k_loss's counter, zero between steps
     int tileT = 0;               // atoms per second-order tile
     int tileQC = 0;              // weight columns per LDS block of the second-order pass
     int tileR = 0;               // sub-tiles of tileT atoms per second-order workgroup
@@ -1365,7 +1365,7 @@ tmd_status tmd_batch_create(tmd_context* ctx, const tmd_model* m, int32_t n_syst
     alloc((void**)&b->sysF, 8 * (size_t)n_systems);
     alloc((void**)&b->loss, 8 * 4 + 8 * (size_t)n_systems);
     alloc((void**)&b->grad, 4 * (size_t)m->S * m->per_species_int);
-    alloc((void**)&b->flag, 4);
+    alloc((void**)&b->flag, 8);
     if (e == hipSuccess) e = hipMemcpy(b->sys_off, sys_off, 8 * (size_t)(n_systems + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->sys_of, sys_of_h.data(), 4 * (size_t)N, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->species, sp_h.data(), 4 * (size_t)N, hipMemcpyHostToDevice);
@@ -1389,7 +1389,7 @@ tmd_status tmd_batch_create(tmd_context* ctx, const tmd_model* m, int32_t n_syst
         tmd_status st = tmd_nlist_create(ctx, nmax, m->S, cap, &nl);
         if (st != TMD_OK) return bail(st);
         int32_t grow = 0;
-        e = hipMemsetAsync(b->flag, 0, 4, ctx->stream);
+        e = hipMemsetAsync(b->flag, 0, 8, ctx->stream);
         if (e != hipSuccess) {
             tmd_nlist_destroy(nl);
             return bail(hip_fail(ctx, e, "pair table"));
@@ -1535,7 +1535,8 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     {
         ProfScope ps_(ctx, "train_loss");
         k_loss<<<b->B, 256, 0, ctx->stream>>>(b->sys_off, b->Ei, b->Fp, b->F_label, N, opts->lambda, b->E_label,
-                                              b->sysE, b->sysF, ctx->d_counter, b->loss, ctx->h_totals, b->loss + 4);
+                                              b->sysE, b->sysF, reinterpret_cast<unsigned int*>(b->flag + 1), b->loss,
+                                              ctx->h_totals, b->loss + 4);
     }
     // 3. descriptor tangent along r
     {

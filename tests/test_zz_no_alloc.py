@@ -106,3 +106,64 @@ def test_noalloc_rejects_what_does_not_fit(tmd, torch):
     nl2.close()
     model.close()
     ctx.close()
+
+
+def test_noalloc_graph_beside_other_evaluations(tmd, torch):
+    """A captured tmd_energy_forces_noalloc shares no buffer with the context's
+    allocating evaluations or its training steps: replays on one stream give
+    the eager totals bit for bit while the context evaluates another system on
+    its own stream (16,384 atoms: eight workgroups merge their sums), and go on
+    doing so after the context that captured them is gone."""
+    _note("noalloc graph beside eager evaluations")
+    spec = inputs.make_model(1, 8, 3, [32], 5.0, seed=104)
+    systems = [inputs.make_system("fcc", 3.61, (16, 16, 16), 0.05, 1, seed=24 + q) for q in range(2)]
+    owner, ctx = tmd.Context(0), tmd.Context(0)
+    model = tmd.Model(owner, spec)
+    data, ref = [], []
+    for s in systems:
+        pos = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+        sp = torch.tensor(s.species, dtype=torch.int32, device="cuda")
+        nl = tmd.NeighborList(owner, s.n, 1, tmd.default_capacity(s.n, s.box, spec.rcut, 1))
+        tmd.build_neighbors(owner, pos, sp, s.box, spec.rcut, 0.0, nl)
+        tot = torch.zeros(7, dtype=torch.float64, device="cuda")
+        F = torch.zeros((s.n, 3), dtype=torch.float32, device="cuda")
+        data.append((pos, sp, s.box, nl, tot, F))
+        tmd.energy_forces_async(owner, model, *data[-1])
+        torch.cuda.synchronize()
+        ref.append((tot.cpu().numpy().copy(), F.cpu().numpy().copy()))
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    lib = tmd.load_library()
+    with torch.cuda.graph(graph, stream=side):
+        assert lib.tmd_context_set_stream(ctx.h, torch.cuda.current_stream().cuda_stream) == 0
+        tmd.energy_forces_noalloc(ctx, model, *data[0])
+    assert lib.tmd_context_set_stream(ctx.h, torch.cuda.current_stream().cuda_stream) == 0
+
+    def check(k):
+        torch.cuda.synchronize()
+        tot, F = data[k][4].cpu().numpy(), data[k][5].cpu().numpy()
+        assert tot[0] == ref[k][0][0] and np.array_equal(F, ref[k][1])
+        assert np.abs(tot[1:] - ref[k][0][1:]).max() <= 1e-12 * np.abs(ref[k][0][1:]).max()
+
+    for _ in range(20):
+        data[0][4].zero_()
+        data[1][4].zero_()
+        torch.cuda.synchronize()
+        for _ in range(3):
+            with torch.cuda.stream(side):
+                graph.replay()
+            tmd.energy_forces_async(ctx, model, *data[1])
+        check(0)
+        check(1)
+    ctx.close()
+    for _ in range(3):
+        data[0][4].zero_()
+        with torch.cuda.stream(side):
+            side.wait_stream(torch.cuda.default_stream())
+            graph.replay()
+        tmd.energy_forces_async(owner, model, *data[1])
+        check(0)
+    del graph
+    for d in data:
+        d[3].close()
+    model.close()
+    owner.close()
