@@ -531,8 +531,8 @@ tmd_status tmd_model_set_params(tmd_model* m, const float* params) {
     // new weights restart the optimiser
     m->opt_t = 0;
     const size_t bytes = (size_t)m->S * m->per_species * 4;
-    if (m->opt_m) TMD_HIP(m->ctx, hipMemset(m->opt_m, 0, bytes));
-    if (m->opt_v) TMD_HIP(m->ctx, hipMemset(m->opt_v, 0, bytes));
+    if (m->opt_m) TMD_HIP(m->ctx, hipMemsetAsync(m->opt_m, 0, bytes, m->ctx->stream));
+    if (m->opt_v) TMD_HIP(m->ctx, hipMemsetAsync(m->opt_v, 0, bytes, m->ctx->stream));
     return upload_params(m, params, false);
 }
 

@@ -372,3 +372,36 @@ def test_tmd_energy_autograd(tmd, ctx, torch):
             vals.append(tmd.energy(p, sp, s.box, ev).item())
         fd = (vals[0] - vals[1]) / (2 * h)
         assert abs(fd - g[i, x].item() / 2.0) <= 2e-3 * max(1.0, abs(fd)) + 1e-3
+
+
+def test_set_params_restarts_the_optimizer_on_another_stream(tmd, torch):
+    """New weights restart Adam before the call returns, whatever the default
+    stream is busy with: a model on a stream of its own (which does not wait
+    for the default one) takes the same first step again bit for bit."""
+    _note("set_params on a non-blocking stream")
+    _, teacher, _ = inputs.workload("train_teacher")
+    _, student, _ = inputs.workload("train_student")
+    b = _cell32_batch()
+    E_l, F_l = _labels(teacher, b)
+    side = torch.cuda.Stream()
+    ctx = tmd.Context(0, stream=side)
+    model = tmd.Model(ctx, student)
+    bt = _device_batch(tmd, ctx, torch, model, b, E_l, F_l)
+    torch.cuda.synchronize()
+    tmd.train_step(ctx, model, bt, lr=1e-3)
+    first = model.get_params()
+    for _ in range(5):
+        tmd.train_step(ctx, model, bt, lr=1e-3)
+    a = torch.randn(8192, 8192, device="cuda")
+    for _ in range(3):
+        a @ a
+        torch.cuda.synchronize()
+        for _ in range(5):
+            a @ a  # some 40 ms on the default stream
+        model.set_params(np.asarray(student.params, dtype=np.float32))
+        tmd.train_step(ctx, model, bt, lr=1e-3)
+        assert np.array_equal(model.get_params(), first)
+    torch.cuda.synchronize()
+    bt.close()
+    model.close()
+    ctx.close()
