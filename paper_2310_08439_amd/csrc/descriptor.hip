@@ -1743,7 +1743,9 @@ tmd_status launch_work_order(tmd_context* ctx, tmd_nlist* nl) {
         nl->wbase_cap = 2 * (nblocks + 1);
     }
     hipError_t e = hipSuccess;
-    int32_t* count = nblocks > kScanBlocks ? (int32_t*)ctx->ws.get("wo.count", sizeof(int32_t) * nblocks, &e) : nullptr;
+    // (at most one block per cell)
+    int32_t* count =
+        nblocks > kScanBlocks ? block_counts(ctx, (int64_t)bg.nc[0] * bg.nc[1] * bg.nc[2], &e) : nullptr;
     if (e != hipSuccess) return hip_fail(ctx, e, "work order workspace");
     WorkGeom g{};
     for (int d = 0; d < 3; ++d) {

@@ -992,14 +992,18 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
     int32_t* cell_sorted = (int32_t*)ctx->ws.get("nb.cell_sorted", sizeof(int32_t) * n, &e);
     int32_t* order = (int32_t*)ctx->ws.get("nb.order", sizeof(int32_t) * n, &e);
     // the flags, the cell counts and (small grids of several species) the
-    // species counts of the cells, cleared together
-    const bool small_grid = ncells <= kScanCells;
-    const int64_t nsp = small_grid && nl->S > 1 ? nl->S * ncells : 0;
-    int32_t* flags = (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + ncells + 1 + nsp), &e);
+    // species counts of the cells, cleared together; the latter where the work
+    // order's block counts go afterwards, which has room for max_cells of them
+    // (a grid of more, nearly as many cells as atoms, groups the species by
+    // launches of their own)
+    const bool small_grid = ncells <= kScanCells, grouped = small_grid && (nl->S == 1 || nl->S * ncells <= max_cells);
+    const int64_t nsp = grouped && nl->S > 1 ? nl->S * ncells : 0;
+    int32_t* flags =
+        (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + ncells + 1 + std::max(nsp, ncells)), &e);
     int32_t* cell_rank = (int32_t*)ctx->ws.get("nb.cell_rank", sizeof(int32_t) * n, &e);
     int32_t *tiles = nullptr, *blkcnt = nullptr, *blkoff = nullptr;
-    if (!small_grid) {
-        tiles = (int32_t*)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((ncells + 1023) / 1024 + 1), &e);
+    if (!small_grid) tiles = (int32_t*)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((ncells + 1023) / 1024 + 1), &e);
+    if (!grouped) {
         blkcnt = (int32_t*)ctx->ws.get("nb.blkcnt", sizeof(int32_t) * kMaxSpecies * nblk, &e);
         blkoff = (int32_t*)ctx->ws.get("nb.blkoff", sizeof(int32_t) * kMaxSpecies * (nblk + 1), &e);
     }
@@ -1051,9 +1055,9 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
         ProfScope ps_(ctx, "nb_sort");
         k_sort_gather<<<(unsigned)((ncells + kBlock / kSortLanes - 1) / (kBlock / kSortLanes)), kBlock, 0, st>>>(
             ncells, cellstart, order, wpos, sys->pos, sys->species, g, nl->perm, nl->shift, nl->xs, nl->sp,
-            cell_sorted, nl->S, cellsp, small_grid ? nl->sp_idx : nullptr);
+            cell_sorted, nl->S, cellsp, grouped ? nl->sp_idx : nullptr);
     }
-    if (!small_grid) {
+    if (!grouped) {
         {
             ProfScope ps_(ctx, "nb_species_blocks");
             k_species_blocks<<<grid_for(n), kBlock, 0, st>>>(n, nl->sp, blkcnt);
@@ -1243,23 +1247,21 @@ tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tm
 
 tmd_status reserve_pruned_rows(tmd_context* ctx, tmd_nlist* nl) { return reserve_pruned(ctx, nl); }
 
-namespace {
-// Most species counts of cells that a build of up to n atoms and S species keeps.
-int64_t flag_cells(int64_t n, int S) {
-    return S > 1 ? S * std::min<int64_t>(kScanCells, std::max<int64_t>(64, 4 * n)) : 0;
+int32_t* block_counts(tmd_context* ctx, int64_t ncells, hipError_t* e) {
+    int32_t* flags = (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + ncells + 1 + ncells), e);
+    return flags ? flags + 64 + ncells + 1 : nullptr;
 }
-}  // namespace
 
 tmd_status reserve_nlist_workspace(tmd_context* ctx, int64_t n, int S) {
+    (void)S;
     hipError_t e = hipSuccess;
     const int64_t nblk = (n + kBlock - 1) / kBlock, cells = std::max<int64_t>(64, 4 * n) + 1;
     (void)ctx->ws.get("nb.wpos", sizeof(double) * 3 * n, &e);
     (void)ctx->ws.get("nb.cell_of", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.cell_sorted", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.order", sizeof(int32_t) * n, &e);
-    (void)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + cells + flag_cells(n, S)), &e);
+    (void)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + 2 * cells), &e);
     (void)ctx->ws.get("nb.tiles", sizeof(int32_t) * ((cells + 1023) / 1024 + 1), &e);
-    (void)ctx->ws.get("wo.count", sizeof(int32_t) * cells, &e);
     (void)ctx->ws.get("nb.cell_rank", sizeof(int32_t) * n, &e);
     (void)ctx->ws.get("nb.blkcnt", sizeof(int32_t) * kMaxSpecies * nblk, &e);
     (void)ctx->ws.get("nb.blkoff", sizeof(int32_t) * kMaxSpecies * (nblk + 1), &e);
@@ -1270,8 +1272,7 @@ tmd_status reserve_nlist_workspace(tmd_context* ctx, int64_t n, int S) {
 size_t nlist_workspace_bytes(int64_t n) {
     const int64_t nblk = (n + kBlock - 1) / kBlock;
     const size_t cells = (size_t)std::max<int64_t>(64, 4 * n) + 1;
-    return (size_t)n * 40 + 8 * cells + 4 * (cells / 1024 + 2) + 8 * (size_t)kMaxSpecies * (nblk + 1) +
-           4 * (size_t)flag_cells(n, kMaxSpecies) + 512;
+    return (size_t)n * 40 + 8 * cells + 4 * (cells / 1024 + 2) + 8 * (size_t)kMaxSpecies * (nblk + 1) + 512;
 }
 
 tmd_status launch_nlist_stats(tmd_context* ctx, const tmd_nlist* nl, int64_t* total_pairs, int32_t* max_row) {

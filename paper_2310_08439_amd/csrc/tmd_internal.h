@@ -474,6 +474,8 @@ tmd_status energy_forces_gated(tmd_context* ctx, const tmd_model* m, const tmd_s
 // Work order for the descriptor and adjoint (see tmd_nlist::wo_valid); called
 // at the end of every successful list build.
 tmd_status launch_work_order(tmd_context* ctx, tmd_nlist* nl);
+// Room for a count per cell, free once the build's species grouping is done.
+int32_t* block_counts(tmd_context* ctx, int64_t ncells, hipError_t* e);
 
 constexpr int kMaxBatchSystems = 4096;
 // Several systems' lists merged into one (tmd_energy_forces_batch): segment s

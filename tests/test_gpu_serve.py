@@ -429,3 +429,27 @@ def test_serve_pruned_rows_after_an_earlier_requests_displacement(tmd, ctx):
         assert np.abs(out["epot"] - epot).max() / len(pos) <= 1e-5
         np.testing.assert_allclose(out["pos"], x, rtol=0, atol=1e-6)
     srv.close()
+
+
+@pytest.mark.parametrize("n_species", [1, 2, 8])
+@pytest.mark.parametrize("max_atoms", [40, 4096, 5000])
+def test_serve_least_budget(tmd, ctx, n_species, max_atoms):
+    """The least budget a server is created with: per slot the evaluation's
+    buffers (G, dG, energies, forces, P, virial and energy partials) and the
+    list build's (positions and five words per atom, two counts per cell of at
+    most max(64, 4 n) cells, scan and species counts), once more the latter for
+    registrations.  A user who sized a budget by it is still served."""
+    _note(f"serve least budget, {n_species} species, {max_atoms} atoms")
+    n, S, slots = max_atoms, n_species, 2
+    F, KD = S * 8 * 4, S * 8 * 16
+    ev = n * (8 * F + 28) + (n + n // 8 + 16384) * 4 * KD + 96 * (4 * n + 64) + 8 * 256 * 14 + 64
+    cells = max(64, 4 * n) + 1
+    lists = n * 40 + 8 * cells + 4 * (cells // 1024 + 2) + 64 * ((n + 255) // 256 + 1) + 512
+    budget = slots * (ev + lists) + lists
+    model = tmd.Model(ctx, inputs.make_model(S, 8, 3, [16], 5.0, seed=105))
+    srv = tmd.Server(model, max_slots=slots, max_atoms=n, skin=1.0, hbm_budget_bytes=budget)
+    srv.close()
+    with pytest.raises(tmd.TMDError) as ei:
+        tmd.Server(model, max_slots=slots, max_atoms=n, skin=1.0, hbm_budget_bytes=budget - 1)
+    assert ei.value.status == 7
+    model.close()
