@@ -263,6 +263,37 @@ size_t eval_workspace_bytes(const tmd_model* m, int64_t n) {
 
 namespace {
 
+// Arrays of a merged list in a context's workspace.
+struct BatchArrays {
+    BatchSeg* segs;
+    double4 *xs, *boxes;
+    int2* chunks;
+    int32_t *nbr, *img, *cnt, *sp_idx;
+};
+BatchArrays batch_arrays(tmd_context* ctx, int64_t nseg, int64_t N, int S, int cap, hipError_t* e) {
+    BatchArrays a;
+    a.segs = (BatchSeg*)ctx->ws.get("batch.segs", sizeof(BatchSeg) * (size_t)nseg, e);
+    a.xs = (double4*)ctx->ws.get("batch.xs", sizeof(double4) * (size_t)N, e);
+    a.boxes = (double4*)ctx->ws.get("batch.boxes", sizeof(double4) * (size_t)N, e);
+    a.chunks = (int2*)ctx->ws.get("batch.chunks", sizeof(int2) * (size_t)(N / kBlock), e);
+    a.nbr = (int32_t*)ctx->ws.get("batch.nbr", sizeof(int32_t) * (size_t)N * S * cap, e);
+    a.img = (int32_t*)ctx->ws.get("batch.img", sizeof(int32_t) * (size_t)N * S * cap, e);
+    a.cnt = (int32_t*)ctx->ws.get("batch.cnt", sizeof(int32_t) * (size_t)N * S, e);
+    a.sp_idx = (int32_t*)ctx->ws.get("batch.sp_idx", sizeof(int32_t) * (size_t)N, e);
+    return a;
+}
+
+}  // namespace
+
+tmd_status reserve_batch_workspace(tmd_context* ctx, const tmd_model* m, int64_t nseg, int64_t N, int cap) {
+    hipError_t e = hipSuccess;
+    (void)batch_arrays(ctx, nseg, N, m->S, cap, &e);
+    if (e != hipSuccess) return hip_fail(ctx, e, "batch workspace allocation");
+    return TMD_OK;
+}
+
+namespace {
+
 tmd_status run_energy_forces_in(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys,
                                 const tmd_nlist* nl, const EvalBuffers& b, double* totals7_dev, double* host_totals,
                                 float* atom_energy, float* forces, const PruneGate* gate) {
@@ -789,30 +820,28 @@ tmd_status tmd_energy_forces_batch(tmd_context* ctx, const tmd_model* m, int32_t
         }
     }
     hipError_t e = hipSuccess;
-    BatchSeg* dsegs = (BatchSeg*)ctx->ws.get("batch.segs", sizeof(BatchSeg) * segs.size(), &e);
-    v.xs = (double4*)ctx->ws.get("batch.xs", sizeof(double4) * N, &e);
-    double4* boxes = (double4*)ctx->ws.get("batch.boxes", sizeof(double4) * N, &e);
-    v.boxes = boxes;
-    int2* chunks = (int2*)ctx->ws.get("batch.chunks", sizeof(int2) * (size_t)(N / kBlock), &e);
-    v.chunks = chunks;
-    v.nbr = (int32_t*)ctx->ws.get("batch.nbr", sizeof(int32_t) * (size_t)N * m->S * cap, &e);
-    v.img = (int32_t*)ctx->ws.get("batch.img", sizeof(int32_t) * (size_t)N * m->S * cap, &e);
-    v.cnt = (int32_t*)ctx->ws.get("batch.cnt", sizeof(int32_t) * (size_t)N * m->S, &e);
-    v.sp_idx = (int32_t*)ctx->ws.get("batch.sp_idx", sizeof(int32_t) * (size_t)N, &e);
+    const BatchArrays w = batch_arrays(ctx, n_systems, N, m->S, cap, &e);
+    v.xs = w.xs;
+    v.boxes = w.boxes;
+    v.chunks = w.chunks;
+    v.nbr = w.nbr;
+    v.img = w.img;
+    v.cnt = w.cnt;
+    v.sp_idx = w.sp_idx;
     if (e != hipSuccess) return hip_fail(ctx, e, "batch workspace allocation");
     EvalBuffers b;
     tmd_status st = eval_buffers(ctx, m, &v, &b);
     if (st != TMD_OK) return st;
     // pageable source: the copy is staged before the call returns
-    TMD_HIP(ctx, hipMemcpyAsync(dsegs, segs.data(), sizeof(BatchSeg) * segs.size(), hipMemcpyHostToDevice,
+    TMD_HIP(ctx, hipMemcpyAsync(w.segs, segs.data(), sizeof(BatchSeg) * segs.size(), hipMemcpyHostToDevice,
                                 ctx->stream));
-    if ((st = launch_batch_merge(ctx, dsegs, n_systems, m->rcut, &v, boxes, chunks, b.Fq)) != TMD_OK) return st;
+    if ((st = launch_batch_merge(ctx, w.segs, n_systems, m->rcut, &v, w.boxes, w.chunks, b.Fq)) != TMD_OK) return st;
     uint16_t* Gb = m->prec == TMD_BF16_MLP ? reinterpret_cast<uint16_t*>(b.G) : nullptr;
     if ((st = launch_descriptors(ctx, m, &v, b.G, b.P, Gb)) != TMD_OK) return st;
     if ((st = launch_mlp(ctx, m, species_groups(&v), m->prec, b.G, Gb, b.Ei, b.dG)) != TMD_OK) return st;
     int nvir = 0;
     if ((st = launch_adjoint(ctx, m, &v, b.dG, b.P, b.Fq, b.vir, b.max_partials, &nvir)) != TMD_OK) return st;
-    return launch_batch_finalize(ctx, dsegs, n_systems, N, b.Fq, b.Ei, b.vir, (int)(N / nvir), totals7);
+    return launch_batch_finalize(ctx, w.segs, n_systems, N, b.Fq, b.Ei, b.vir, (int)(N / nvir), totals7);
 }
 
 tmd_status tmd_energy_forces_noalloc(tmd_context* ctx, const tmd_model* m, const tmd_system_view* sys,

@@ -381,6 +381,11 @@ tmd_status run_request(tmd_server* sv, tmd_context* ctx, hipEvent_t* ev, System*
     return TMD_OK;
 }
 
+// Systems of at most this many atoms (and padded batches of at most
+// kServeBatchAtoms atoms, kServeBatchSystems systems) are batched.
+constexpr int kServeBatchSystems = 64;
+constexpr int64_t kServeBatchAtoms = 65536;
+
 // Energy-and-force requests of several small systems with resident lists in
 // one tmd_energy_forces_batch call (lists rebuilt first where positions have
 // moved beyond skin/2).  outs[i] gets request i's result.
@@ -397,10 +402,21 @@ tmd_status run_batch(tmd_server* sv, tmd_context* ctx, const std::vector<System*
     hipError_t e = hipSuccess;
     // totals [nb][7], then the forces of every system (an MD request recomputes
     // its starting forces, so the resident force arrays need not be written)
-    double* tot = (double*)ctx->ws.get("serve.batch_out", sizeof(double) * 7 * (size_t)nb + 4 * foff[nb], &e);
+    // Room for the largest request that comes alone, as far as the accounted
+    // bytes go (tmd_serve_create), so that these arrays and the merged list's do
+    // not grow with every larger system: growing waits for the whole device.
+    int cap = 64;
+    for (const System* sys : systems) cap = std::max(cap, sys->nl->cap);
+    const int64_t lim = std::min<int64_t>(sv->opts.max_atoms, kServeBatchAtoms);
+    const int64_t lone = std::min<int64_t>((std::min<int64_t>(sv->opts.batch_atoms, lim) + kBlock - 1) / kBlock,
+                                           lim * 64 / cap / kBlock) * kBlock;
+    const size_t out = sizeof(double) * 7 * (size_t)nb + 4 * foff[nb];
+    double* tot = (double*)ctx->ws.get(
+        "serve.batch_out", std::max(out, sizeof(double) * 7 * (size_t)kServeBatchSystems + 12 * (size_t)lone), &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "batch outputs");
     float* fst = reinterpret_cast<float*>(tot + 7 * (size_t)nb);
     tmd_status st;
+    if ((st = reserve_batch_workspace(ctx, m, kServeBatchSystems, lone, cap)) != TMD_OK) return st;
     for (int i = 0; i < nb; ++i) {
         System* sys = systems[i];
         if (!sys->nl_valid && (st = build_list(sv, ctx, sys, &rebuilds[i])) != TMD_OK) return st;
@@ -430,11 +446,6 @@ tmd_status run_batch(tmd_server* sv, tmd_context* ctx, const std::vector<System*
     }
     return TMD_OK;
 }
-
-// Systems of at most this many atoms (and padded batches of at most
-// kServeBatchAtoms atoms, kServeBatchSystems systems) are batched.
-constexpr int kServeBatchSystems = 64;
-constexpr int64_t kServeBatchAtoms = 65536;
 
 // Whether energy-and-force requests on a system may be evaluated together with others.
 bool batchable(const tmd_server* sv, const System* sys) {

@@ -498,8 +498,11 @@ struct BatchSeg {
 };
 // Merged positions, per-atom boxes, rows and species grouping into vnl's arrays;
 // the force accumulators Fq [vnl->n][3] are cleared.
-tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, double rcut, tmd_nlist* vnl, double4* boxes, int2* chunks,
-                              unsigned long long* Fq);
+tmd_status launch_batch_merge(tmd_context* ctx, const BatchSeg* segs, int nseg, double rcut, tmd_nlist* vnl,
+                              double4* boxes, int2* chunks, unsigned long long* Fq);
+// Pre-size the merged list's arrays for nseg segments of N atoms (with their
+// padding) and rows of cap entries.
+tmd_status reserve_batch_workspace(tmd_context* ctx, const tmd_model* m, int64_t nseg, int64_t N, int cap);
 // Forces to each segment's output and per-segment totals [nseg][7]; the adjoint
 // wrote one virial partial per vir_atoms combined atoms.
 tmd_status launch_batch_finalize(tmd_context* ctx, const BatchSeg* segs, int nseg, int64_t N,
