@@ -45,8 +45,9 @@ __device__ __forceinline__ double nh_half(double& xi, double& eta, double& ke, c
 // v *= scale0; v *= scale1 (where non-null); v += (dt/2) a; x += dt v; and
 // (maxd2 non-null) the largest squared displacement since the last list build,
 // as the bits of a non-negative double (ordered like the values); over is set
-// when it exceeds limit2 (sticky, never cleared here).  Grid-stride over a few
-// workgroups per CU, so that few workgroups meet at the one atomicMax.
+// when it exceeds limit2 (sticky, never cleared here).  xmark (nullable): keeps
+// the new positions (mark) or gives those that maxr2 measures from.  Grid-stride
+// over a few workgroups per CU, so that few workgroups meet at the one atomicMax.
 __global__ void __launch_bounds__(256) k_kick_drift(int64_t n, double* __restrict__ x, double* __restrict__ v,
                                                     const float* __restrict__ F, const int32_t* __restrict__ sp,
                                                     const double* __restrict__ acc, double dt,
@@ -54,13 +55,15 @@ __global__ void __launch_bounds__(256) k_kick_drift(int64_t n, double* __restric
                                                     const double* __restrict__ scale1,
                                                     const double* __restrict__ xref,
                                                     unsigned long long* __restrict__ maxd2, double limit2,
-                                                    unsigned long long* __restrict__ over) {
-    __shared__ double red[256];
-    double d2 = 0.0;  // largest over this thread's atoms
+                                                    unsigned long long* __restrict__ over,
+                                                    double* __restrict__ xmark, bool mark,
+                                                    unsigned long long* __restrict__ maxr2) {
+    __shared__ double red[2][256];
+    double d2 = 0.0, r2 = 0.0;  // largest over this thread's atoms
     const double s0 = scale0 ? *scale0 : 1.0, s1 = scale1 ? *scale1 : 1.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double a = acc[sp[i]];
-        double di = 0.0;
+        double di = 0.0, ri = 0.0;
         for (int c = 0; c < 3; ++c) {
             double v0 = v[3 * i + c];
             {
@@ -76,19 +79,28 @@ __global__ void __launch_bounds__(256) k_kick_drift(int64_t n, double* __restric
                 const double d = xi - xref[3 * i + c];
                 di += d * d;
             }
+            if (xmark) {
+                if (mark) xmark[3 * i + c] = xi;
+                const double d = mark ? 0.0 : xi - xmark[3 * i + c];
+                ri += d * d;
+            }
         }
         d2 = fmax(d2, di);
+        r2 = fmax(r2, ri);
     }
     if (!maxd2) return;  // uniform over the grid
-    red[threadIdx.x] = d2;
+    red[0][threadIdx.x] = d2;
+    red[1][threadIdx.x] = r2;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
+        if ((int)threadIdx.x < w)
+            for (int q = 0; q < 2; ++q) red[q][threadIdx.x] = fmax(red[q][threadIdx.x], red[q][threadIdx.x + w]);
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        atomicMax(maxd2, (unsigned long long)__double_as_longlong(red[0]));
-        if (over && red[0] > limit2) *over = 1ull;
+        atomicMax(maxd2, (unsigned long long)__double_as_longlong(red[0][0]));
+        if (xmark) atomicMax(maxr2, (unsigned long long)__double_as_longlong(red[1][0]));
+        if (over && red[0][0] > limit2) *over = 1ull;
     }
 }
 
@@ -197,9 +209,11 @@ unsigned blocks_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 tmd_status launch_kick_drift(tmd_context* ctx, int64_t n, double* x, double* v, const float* F, const int32_t* sp,
                              const double* acc, double dt, const double* scale0, const double* scale1,
-                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over) {
+                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over,
+                             double* xmark, bool mark, unsigned long long* maxr2) {
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks_of(n), 4 * (int64_t)ctx->num_cus));
-    k_kick_drift<<<grid, kBlock, 0, ctx->stream>>>(n, x, v, F, sp, acc, dt, scale0, scale1, xref, maxd2, limit2, over);
+    k_kick_drift<<<grid, kBlock, 0, ctx->stream>>>(n, x, v, F, sp, acc, dt, scale0, scale1, xref, maxd2, limit2, over,
+                                                   xmark, mark, maxr2);
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;
 }

@@ -486,7 +486,8 @@ __global__ void __launch_bounds__(256) k_prune(int64_t n, int S, int cap, double
 // Does this evaluation need new pruned rows (see PruneGate)?  One thread.
 struct GateArgs {
     const unsigned long long* maxd2;
-    double* state;
+    const unsigned long long* maxr2;  // nullptr: not known
+    double* state;                    // [3], see tmd_nlist::prune_state
     int32_t* flag;  // nullptr: no gate
     int force;
     int at_build;  // the list was built at these positions (maxd2 still refers to the build before)
@@ -494,9 +495,13 @@ struct GateArgs {
 };
 __device__ __forceinline__ void prune_gate(const GateArgs& g) {
     const double d = g.at_build ? 0.0 : sqrt(__longlong_as_double((long long)g.maxd2[0]));
-    if (g.force || !(d + g.state[0] < g.half_margin)) {
+    const double r = g.maxr2 ? sqrt(__longlong_as_double((long long)g.maxr2[0])) : __builtin_inf();
+    const bool complete = fmin(d + g.state[1], r + g.state[2]) < g.half_margin;
+    if (g.force || !complete || !(d + g.state[0] < g.half_margin)) {
         g.flag[0] = 1;
-        g.state[0] = d;
+        g.state[0] = g.force ? 0.0 : d;
+        g.state[1] = d;
+        g.state[2] = r;
     } else {
         g.flag[0] = 0;
     }
@@ -1182,7 +1187,7 @@ tmd_status reserve_pruned(tmd_context* ctx, tmd_nlist* nl) {
     hipError_t e = hipMalloc((void**)&nl->pnbr, 4 * lst);
     if (e == hipSuccess) e = hipMalloc((void**)&nl->pimg, 4 * lst);
     if (e == hipSuccess) e = hipMalloc((void**)&nl->pcnt, 4 * (size_t)nl->nmax * nl->S);
-    if (e == hipSuccess) e = hipMalloc((void**)&nl->prune_state, 16);
+    if (e == hipSuccess) e = hipMalloc((void**)&nl->prune_state, 32);
     if (e != hipSuccess) {
         for (void** q : {(void**)&nl->pnbr, (void**)&nl->pimg, (void**)&nl->pcnt, (void**)&nl->prune_state}) {
             if (*q) (void)hipFree(*q);
@@ -1190,7 +1195,7 @@ tmd_status reserve_pruned(tmd_context* ctx, tmd_nlist* nl) {
         }
         return hip_fail(ctx, e, "pruned neighbour list allocation");
     }
-    nl->prune_flag = reinterpret_cast<int32_t*>(nl->prune_state + 1);
+    nl->prune_flag = reinterpret_cast<int32_t*>(nl->prune_state + 3);
     return TMD_OK;
 }
 
@@ -1238,7 +1243,8 @@ tmd_status launch_refresh_prune(tmd_context* ctx, const tmd_system_view* sys, tm
     if (!gate->maxd2 || !(gate->margin > 0.0))
         return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "prune gate without displacements");
     const int force = (nl->pruned_build_id != nl->build_id || nl->pruned_margin != gate->margin) ? 1 : 0;
-    const GateArgs g{gate->maxd2, nl->prune_state, nl->prune_flag, force, gate->at_build ? 1 : 0, 0.5 * gate->margin};
+    const GateArgs g{gate->maxd2, gate->maxr2, nl->prune_state,         nl->prune_flag,
+                     force,       gate->at_build ? 1 : 0, 0.5 * gate->margin};
     if ((st = launch_refresh_positions(ctx, sys, nl, zero, counter, g)) != TMD_OK) return st;
     nl->pruned_build_id = nl->build_id;
     nl->pruned_margin = gate->margin;

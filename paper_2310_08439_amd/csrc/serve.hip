@@ -203,10 +203,12 @@ struct SlotBuffers {
     double* tot = nullptr;                 // [7 (n_steps + 1)]
     double* ekin = nullptr;                // [4 (n_steps + 1)] kinetic tensor diagonal and total
     double* part = nullptr;                // [3 kKeBlocks]
-    unsigned long long* maxd2 = nullptr;   // [n_steps + 1] largest squared displacement since the build, per step
+    unsigned long long* max2 = nullptr;    // [n_steps + 1][2] largest squared displacements since the build and since
+                                           // the request's first step, per step
     unsigned long long* flag = nullptr;    // [1] nonzero: some step moved an atom beyond skin/2
     double* x0 = nullptr;                  // [n][3] positions and velocities at the start of an MD request
     double* v0 = nullptr;
+    double* x1 = nullptr;                  // [n][3] positions after its first step
 };
 
 tmd_status slot_buffers(tmd_context* ctx, int n_steps, int64_t n, SlotBuffers* b) {
@@ -214,10 +216,11 @@ tmd_status slot_buffers(tmd_context* ctx, int n_steps, int64_t n, SlotBuffers* b
     b->tot = (double*)ctx->ws.get("md.tot", sizeof(double) * 7 * (size_t)(n_steps + 1), &e);
     b->ekin = (double*)ctx->ws.get("md.ekin", sizeof(double) * 4 * (size_t)(n_steps + 1), &e);
     b->part = (double*)ctx->ws.get("md.part", sizeof(double) * 3 * kKeBlocks, &e);
-    b->maxd2 = (unsigned long long*)ctx->ws.get("md.maxd2", sizeof(unsigned long long) * (size_t)(n_steps + 1), &e);
+    b->max2 = (unsigned long long*)ctx->ws.get("md.max2", sizeof(unsigned long long) * 2 * (size_t)(n_steps + 1), &e);
     b->flag = (unsigned long long*)ctx->ws.get("md.flag", sizeof(unsigned long long), &e);
     b->x0 = (double*)ctx->ws.get("md.x0", 24 * (size_t)n, &e);
     b->v0 = (double*)ctx->ws.get("md.v0", 24 * (size_t)n, &e);
+    b->x1 = (double*)ctx->ws.get("md.x1", 24 * (size_t)n, &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "MD workspace");
     return TMD_OK;
 }
@@ -229,10 +232,9 @@ tmd_status kinetic(tmd_context* ctx, const System* sys, double dt, double* part,
 }
 
 // The steps of an MD request with no host synchronisation between them: each
-// step's largest displacement since the list build (maxd2[s]) gates the
-// reuse of pruned rows on the device, and a sticky device flag records
-// whether any step moved an atom beyond skin/2, which would have made the
-// list incomplete.  The caller reads the flag with the results.  The steps go
+// step's largest displacements (max2[s]) gate the reuse of pruned rows on the
+// device, and a sticky device flag records whether any step moved an atom beyond
+// skin/2, which would have made the list incomplete.  The caller reads the flag with the results.  The steps go
 // out in chunks of kMdChunkAtomSteps: after queueing chunk c the host waits
 // for the end of chunk c - 1 (ev[0], ev[1] alternate), which leaves chunk c
 // queued, so the device never idles for the wait.
@@ -241,15 +243,16 @@ tmd_status md_steps_device_gated(tmd_server* sv, tmd_context* ctx, System* sys, 
     const tmd_model* m = sv->model;
     const double half_skin2 = 0.25 * sv->opts.skin * sv->opts.skin;
     tmd_status st;
-    if ((st = launch_zero_u64(ctx, b.maxd2, nsteps + 1)) != TMD_OK) return st;
+    if ((st = launch_zero_u64(ctx, b.max2, 2 * ((int64_t)nsteps + 1))) != TMD_OK) return st;
     int64_t queued = 0;  // atom-steps queued since the last chunk end
     int chunk = 0;
     for (int s = 1; s <= nsteps; ++s) {
         if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, nullptr, nullptr,
-                                    sys->xref, b.maxd2 + s, half_skin2, b.flag)) != TMD_OK)
+                                    sys->xref, b.max2 + 2 * s, half_skin2, b.flag, b.x1, s == 1, b.max2 + 2 * s + 1)) != TMD_OK)
             return st;
         PruneGate gate;
-        gate.maxd2 = b.maxd2 + s;
+        gate.maxd2 = b.max2 + 2 * s;
+        gate.maxr2 = b.max2 + 2 * s + 1;
         gate.margin = 0.2 * sv->opts.skin;
         if ((st = energy_forces_gated(ctx, m, &view, sys->nl, b.tot + 7 * s, nullptr, sys->F, &gate)) != TMD_OK)
             return st;
@@ -273,26 +276,29 @@ tmd_status md_steps_host_checked(tmd_server* sv, tmd_context* ctx, System* sys, 
     const double half_skin2 = 0.25 * sv->opts.skin * sv->opts.skin;
     tmd_status st;
     for (int s = 1; s <= nsteps; ++s) {
-        if ((st = launch_zero_u64(ctx, b.maxd2 + s, 1)) != TMD_OK) return st;
+        unsigned long long* const maxd2 = b.max2 + 2 * s;
+        unsigned long long* const maxr2 = maxd2 + 1;
+        if ((st = launch_zero_u64(ctx, maxd2, 2)) != TMD_OK) return st;
         if ((st = launch_kick_drift(ctx, sys->n, sys->x, sys->v, sys->F, sys->sp, sys->acc, dt, nullptr, nullptr,
-                                    sys->xref, b.maxd2 + s, half_skin2, nullptr)) != TMD_OK)
+                                    sys->xref, maxd2, half_skin2, nullptr, b.x1, s == 1, maxr2)) != TMD_OK)
             return st;
         unsigned long long bits = 0;
-        TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, b.maxd2 + s, sizeof(bits), hipMemcpyDeviceToHost, ctx->stream));
+        TMD_HIP(ctx, hipMemcpyAsync(ctx->h_flags, maxd2, sizeof(bits), hipMemcpyDeviceToHost, ctx->stream));
         TMD_HIP(ctx, hipStreamSynchronize(ctx->stream));
         std::memcpy(&bits, ctx->h_flags, sizeof(bits));
         double d2;
         std::memcpy(&d2, &bits, sizeof(d2));
-        // b.maxd2[s] holds this system's displacement since its build: the
-        // pruned rows are reused while it allows (the request's first
-        // evaluation pruned to the cutoff, so the first step here prunes)
+        // maxd2 holds this system's displacement since its build: the pruned
+        // rows are reused while it allows (the request's first evaluation pruned
+        // to the cutoff, so the first step here prunes)
         PruneGate gate;
         if (!(d2 <= half_skin2)) {
             sys->nl_valid = false;
             if ((st = build_list(sv, ctx, sys, rebuilds)) != TMD_OK) return st;
             gate.at_build = true;
         }
-        gate.maxd2 = b.maxd2 + s;
+        gate.maxd2 = maxd2;
+        gate.maxr2 = maxr2;
         gate.margin = 0.2 * sv->opts.skin;
         if ((st = energy_forces_gated(ctx, m, &view, sys->nl, b.tot + 7 * s, nullptr, sys->F,
                                       sv->opts.skin > 0.0 ? &gate : nullptr)) != TMD_OK)

@@ -294,7 +294,7 @@ struct tmd_nlist {
     int32_t* pnbr = nullptr;
     int32_t* pimg = nullptr;
     int32_t* pcnt = nullptr;
-    double* prune_state = nullptr;  // device: displacement since the build at the last margin prune
+    double* prune_state = nullptr;  // device: (d_0, d_p, r_p) of the last margin prune (PruneGate)
     int32_t* prune_flag = nullptr;  // device: 1 when this evaluation prunes
     int64_t build_id = 0;           // count of builds
     int64_t pruned_build_id = -1;   // build the pruned rows come from (margin prunes only)
@@ -422,10 +422,13 @@ tmd_status reserve_pruned_rows(tmd_context* ctx, tmd_nlist* nl);
 // First half of a step: v *= *scale0, v *= *scale1 (each nullable), v += (dt/2) a,
 // x += dt v; maxd2 (nullable) receives the largest squared displacement from
 // xref as ordered bits, and *over (nullable) is set when it exceeds limit2
-// (sticky: never cleared here).
+// (sticky: never cleared here).  xmark (nullable, with maxd2 and maxr2): the new
+// positions are kept there (mark), or maxr2 receives the largest squared
+// displacement from them.
 tmd_status launch_kick_drift(tmd_context* ctx, int64_t n, double* x, double* v, const float* F, const int32_t* sp,
                              const double* acc, double dt, const double* scale0, const double* scale1,
-                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over);
+                             const double* xref, unsigned long long* maxd2, double limit2, unsigned long long* over,
+                             double* xmark = nullptr, bool mark = false, unsigned long long* maxr2 = nullptr);
 // Nose-Hoover variable of a system (state nullptr: none); second: apply the
 // half step that ends a step before the one that begins the next.
 struct Thermostat {
@@ -445,16 +448,23 @@ tmd_status launch_kick_kinetic(tmd_context* ctx, int64_t n, double* v, const flo
 tmd_status launch_zero_u64(tmd_context* ctx, unsigned long long* p, int64_t n);
 // Displacement tracking that lets pruned rows be reused: maxd2 (device) holds
 // the bits of the largest squared displacement of any atom since the list was
-// built, for the positions being evaluated.  Rows pruned to rcut + margin when
-// the largest displacement since the build was d_p keep every pair within
-// rcut while d + d_p < margin / 2 (each of a pair's atoms moved by at most
-// d + d_p since the prune), so they are rebuilt only when that fails.  A prune
-// is also forced by a new build, by another margin and after an evaluation
-// without a gate; the last two may find the atoms anywhere within the skin, so
-// d_p is what maxd2 says, except at the very positions of a build (at_build),
-// where it is 0 and maxd2 need not have been cleared.
+// built, for the positions being evaluated, and maxr2 (nullable) that since
+// another, later state, from which it is smaller (the first step of a server's
+// MD request, whose list may be older).  Rows pruned to rcut + margin when these
+// displacements were d_p and r_p keep every pair within rcut while
+// d + d_p < margin / 2 or r + r_p < margin / 2 (each of a pair's atoms moved by
+// at most that since the prune); when neither holds they are made anew.  A
+// prune is also forced by a new build, by another margin and after an
+// evaluation without a gate; the last two may find the atoms anywhere within
+// the skin, so that d_p is what maxd2 says, except at the very positions of a
+// build (at_build), where it is 0 and maxd2 need not have been cleared.  Rows
+// are made anew at d + d_0 >= margin / 2 as well, d_0 = 0 after a forced prune
+// and d_p after another: this alone would not do (an older list's d_p is not
+// 0), but when rows are made anew decides the last bits of the forces, through
+// the order of their sums, and a request's steps keep theirs.
 struct PruneGate {
     const unsigned long long* maxd2 = nullptr;
+    const unsigned long long* maxr2 = nullptr;
     double margin = 0.0;
     bool at_build = false;
 };
