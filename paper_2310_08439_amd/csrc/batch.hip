@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(256) k_batch_rows(const BatchSeg* __restrict__
                 const double4 xj = xs[q];
                 const double dx = (xj.x - xi.x) + (double)nx * sg.L[0], dy = (xj.y - xi.y) + (double)ny * sg.L[1],
                              dz = (xj.z - xi.z) + (double)nz * sg.L[2];
-                keep = dx * dx + dy * dy + dz * dz < rc2;
+                keep = !(dx * dx + dy * dy + dz * dz >= rc2);  // (a NaN distance is not passed over)
             }
             const unsigned long long m = __ballot(keep);
             if (keep) {

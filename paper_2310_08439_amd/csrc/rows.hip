@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256) k_descriptor_rows(PathArgs a, int64_t nbl
                 d = pos.disp(pos.fetch(a.nbr[base + c], im, slot), im);
                 r2 = d.x * d.x + d.y * d.y + d.z * d.z;
             }
-            if (r2 < a.rc2) {
+            if (!(r2 >= a.rc2)) {  // (a NaN distance is not passed over)
                 const float rinv = __builtin_amdgcn_rsqf(r2), R = r2 * rinv;
                 reduced_monomials<3>(d.x * rinv, d.y * rinv, d.z * rinv, Mv);
                 fc = TAB ? 1.0f : 0.5f * __builtin_amdgcn_cosf(R * a.half_inv_rc) + 0.5f;
@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(kRowThreads, RAD == kRadDirect && KC * NCH == 
                     const int32_t im = a.img[base + c];
                     const float3 e = pos.disp(pos.fetch(a.nbr[base + c], im, q), im);
                     const float e2 = e.x * e.x + e.y * e.y + e.z * e.z;
-                    in = e2 < a.rc2;
+                    in = !(e2 >= a.rc2);
                     if (in) d = e, r2 = e2;
                 }
                 float gx, gy, gz;

@@ -287,3 +287,40 @@ def test_network_shapes_many_atoms(ctx, hidden, bf16):
     _, Ea, F, _ = ev.energy_forces(pos, torch.tensor(s.species, dtype=torch.int32, device="cuda"), s.box)
     parity.check_sampled(Ea.cpu().numpy().astype(np.float64), F.cpu().numpy().astype(np.float64), s, spec, bf16,
                          n_sample=300)
+
+
+# a coordinate that is no number (an MD run that blew up) shows in the energy
+# and the virial of its system, and in no other of the batch
+@pytest.mark.parametrize("K,M,table", [(8, 3, 0.0), (12, 3, 0.0), (16, 3, 0.005), (6, 3, 0.0), (8, 2, 0.0)])
+def test_nan_position(ctx, K, M, table):
+    import torch
+    from paper_2310_08439_amd import tmd
+    spec = inputs.make_model(2, K, M, [16], 5.0, seed=K)
+    spec.tab_dr = table
+    model = tmd.Model(ctx, spec, tmd.FP32)
+    systems = [_thin(1, 6, 4, 2, 31), _thin(4, 4, 4, 2, 32), _thin(4, 4, 3, 2, 33)]
+    views, lists, forces = [], [], []
+    for s in systems:
+        x = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+        sp = torch.tensor(s.species, dtype=torch.int32, device="cuda")
+        nl = tmd.NeighborList(ctx, s.n, 2, tmd.default_capacity(s.n, s.box, 5.0, 1))
+        tmd.build_neighbors(ctx, x, sp, s.box, 5.0, 0.0, nl)
+        views.append((x, sp, s.box))
+        lists.append(nl)
+        forces.append(torch.empty((s.n, 3), dtype=torch.float32, device="cuda"))
+    totals = torch.empty((3, 7), dtype=torch.float64, device="cuda")
+    print(f"[case] NaN position, K = {K}, M = {M}, table {table}", flush=True)
+    tmd.energy_forces_batch(ctx, model, views, lists, totals, forces)
+    good, good_f = totals.cpu().numpy(), [f.cpu().numpy() for f in forces]
+    assert np.isfinite(good).all()
+    views[1][0][5, 0] = float("nan")
+    tmd.energy_forces_batch(ctx, model, views, lists, totals, forces)
+    t = totals.cpu().numpy()
+    assert np.isnan(t[1]).all()
+    for q in (0, 2):
+        assert np.array_equal(t[q], good[q]) and np.array_equal(forces[q].cpu().numpy(), good_f[q])
+    # the thin box alone, whose list has no work order
+    one = torch.empty(7, dtype=torch.float64, device="cuda")
+    views[0][0][7, 2] = float("nan")
+    tmd.energy_forces_async(ctx, model, *views[0], lists[0], one, forces[0], None)
+    assert np.isnan(one.cpu().numpy()).all()
