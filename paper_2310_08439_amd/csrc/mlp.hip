@@ -17,7 +17,8 @@
 //   FP32: v_mfma_f32_16x16x4_f32.  One K-step covers 4 units, lane group g
 //         holding unit 16*blk + 4g + r in step (blk, r).
 // Three forms: k_mlp (a layer's rows shared by four waves, weights from L2),
-// k_mlp_staged and k_mlp_resident (whole layers per wave, weights in LDS).  All
+// k_mlp_staged (whole layers per wave, weights through LDS, many atoms) and
+// k_mlp_resident (the same, weights kept in LDS, large BF16 systems).  All
 // add a unit's products in the same order, so they agree bit for bit.
 #include "tmd_internal.h"
 
@@ -411,62 +412,82 @@ __global__ void __launch_bounds__(256) k_mlp(MlpArgs a) {
     }
 }
 
-// Staged form (H = 128, one or two hidden layers): eight waves take 16 atoms
-// each, activations never leave a wave's registers, and each layer's weights
-// pass once per 128 atoms through LDS, 32 KB at a time.  It fills the chip in one round
-// from 16,384 to 65,536 atoms, where the form above needs two or three: 54,000
-// atoms, 96-128-128-1: 21 us against 32.
-// (128 registers: two workgroups on a CU; with 136 the FP32 form took 1,094 us
-// for 877,952 atoms.)
-template <bool BF16, int L, int ACT>
-__global__ void __launch_bounds__(512, L == 1 || ACT == TMD_ACT_TANH ? 4 : 2) k_mlp_staged(MlpArgs a) {
+// Staged form: every wave takes 16 atoms (128 units, eight waves) or 32 (fewer
+// units, four waves), activations never leave a wave's registers, and each
+// layer's weights pass once per 128 atoms through LDS, panels of four reduction
+// blocks at a time.  Bound by the products and, in FP32, their operands' way
+// from LDS: 1,000,188 atoms of 32-64-64: 239 us in FP32 (k_mlp, weights from L2
+// per 32 atoms: 334), 82 in BF16 (207); of 32-32 73 (192) and 51 (173); 54,000
+// of 96-128-128 in BF16 21 (32).  (128 registers where one or two layers allow
+// it, so that four waves share a SIMD: with 136 the FP32 form of 128-128 took
+// 1,094 us for 877,952 atoms, with 128 892.)
+constexpr int staged_waves(int H) { return H == 128 ? 8 : 4; }
+constexpr int staged_cols(int H) { return H == 128 ? 1 : 2; }  // 16-atom columns of a wave
+// Waves on a SIMD that the registers are to allow (512 / waves each).
+constexpr int staged_occupancy(int H, int L, int act) {
+    if (H == 32) return 4;
+    if (H == 64) return act == TMD_ACT_TANH ? (L <= 2 ? 4 : L == 3 ? 3 : 2) : (L == 1 ? 4 : 2);
+    return L == 1 || (L == 2 && act == TMD_ACT_TANH) ? 4 : 2;
+}
+template <bool BF16, int H, int L, int ACT>
+__global__ void __launch_bounds__(64 * staged_waves(H), staged_occupancy(H, L, ACT)) k_mlp_staged(MlpArgs a) {
     using O = Op<BF16>;
     using A = typename O::A;
     using T = std::conditional_t<BF16, __hip_bfloat16, float>;
-    constexpr int H = 128, NB = H / 16, KB = H / O::kBlock;
-    constexpr int PB = 4;          // reduction blocks of 1 KB per row block in a panel
-    constexpr int RB = 32 / KB;    // row blocks of W_1^T in a panel
+    constexpr int CB = staged_cols(H), kThreads = 64 * staged_waves(H), kAtoms = kThreads / 4 * CB;
+    constexpr int NB = H / 16, KB = H / O::kBlock;
+    constexpr int PB = 4;              // reduction blocks of 1 KB per row block in a panel
+    constexpr int RB = NB * PB / KB;   // row blocks of W_1^T in a panel
     // BF16: a panel in operand order.  FP32: rows padded by 28 floats (pads of
     // 20 to 36 are alike, 4 or 44 and more a quarter slower).
     constexpr int PS = 16 * PB + 28, FS = H + 28;
-    __shared__ __attribute__((aligned(16))) T lds[BF16 ? 16 * 1024 : H * PS];
+    constexpr int kLds = BF16 ? NB * PB * 512 : (H * PS > 16 * RB * FS ? H * PS : 16 * RB * FS);
+    __shared__ __attribute__((aligned(16))) T lds[kLds];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int col = lane & 15, grp = lane >> 4;
     const int64_t tile = blockIdx.x;
     int s = 0;
     for (int q = 0; q < a.S; ++q)
         if (tile >= a.tile_off[q] && tile < a.tile_off[q + 1]) s = q;
-    const int64_t r = a.sp_off[s] + (tile - a.tile_off[s]) * 128 + wv * 16 + col;
-    const bool valid = r < a.sp_off[s + 1];
-    const int64_t atom = valid ? (int64_t)a.sp_idx[r] : 0;
+    const int64_t first = a.sp_off[s] + (tile - a.tile_off[s]) * kAtoms + wv * 16 * CB + col;
+    bool valid[CB];
+    int64_t atom[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        valid[cb] = first + 16 * cb < a.sp_off[s + 1];
+        atom[cb] = valid[cb] ? (int64_t)a.sp_idx[first + 16 * cb] : 0;
+    }
     const T* wsp;
     if constexpr (BF16) wsp = a.wbf + s * a.wstride;
     else wsp = a.w32 + s * a.wstride;
     const float* bias = a.bias + (int64_t)s * L * H;
-    f32x4 acc[NB], x[NB], dact[L][NB];
+    f32x4 acc[NB][CB], x[NB][CB], dact[L][NB][CB];
     auto set_bias = [&](const float* bl) {
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob) {
             f32x4 init = {0, 0, 0, 0};
             if (bl) init = *reinterpret_cast<const f32x4*>(bl + 16 * ob + 4 * grp);
-            acc[ob] = init;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = init;
         }
     };
     auto activate = [&](int l) {
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float z = acc[ob][q];
-                const float y = act_f<ACT>(z);
-                dact[l][ob][q] = act_df<ACT>(z, y);
-                acc[ob][q] = y;
-            }
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float z = acc[ob][cb][q];
+                    const float y = act_f<ACT>(z);
+                    dact[l][ob][cb][q] = act_df<ACT>(z, y);
+                    acc[ob][cb][q] = y;
+                }
     };
     // blocks c .. c + n - 1 of every row block of a matrix with nk blocks a row
     auto panel = [&](const T* W, int nk, int c, int n) {
         __syncthreads();
-        for (int q = threadIdx.x; q < NB * n * 64; q += 512) {
+        for (int q = threadIdx.x; q < NB * n * 64; q += kThreads) {
             const int ob = q / (n * 64), e = q - ob * (n * 64);
             const uint4 v = reinterpret_cast<const uint4*>(W)[(ob * nk + c) * 64 + e];
             if constexpr (BF16) reinterpret_cast<uint4*>(lds)[q] = v;
@@ -478,22 +499,31 @@ __global__ void __launch_bounds__(512, L == 1 || ACT == TMD_ACT_TANH ? 4 : 2) k_
         if constexpr (BF16) return O::load_w(lds, n, ob, k, lane);
         else return *reinterpret_cast<const f32x4*>(lds + (16 * ob + col) * PS + 16 * k + 4 * grp);
     };
-    auto operand = [&](const f32x4 (&v)[NB], int k) {
-        if constexpr (BF16) return cat8(to_bf4(v[2 * k]), to_bf4(v[2 * k + 1]));
-        else return v[k];
+    auto operand = [&](const f32x4 (&v)[NB][CB], int k, int cb) {
+        if constexpr (BF16) return cat8(to_bf4(v[2 * k][cb]), to_bf4(v[2 * k + 1][cb]));
+        else return v[k][cb];
     };
     auto dense = [&](const T* W, const float* bl) {
 #pragma unroll
-        for (int ob = 0; ob < NB; ++ob) x[ob] = acc[ob];
+        for (int ob = 0; ob < NB; ++ob)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) x[ob][cb] = acc[ob][cb];
         set_bias(bl);
+        constexpr int n = PB < KB ? PB : KB;
 #pragma unroll
-        for (int c = 0; c < KB; c += PB) {
-            panel(W, KB, c, PB);
+        for (int c = 0; c < KB; c += n) {
+            panel(W, KB, c, n);
 #pragma unroll
-            for (int k = 0; k < PB; ++k) {
-                const A xv = operand(x, c + k);
+            for (int k = 0; k < n; ++k) {
+                A xv[CB];
 #pragma unroll
-                for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(from_panel(PB, ob, k), xv, acc[ob]);
+                for (int cb = 0; cb < CB; ++cb) xv[cb] = operand(x, c + k, cb);
+#pragma unroll
+                for (int ob = 0; ob < NB; ++ob) {
+                    const A w = from_panel(n, ob, k);
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = O::mul(w, xv[cb], acc[ob][cb]);
+                }
             }
         }
     };
@@ -504,9 +534,15 @@ __global__ void __launch_bounds__(512, L == 1 || ACT == TMD_ACT_TANH ? 4 : 2) k_
         const int n = min(PB, nk - c);
         panel(wsp + a.w_off[0], nk, c, n);
         for (int k = 0; k < n; ++k) {
-            const A xv = O::load_g(a, atom, c + k, grp, valid);
+            A xv[CB];
 #pragma unroll
-            for (int ob = 0; ob < NB; ++ob) acc[ob] = O::mul(from_panel(n, ob, k), xv, acc[ob]);
+            for (int cb = 0; cb < CB; ++cb) xv[cb] = O::load_g(a, atom[cb], c + k, grp, valid[cb]);
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                const A w = from_panel(n, ob, k);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[ob][cb] = O::mul(w, xv[cb], acc[ob][cb]);
+            }
         }
     }
     activate(0);
@@ -516,49 +552,64 @@ __global__ void __launch_bounds__(512, L == 1 || ACT == TMD_ACT_TANH ? 4 : 2) k_
         activate(l);
     }
     const float* wo = a.wout + (int64_t)s * H;
-    float e = 0.0f;
+    float e[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) e[cb] = 0.0f;
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
         const f32x4 w4 = *reinterpret_cast<const f32x4*>(wo + 16 * ob + 4 * grp);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            e = fmaf(w4[q], acc[ob][q], e);
-            acc[ob][q] = w4[q] * dact[L - 1][ob][q];
-        }
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                e[cb] = fmaf(w4[q], acc[ob][cb][q], e[cb]);
+                acc[ob][cb][q] = w4[q] * dact[L - 1][ob][cb][q];
+            }
     }
-    e += __shfl_xor(e, 16);
-    e += __shfl_xor(e, 32);
-    if (grp == 0 && valid) a.Ei[atom] = e + a.bout[s];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        e[cb] += __shfl_xor(e[cb], 16);
+        e[cb] += __shfl_xor(e[cb], 32);
+        if (grp == 0 && valid[cb]) a.Ei[atom[cb]] = e[cb] + a.bout[s];
+    }
 #pragma unroll
     for (int l = L - 1; l >= 1; --l) {
         dense(wsp + a.wt_off[l], nullptr);
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[ob][q] *= dact[l - 1][ob][q];
-    }
-    A xv[KB];
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int k = 0; k < KB; ++k) xv[k] = operand(acc, k);
+                for (int q = 0; q < 4; ++q) acc[ob][cb][q] *= dact[l - 1][ob][cb][q];
+    }
+    A xv[KB][CB];
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) xv[k][cb] = operand(acc, k, cb);
     for (int f0 = 0; f0 < a.Fpad / 16; f0 += RB) {
         const int nf = min(RB, a.Fpad / 16 - f0);
         __syncthreads();
-        for (int q = threadIdx.x; q < nf * KB * 64; q += 512) {
+        for (int q = threadIdx.x; q < nf * KB * 64; q += kThreads) {
             const uint4 v = reinterpret_cast<const uint4*>(wsp + a.wt_off[0])[f0 * KB * 64 + q];
             if constexpr (BF16) reinterpret_cast<uint4*>(lds)[q] = v;
             else *reinterpret_cast<uint4*>(lds + (q / (KB * 64) * 16 + (q & 15)) * FS + 4 * (q % (KB * 64) >> 4)) = v;
         }
         __syncthreads();
         for (int fb = 0; fb < nf; ++fb) {
-            f32x4 out = {0, 0, 0, 0};
+            f32x4 out[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) out[cb] = f32x4{0, 0, 0, 0};
 #pragma unroll
             for (int k = 0; k < KB; ++k) {
                 A w;
                 if constexpr (BF16) w = O::load_w(lds, KB, fb, k, lane);
                 else w = *reinterpret_cast<const f32x4*>(lds + (16 * fb + col) * FS + 16 * k + 4 * grp);
-                out = O::mul(w, xv[k], out);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) out[cb] = O::mul(w, xv[k][cb], out[cb]);
             }
-            store_dg4(a.dG, atom, a.F, 16 * (f0 + fb) + 4 * grp, valid, out);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) store_dg4(a.dG, atom[cb], a.F, 16 * (f0 + fb) + 4 * grp, valid[cb], out[cb]);
         }
     }
 }
@@ -718,11 +769,6 @@ constexpr int kMaxResidentLds = 150 * 1024;
 
 using MlpFn = void (*)(MlpArgs);
 
-// Shape of a workgroup: W waves of CB 16-atom column blocks each.  H <= 64:
-// 4 waves x 2 blocks.  H = 128: 1 block per wave, so that a wave's
-// activations and derivatives fit in far fewer registers (4 waves per SIMD
-// for two hidden layers), with 8 waves per workgroup so that each staged
-// weight panel is still shared by 128 atoms.
 template <bool BF16, int H, int ACT, int CB>
 MlpFn pick_L(int L) {
     switch (L) {
@@ -747,11 +793,85 @@ MlpFn pick_act(int act, int H, int L) {
     return act == TMD_ACT_SQUAREPLUS ? pick_H<BF16, TMD_ACT_SQUAREPLUS, CB>(H, L) : pick_H<BF16, TMD_ACT_TANH, CB>(H, L);
 }
 
+template <bool BF16, int H, int ACT>
+MlpFn pick_staged_L(int L) {
+    switch (L) {
+        case 1: return k_mlp_staged<BF16, H, 1, ACT>;
+        case 2: return k_mlp_staged<BF16, H, 2, ACT>;
+        case 3: return k_mlp_staged<BF16, H, 3, ACT>;
+        default:  // (FP32 with 128 units: k_mlp at any size)
+            if constexpr (!BF16 && H == 128) return nullptr;
+            else return k_mlp_staged<BF16, H, 4, ACT>;
+    }
+}
+template <bool BF16, int ACT>
+MlpFn pick_staged_H(int H, int L) {
+    switch (H) {
+        case 32: return pick_staged_L<BF16, 32, ACT>(L);
+        case 64: return pick_staged_L<BF16, 64, ACT>(L);
+        default: return pick_staged_L<BF16, 128, ACT>(L);
+    }
+}
 template <bool BF16>
-MlpFn pick_staged(int act, int L) {
-    if (act == TMD_ACT_SQUAREPLUS)
-        return L == 1 ? k_mlp_staged<BF16, 1, TMD_ACT_SQUAREPLUS> : k_mlp_staged<BF16, 2, TMD_ACT_SQUAREPLUS>;
-    return L == 1 ? k_mlp_staged<BF16, 1, TMD_ACT_TANH> : k_mlp_staged<BF16, 2, TMD_ACT_TANH>;
+MlpFn pick_staged(int act, int H, int L) {
+    return act == TMD_ACT_SQUAREPLUS ? pick_staged_H<BF16, TMD_ACT_SQUAREPLUS>(H, L)
+                                     : pick_staged_H<BF16, TMD_ACT_TANH>(H, L);
+}
+
+// Whether N atoms take the staged form.  k_mlp reads a layer's weights from L2
+// for every 16 or 32 atoms, the staged form for every 128 but with a quarter of
+// the workgroups, and eight times their work each: it is taken beyond so many
+// atoms per CU that its first rounds are filled, later where k_mlp hides the
+// weights behind more products (FP32, three and four layers).  Measured at 32,
+// 96 and 512 features, 864 to 1,000,188 atoms; us, staged against k_mlp, on
+// both sides of the line (256 CUs), 96 features unless noted:
+//   FP32  32 wide       16,384 14.8 / 12.0   24,624 15.4 / 16.3   1,000,188 201 / 348 (one layer)
+//   FP32  64, 1         32,000 21.2 / 20.6   48,668 27.7 / 27.2   1,000,188 280 / 404
+//         64, 2         32,000 27.5 / 25.4   48,668 36.3 / 36.4   1,000,188 406 / 535
+//         64, 3         70,304 61.2 / 56.8  256,000 156 / 177
+//         64, 4        108,000 108 / 98     442,368 352 / 360
+//   FP32 128, 1         16,384 26.0 / 17.5   24,624 26.3 / 26.9   1,000,188 480 / 660
+//        128, 2         48,668 73.1 / 70.0  108,000 140 / 149     1,000,188 1,029 / 1,287
+//        128, 3, 4   1,000,188 1,897 / 1,736 and 2,538 / 2,407
+//   BF16  32 wide       16,384 11.0 / 10.3   24,624 12.5 / 13.0   1,000,188 152 / 263 (one layer)
+//   BF16  64, 1         16,384 12.5 / 10.4   24,624 12.8 / 13.4   1,000,188 164 / 284
+//         64, 3, 4      32,000 18.6 / 17.3   48,668 20.0 / 23.9 (three)
+//   BF16 128, 1, 2      16,384 17.3 / 13.8   24,624 18.7 / 20.4 (two)
+//        128, 3         48,668 36.7 / 31.8  442,368 221 / 230
+//        128, 4         16,384 25.2 / 18.7   24,624 26.4 / 28.4   1,000,188 618 / 747
+// With 128 units and few features (the first layer is cheap, the others
+// dominate) a single round of staged workgroups, 96 to 128 atoms per CU, beats
+// the second round of k_mlp's: 32,000 atoms of 32-128-128-128 in FP32 58.5 / 66.9.
+// Squareplus keeps more registers (its derivative is not formed from its value):
+// with four layers the staged form spills and is left out but for few features.
+// Few features (up to 64) make k_mlp's first layer, which reads them once per
+// wave, no shorter: 32,000 atoms of 18-64-64-64 in BF16 14.9 / 19.3.
+bool take_staged(const tmd_model* m, bool bf16, int64_t N, int64_t cus) {
+    constexpr int64_t never = INT64_MAX / 1024;
+    static const int64_t from[2][2][3][4] = {  // [activation][BF16][units][layers]
+        {{{64, 64, 64, 64}, {128, 128, 384, 768}, {96, 256, never, never}},
+         {{64, 64, 64, 64}, {64, 64, 128, 128}, {64, 64, 1024, 96}}},
+        {{{64, 64, 64, 64}, {128, 384, 768, never}, {96, 256, never, never}},
+         {{64, 64, 64, 64}, {64, 64, 128, never}, {64, 64, 1024, never}}}};
+    const int h = m->H == 32 ? 0 : m->H == 64 ? 1 : 2, L = m->L;
+    const bool sp = m->act == TMD_ACT_SQUAREPLUS;
+    int64_t t = from[sp][bf16][h][L - 1];
+    if (m->Fpad <= 64) {
+        if (h == 1 && (L == 1 || (bf16 && (L == 3 || (L == 4 && !sp && m->F % 4 != 0))))) t = 64;
+        if (h == 1 && sp && !bf16 && (L == 2 || L == 3)) t = L == 2 ? 128 : 384;
+        if (h == 1 && sp && bf16 && L == 4) t = 384;
+        if (h == 2 && !bf16 && (L == 2 || L == 3) && N > 96 * cus && N <= 128 * cus) return true;
+    }
+    return N > t * cus;
+}
+
+// Whether BF16 networks with resident weights take that form (rfn fits in LDS):
+// from one 16-atom tile per wave on.  Squareplus with three layers of 64 runs
+// out of registers there (70,304 atoms of 96-64-64-64: 38 us, staged 31;
+// 256,000: 78 and 71; 1,000,188: 234 and 255).
+bool take_resident(const tmd_model* m, int64_t N, int64_t cus) {
+    const bool slow = m->act == TMD_ACT_SQUAREPLUS && m->H == 64 && m->L == 3 && m->Fpad > 64;
+    return N >= (slow ? 2048 : 256) * cus;
 }
 
 }  // namespace
@@ -774,19 +894,15 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     a.Fpad = m->Fpad;
     a.act = m->act;
     a.L = m->L;
-    // 16 atoms per workgroup up to about one round of workgroups (four on a CU),
-    // 32 from 24,576 on: 23,040 atoms of 512-128-128-128-128 in FP32 took 134
-    // with 16, 146 with 32, 32,000 of 32-64-64 19.8 and 18.0, 98,646 of
-    // 96-128-128 148 and 137 us.  One or two layers of 128: in BF16 the staged
-    // form from 16,384 on (30,000 atoms: 18 against 21 and 23 us with 32 and 16
-    // atoms; 4,096: 15 against 9), in FP32 from 65,536 on (98,642 atoms: 139
-    // against 139, 877,952: 892 against 1,090).
-    const int64_t N = g.off[m->S];
-    const bool wide = N >= 24 * 1024;
+    // 16 atoms per workgroup, 32 beyond 96 per CU: 23,040 atoms of
+    // 512-128-128-128-128 in FP32 took 134 with 16, 146 us with 32, 32,000 of
+    // 32-64-64 19.1 and 18.1, 24,624 of 96-128-128 49 and 47.
+    const int64_t N = g.off[m->S], cus = ctx->num_cus;
+    const bool wide = N > 96 * cus;
     const bool bf16 = prec == TMD_BF16_MLP;
-    MlpFn staged = nullptr;
-    if (N >= (bf16 ? 16 * 1024 : 64 * 1024) && m->H == 128 && m->L <= 2)
-        staged = bf16 ? pick_staged<true>(m->act, m->L) : pick_staged<false>(m->act, m->L);
+    const MlpFn staged = take_staged(m, bf16, N, cus)
+                             ? (bf16 ? pick_staged<true>(m->act, m->H, m->L) : pick_staged<false>(m->act, m->H, m->L))
+                             : nullptr;
     const MlpFn fn = staged ? staged
                      : bf16
                          ? (wide ? pick_act<true, 2>(m->act, m->H, m->L) : pick_act<true, 1>(m->act, m->H, m->L))
@@ -818,7 +934,7 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     if (tiles == 0) return TMD_OK;
     const int rlds = resident_lds_bytes(m->H, m->L, m->Fpad);
     ResidentFn rfn = nullptr;
-    if (prec == TMD_BF16_MLP && rlds <= kMaxResidentLds && N >= (int64_t)16 * 16 * ctx->num_cus)
+    if (prec == TMD_BF16_MLP && rlds <= kMaxResidentLds && take_resident(m, N, cus))
         rfn = m->act == TMD_ACT_SQUAREPLUS ? pick_resident<TMD_ACT_SQUAREPLUS>(m->H, m->L)
                                            : pick_resident<TMD_ACT_TANH>(m->H, m->L);
     if (rfn) {
@@ -828,7 +944,7 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
         rfn<<<(unsigned)ctx->num_cus, 1024, rlds, ctx->stream>>>(a);
     } else {
         ProfScope ps_(ctx, "mlp");
-        fn<<<(unsigned)tiles, staged ? 512 : 256, 0, ctx->stream>>>(a);
+        fn<<<(unsigned)tiles, staged ? 64 * staged_waves(m->H) : 256, 0, ctx->stream>>>(a);
     }
     TMD_HIP(ctx, hipGetLastError());
     return TMD_OK;

@@ -324,3 +324,55 @@ def test_nan_position(ctx, K, M, table):
     views[0][0][7, 2] = float("nan")
     tmd.energy_forces_async(ctx, model, *views[0], lists[0], one, forces[0], None)
     assert np.isnan(one.cpu().numpy()).all()
+
+
+# the network's forms agree bit for bit: a system of a batch that is large enough
+# for the forms with weights in LDS against the same system alone (16 atoms per
+# workgroup); 65 to 1,030 copies of 256 atoms lie on the far sides of the rules
+# between the forms for 256 compute units
+@pytest.mark.parametrize("K,M", [(12, 3), (5, 2)])  # 96 features; 30, no multiple of four
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_network_forms_agree(ctx, K, M, act, bf16):
+    import torch
+    from paper_2310_08439_amd import tmd
+    s = inputs.make_system("fcc", 3.61, (4, 4, 4), 0.05, 2, seed=7)
+    x = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+    sp = torch.tensor(s.species, dtype=torch.int32, device="cuda")
+    nl = tmd.NeighborList(ctx, s.n, 2, tmd.default_capacity(s.n, s.box, 5.0, 1))
+    tmd.build_neighbors(ctx, x, sp, s.box, 5.0, 0.0, nl)
+    most = 1030
+    forces = torch.empty((most, s.n, 3), dtype=torch.float32, device="cuda")
+    totals = torch.empty((most, 7), dtype=torch.float64, device="cuda")
+    for hidden in ([32], [20, 32], [32] * 3, [32] * 4, [64], [64, 50], [64] * 3, [64] * 4, [128], [128, 100],
+                   [128] * 3, [128] * 4):
+        spec = inputs.make_model(2, K, M, hidden, 5.0, seed=K, activation=act)
+        model = tmd.Model(ctx, spec, tmd.BF16_MLP if bf16 else tmd.FP32)
+        print(f"[case] network {hidden}, K = {K}, activation {act}, bf16 {bf16}", flush=True)
+        tmd.energy_forces_batch(ctx, model, [(x, sp, s.box)], [nl], totals[:1], [forces[0]])
+        t1, f1 = totals[0].clone(), forces[0].clone()
+        for count in (65, 97, 130, 390, most):
+            totals.zero_()
+            forces.zero_()
+            tmd.energy_forces_batch(ctx, model, [(x, sp, s.box)] * count, [nl] * count, totals[:count],
+                                    [forces[q] for q in range(count)])
+            assert torch.equal(totals[:count], t1.expand(count, 7))
+            assert torch.equal(forces[:count], f1.expand(count, s.n, 3))
+        model.close()
+
+
+# 70,304 atoms in FP32 against the oracle: weights staged in LDS, or read from L2
+# where squareplus keeps too many registers
+@pytest.mark.parametrize("hidden", [[32] * 2, [64], [64] * 4, [128], [128, 128]])
+@pytest.mark.parametrize("act", [0, 1])
+def test_network_staged_fp32(ctx, hidden, act):
+    import torch
+    from paper_2310_08439_amd import tmd
+    s = _thin(26, 26, 26, 2, 6)  # 70,304 atoms
+    spec = inputs.make_model(2, 12, 3, hidden, 5.0, seed=98, activation=act)
+    print(f"[case] network {hidden}, activation {act}, {s.n} atoms", flush=True)
+    pos = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+    ev = tmd.Evaluator(spec, s.n, s.box, precision=tmd.FP32, ctx=ctx)
+    _, Ea, F, _ = ev.energy_forces(pos, torch.tensor(s.species, dtype=torch.int32, device="cuda"), s.box)
+    parity.check_sampled(Ea.cpu().numpy().astype(np.float64), F.cpu().numpy().astype(np.float64), s, spec, False,
+                         n_sample=300)
