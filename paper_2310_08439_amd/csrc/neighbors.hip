@@ -169,7 +169,7 @@ __global__ void k_scan_add(int64_t ncells, const int32_t* __restrict__ tile_off,
 // in place = first slot of the cell's species-s atoms in the species grouping.
 // It replaces six launches of 2 to 4 us each (three for the cell starts, three
 // for the grouping), which larger grids still take because one workgroup would
-// then be slower.
+// then be slower (of several species the latter earlier: launch_build_neighbors).
 constexpr int kScanCells = 16384;
 __global__ void __launch_bounds__(1024) k_scan_cells(int ncells, int S, const int32_t* __restrict__ count,
                                                      int32_t* __restrict__ start, int32_t* __restrict__ cellsp,
@@ -353,6 +353,10 @@ __global__ void __launch_bounds__(256) k_sort_gather(int64_t ncells, const int32
             const int32_t vj = j0 + lane < m ? order[lo + j0 + lane] : INT32_MAX;
             const int32_t sj = cellsp && j0 + lane < m ? species[vj] : -1;
             const int nj = min(kSortLanes, m - j0);
+            if (!cellsp) {  // the same for all
+                for (int t = 0; t < nj; ++t) r += __shfl(vj, t, kSortLanes) < v ? 1 : 0;
+                continue;
+            }
             for (int t = 0; t < nj; ++t) {
                 const bool less = __shfl(vj, t, kSortLanes) < v;
                 const bool same = __shfl(sj, t, kSortLanes) == sv;  // (outside any branch: every lane is read)
@@ -547,13 +551,15 @@ struct FillArgs {
 
 // What the host needs after a build goes straight to pinned host memory, so
 // that no copy follows the fill: its first workgroup stores what the earlier
-// launches left in flags (errors of the input in [0], counts from [4] on), and
-// a fill that fails stores a mark in host[3], upon which the host reads flags
-// itself.
+// launches left in flags (errors of the input in [0], counts from [4] on), a
+// fill that fails stores a mark in host[3], upon which the host reads flags
+// itself, and one that meets a crowded cell a mark in host[2].
 __device__ __forceinline__ void publish_flags(const FillArgs& a) {
-    if (blockIdx.x == 0 && threadIdx.x < 16 && threadIdx.x != 3) a.host[threadIdx.x] = a.flags[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x < 16 && threadIdx.x != 2 && threadIdx.x != 3)
+        a.host[threadIdx.x] = a.flags[threadIdx.x];
 }
 __device__ __forceinline__ void fill_failed(const FillArgs& a) { a.host[3] = 1; }
+__device__ __forceinline__ void fill_crowded(const FillArgs& a) { a.host[2] = 1; }
 
 // Systems of at most this many atoms have every workgroup of k_fill stage all
 // positions in LDS (32 KB): their cells are few and crowded, so each thread
@@ -693,10 +699,7 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells, 
     int a0 = __builtin_amdgcn_readfirstlane(a.cellstart[cell]);
     int natoms = __builtin_amdgcn_readfirstlane(a.cellstart[cell + 1]) - a0;
     if (natoms > kMaxCellAtoms) {  // the host reruns the build with k_fill
-        if (lane == 0) {
-            atomicOr(&a.flags[2], 1);
-            fill_failed(a);
-        }
+        if (lane == 0) fill_crowded(a);
         return;
     }
     if (split > 1) {  // this wave's share of the cell's atoms
@@ -736,10 +739,7 @@ __global__ void __launch_bounds__(256) k_fill_cells(FillArgs a, int64_t ncells, 
     const int total = __shfl(pre, 63);
     pre -= count;  // exclusive
     if (total > kMaxCandidates) {  // the host reruns the build with k_fill
-        if (lane == 0) {
-            atomicOr(&a.flags[2], 1);
-            fill_failed(a);
-        }
+        if (lane == 0) fill_crowded(a);
         return;
     }
     // candidate -> stencil cell table: stencil cell s owns candidates [pre_s, pre_s + count_s)
@@ -998,10 +998,15 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
     int32_t* order = (int32_t*)ctx->ws.get("nb.order", sizeof(int32_t) * n, &e);
     // the flags, the cell counts and (small grids of several species) the
     // species counts of the cells, cleared together; the latter where the work
-    // order's block counts go afterwards, which has room for max_cells of them
-    // (a grid of more, nearly as many cells as atoms, groups the species by
-    // launches of their own)
-    const bool small_grid = ncells <= kScanCells, grouped = small_grid && (nl->S == 1 || nl->S * ncells <= max_cells);
+    // order's block counts go afterwards, which has room for max_cells of them.
+    // A grid of more (nearly as many cells as atoms) groups the species by
+    // launches of their own; so does one that one workgroup would scan for too
+    // long (12,384 cells of two species 27 us against 33 in launches, 11,500 of
+    // three 35 against 31), and one of crowded cells, whose sort is quadratic
+    // (500 atoms a cell: 5,290 us a build, 5,630 with the grouping).
+    const bool small_grid = ncells <= kScanCells;
+    const bool grouped = small_grid && (nl->S == 1 || (nl->S * ncells <= max_cells && n <= 64 * ncells &&
+                                                       (nl->S + 1) * ncells <= 40000));
     const int64_t nsp = grouped && nl->S > 1 ? nl->S * ncells : 0;
     int32_t* flags =
         (int32_t*)ctx->ws.get("nb.flags", sizeof(int32_t) * (size_t)(64 + ncells + 1 + std::max(nsp, ncells)), &e);
@@ -1129,8 +1134,7 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
         return TMD_OK;
     };
     tmd_status rst = TMD_OK;
-    if (ctx->h_flags[3] && (rst = read_flags()) != TMD_OK) return rst;
-    if (by_cell && (ctx->h_flags[2] & 1)) {
+    if (by_cell && ctx->h_flags[2]) {
         // a cell holds more atoms than one wave can track: per-atom fill instead
         {
             ProfScope ps_(ctx, "nb_fill");
@@ -1141,6 +1145,8 @@ tmd_status launch_build_neighbors(tmd_context* ctx, const tmd_system_view* sys, 
         }
         TMD_HIP(ctx, hipGetLastError());
         if ((rst = read_flags()) != TMD_OK) return rst;
+    } else if (ctx->h_flags[3] && (rst = read_flags()) != TMD_OK) {
+        return rst;
     }
     const int32_t errs = ctx->h_flags[0];
     if (errs & kErrSpecies) return fail(ctx, TMD_ERR_INVALID_ARGUMENT, "species index outside [0, n_species)");

@@ -376,3 +376,28 @@ def test_network_staged_fp32(ctx, hidden, act):
     _, Ea, F, _ = ev.energy_forces(pos, torch.tensor(s.species, dtype=torch.int32, device="cuda"), s.box)
     parity.check_sampled(Ea.cpu().numpy().astype(np.float64), F.cpu().numpy().astype(np.float64), s, spec, False,
                          n_sample=300)
+
+
+# species grouped while the cells are sorted, or by launches of their own: cells of
+# up to 64 atoms on average and more, grids of few and many counts; every K runs
+# the network on the grouping, a wrong one shows in the energies
+@pytest.mark.parametrize("n,edge,rcut", [(512, 10.2, 5.0), (513, 10.2, 5.0), (800, 10.2, 5.0), (3000, 66.0, 3.0),
+                                         (4000, 70.0, 3.0), (13000, 75.1, 3.0)])
+@pytest.mark.parametrize("n_species", [1, 3])
+def test_species_grouping(ctx, n, edge, rcut, n_species):
+    import oracle
+    rng = np.random.default_rng(n)
+    m = int(np.ceil(n ** (1 / 3)))
+    grid = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    pos = (grid[rng.permutation(m ** 3)[:n]] + 0.5 + rng.uniform(-0.2, 0.2, size=(n, 3))) * (edge / m)
+    s = inputs.System(pos=pos, species=rng.integers(0, n_species, n).astype(np.int32), box=np.full(3, edge),
+                      masses=np.ones(n_species))
+    spec = inputs.make_model(n_species, 8, 2, [32], rcut, seed=10, r_min=0.5)
+    print(f"[case] {n} atoms, edge {edge}, {n_species} species", flush=True)
+    E, Ea, F, W = _evaluate(ctx, spec, s)
+    Er, Ear, Fr, Wr = oracle.energy_forces(spec, s.pos, s.species, s.box)
+    # the bars scale with the neighbour count relative to the ~50 of the
+    # configurations they were set for, and with the largest force
+    scale = max(1.0, n * 4.19 * rcut ** 3 / edge ** 3 / 50.0) * max(1.0, float(np.abs(Fr).max()))
+    assert np.abs(Ea - Ear).max() <= parity.E_FP32 * scale
+    assert np.abs(F - Fr).max() <= parity.FMAX_FP32 * scale
