@@ -401,3 +401,82 @@ def test_species_grouping(ctx, n, edge, rcut, n_species):
     scale = max(1.0, n * 4.19 * rcut ** 3 / edge ** 3 / 50.0) * max(1.0, float(np.abs(Fr).max()))
     assert np.abs(Ea - Ear).max() <= parity.E_FP32 * scale
     assert np.abs(F - Fr).max() <= parity.FMAX_FP32 * scale
+
+
+# several sub-tiles of atoms per workgroup of the second-order pass (and of the
+# vector kernel, four layers), with a remainder on each side of the species
+# boundary, and few enough for one each; both activations.  A batch repeated has
+# the loss and gradient of the batch itself (means over systems and atoms).
+# Bars: FP32 sums of a thousand terms in a row round by at most 1e3 * 2^-24 = 6e-5
+# of their magnitudes.
+@pytest.mark.parametrize("repeat", [1, 171])
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("K,M,hidden", [(8, 3, [128] * 3), (6, 2, [64, 50]), (4, 3, [32]), (8, 3, [32] * 4)])
+def test_second_order_pass_sub_tiles(ctx, K, M, hidden, act, repeat):
+    import oracle
+    import torch
+    from paper_2310_08439_amd import tmd
+    print(f"[case] gradient, K = {K}, hidden {hidden}, activation {act}, repeated {repeat}", flush=True)
+    b = inputs.train_batch(n_cells=3, seed=51, cells=(("fcc", 3.61, (3, 3, 3)), ("bcc", 3.16, (4, 4, 4)),
+                                                      ("hcp", 2.553, (4, 3, 3))))
+    sp = (np.random.default_rng(8).random(b.n) < 0.3).astype(np.int32)
+    teacher = inputs.make_model(2, K, M, hidden, 5.0, seed=1031, activation=act)
+    student = inputs.make_model(2, K, M, hidden, 5.0, seed=2031, activation=act)
+    B = b.n_systems
+    E_l, F_l = np.zeros(B), np.zeros((b.n, 3))
+    for q in range(B):
+        a0, a1 = b.sys_off[q], b.sys_off[q + 1]
+        E_l[q], _, F_l[a0:a1], _ = oracle.energy_forces(teacher, b.pos[a0:a1], sp[a0:a1], b.boxes[q])
+    F_l = F_l.astype(np.float32)
+    off = np.concatenate([[0]] + [b.sys_off[1:] + k * b.n for k in range(repeat)]).astype(np.int64)
+    model = tmd.Model(ctx, student)
+    bt = tmd.Batch(ctx, model, off, torch.tensor(np.tile(b.pos, (repeat, 1)), dtype=torch.float64, device="cuda"),
+                   torch.tensor(np.tile(sp, repeat), device="cuda"), np.tile(b.boxes, (repeat, 1)),
+                   np.tile(E_l, repeat), torch.tensor(np.tile(F_l, (repeat, 1)), device="cuda"))
+    grad = torch.empty(model.n_params, dtype=torch.float32, device="cuda")
+    loss = tmd.train_step(ctx, model, bt, lam=0.1, lr=0.0, grad=grad)[0]
+    lr_, _, _, gr = oracle.train_loss_grad(student, b.sys_off, b.pos, sp, b.boxes, E_l, F_l, 0.1)
+    g = grad.cpu().numpy().astype(np.float64)
+    print(f"  loss {loss:.8e} vs {lr_:.8e}, gradient off by {np.linalg.norm(g - gr) / np.linalg.norm(gr):.2e}", flush=True)
+    assert abs(loss - lr_) <= 1e-4 * lr_
+    assert np.abs(g - gr).max() <= 6e-5 * np.abs(gr).max()
+    assert np.linalg.norm(g - gr) <= 6e-5 * np.linalg.norm(gr)
+    bt.close()
+    model.close()
+
+
+# tmd_energy_forces_noalloc when its scratch leaves no room for the adjoint's
+# finest split (a virial partial per 32 atoms) but for one per cell of the list:
+# 64 atoms per workgroup, against the allocating call
+def test_noalloc_coarse_split(ctx):
+    import torch
+    from paper_2310_08439_amd import tmd
+    spec = inputs.make_model(2, 8, 3, [16], 8.0, seed=106)
+    model = tmd.Model(ctx, spec, tmd.FP32)
+    s = inputs.make_system("fcc", 3.61, (2, 60, 90), 0.05, 2, seed=1)
+    cells = 27 * 40  # of edge 8 A, one across the box's 7.2 A: no work order
+    # bytes of n atoms in the scratch, in 256-byte pieces: G and dG (64 features),
+    # energies, forces, P and totals, then the virial partials
+    up = lambda v: (v + 255) // 256 * 256
+    fixed = lambda n: 2 * up(4 * n * 64) + up(4 * n) + up(24 * n) + up(4 * n * 2 * 8 * 16) + 256 * 14 * 8
+    scratch = tmd.load_library().tmd_noalloc_scratch_bytes()
+    n = next(n for n in range(s.n, 0, -1) if fixed(n) + up(96 * cells) <= scratch)
+    assert fixed(n) + up(96 * ((n + 31) // 32)) > scratch
+    keep = np.sort(np.random.default_rng(1).permutation(s.n)[:n])
+    s = inputs.System(pos=s.pos[keep], species=s.species[keep], box=s.box, masses=s.masses)
+    print(f"[case] {n} atoms, box {s.box}", flush=True)
+    x = torch.tensor(s.pos, dtype=torch.float64, device="cuda")
+    sp = torch.tensor(s.species, dtype=torch.int32, device="cuda")
+    nl = tmd.NeighborList(ctx, s.n, 2, tmd.default_capacity(s.n, s.box, 8.0, 1))
+    tmd.build_neighbors(ctx, x, sp, s.box, 8.0, 0.0, nl)
+    out = []
+    for fn in (tmd.energy_forces_async, tmd.energy_forces_noalloc):
+        t = torch.zeros(7, dtype=torch.float64, device="cuda")
+        F = torch.zeros((s.n, 3), dtype=torch.float32, device="cuda")
+        Ea = torch.zeros(s.n, dtype=torch.float32, device="cuda")
+        fn(ctx, model, x, sp, s.box, nl, t, F, Ea)
+        out.append((t.cpu().numpy(), F, Ea))
+    assert out[0][0][0] == out[1][0][0]
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
+    # FP64 sums of the atoms' virials in another order
+    assert np.abs(out[0][0][1:] - out[1][0][1:]).max() <= 1e-12 * np.abs(out[0][0][1:]).max()
