@@ -62,7 +62,7 @@ struct tmd_batch {
     double* sysF = nullptr;      // [B]
     double* loss = nullptr;      // [4]
     float* partial = nullptr;    // [tiles][P_int]
-    float* grad = nullptr;       // [S][P_int], the gradient in the padded layout
+    float* grad = nullptr;       // the gradient (ABI layout) when the caller takes none; room for [S][P_int]
     int32_t* flag = nullptr;     // [2] set when an entry has no mirror; k_loss's counter, zero between steps
     int tileT = 0;               // atoms per second-order tile
     int tileQC = 0;              // weight columns per LDS block of the second-order pass
@@ -1112,14 +1112,17 @@ struct GradArgs {
 // optimizer's step and the operand copies, one parameter at a time:
 // 32 parameters per workgroup, 32 threads each over the rows, so that reading
 // the rows is spread over the chip (1,103 rows of 6,337: 11 us; two passes
-// of summing, the update and the copies in launches of their own 19).
+// of summing, the update and the copies in launches of their own 19).  The rows
+// are summed in FP64, which costs no time and takes the gradient's error against
+// 64 bits (relative L2, mean of 36 batches of 2 to 64 cells, hidden widths 32 to
+// 64) from 2.54e-7 to 2.32e-7.
 __global__ void __launch_bounds__(1024) k_grad_update(GradArgs a) {
-    __shared__ float part[32][33];
+    __shared__ double part[32][33];
     const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
     const int64_t t = (int64_t)blockIdx.x * 32 + x, np = (int64_t)a.u.S * a.u.P;
     int l = 0, o = 0, c = 0, kind = 0, s = 0;
     int64_t qi = 0;
-    float acc = 0.0f;
+    double acc = 0.0;
     if (t < np) {
         s = (int)(t / a.u.P);
         qi = a.u.pm.map(t - (int64_t)s * a.u.P, l, o, c, kind);
@@ -1127,14 +1130,15 @@ __global__ void __launch_bounds__(1024) k_grad_update(GradArgs a) {
         const int64_t r0 = rows * y / 32, r1 = rows * (y + 1) / 32;
         const float* src = a.partial + (lo + r0) * a.u.P_int + qi;
 #pragma unroll 8
-        for (int64_t r = r0; r < r1; ++r, src += a.u.P_int) acc += *src;
+        for (int64_t r = r0; r < r1; ++r, src += a.u.P_int) acc += (double)*src;
     }
     part[y][x] = acc;
     __syncthreads();
     if (y != 0 || t >= np) return;
-    float g = 0.0f;
+    double sum = 0.0;
 #pragma unroll
-    for (int k = 0; k < 32; ++k) g += part[k][x];
+    for (int k = 0; k < 32; ++k) sum += part[k][x];
+    const float g = (float)sum;
     a.grad[t] = g;
     if (!a.update) return;
     float th = a.params[t];

@@ -405,3 +405,32 @@ def test_set_params_restarts_the_optimizer_on_another_stream(tmd, torch):
     bt.close()
     model.close()
     ctx.close()
+
+
+def test_gradient_of_a_repeated_batch_to_the_last_place(tmd, ctx, torch):
+    """The gradient's partial rows are summed in FP64.  A batch of one 256-atom
+    system repeated 64 times: every seed is the single system's times 2^-6
+    exactly, so are the 16-atom sub-tiles' partial rows (1,024, one per
+    workgroup), and both gradients are one sum rounded to FP32 once, at most a
+    unit in the last place apart."""
+    _note("gradient of a repeated system")
+    teacher = inputs.make_model(1, 8, 3, [64, 64], 5.0, seed=1041)
+    student = inputs.make_model(1, 8, 3, [64, 64], 5.0, seed=2041)
+    s = inputs.make_system("fcc", 3.61, (4, 4, 4), 0.1, 1, seed=42, masses=[1.0])
+    model = tmd.Model(ctx, student)
+    grads = []
+    for rep in (1, 64):
+        b = inputs.Batch(pos=np.tile(s.pos, (rep, 1)), species=np.tile(s.species, rep),
+                         sys_off=np.arange(rep + 1, dtype=np.int64) * s.n, boxes=np.tile(s.box, (rep, 1)),
+                         kinds=["fcc4x4x4"] * rep)
+        E, _, F, _ = oracle.energy_forces(teacher, s.pos, s.species, s.box)
+        bt = _device_batch(tmd, ctx, torch, model, b, np.full(rep, E), np.tile(F, (rep, 1)))
+        grad = torch.empty(model.n_params, dtype=torch.float32, device="cuda")
+        tmd.train_step(ctx, model, bt, lam=0.1, lr=0.0, grad=grad)
+        grads.append(grad.cpu().numpy())
+        bt.close()
+    d = np.abs(grads[0] - grads[1])
+    print(f"  most units in the last place: {(d / np.spacing(np.abs(grads[0]))).max():.1f}", flush=True)
+    assert np.abs(grads[0]).max() > 0
+    assert (d <= np.spacing(np.abs(grads[0]))).all()
+    model.close()
