@@ -242,16 +242,14 @@ __device__ __forceinline__ void load_P(const PtArgs& a, int64_t i, int b, int ch
 }
 
 // Per-entry g = dE_i/dD_c (the adjoint chain of Sec. III.A); chunk lanes of
-// an atom are adjacent and combine their partial sums with shuffles, and
-// kEntryLanes groups of them take the row's entries in turn (17,648 atoms, 60
-// entries each: 30 us; one group 46, with one wave on a SIMD).
-constexpr int kEntryLanes = 4, kTangentLanes = 8;
-template <int KC, int M>
+// an atom are adjacent and combine their partial sums with shuffles, and E
+// groups of them take the row's entries in turn (entry_lanes).
+template <int KC, int M, int E>
 __global__ void __launch_bounds__(256) k_pt_adjoint(PtArgs a) {
     constexpr int D = Moments<M>::D;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = (t >> a.nch_log2) / kEntryLanes;
-    const int el = (int)(t >> a.nch_log2) % kEntryLanes;
+    const int64_t i = (t >> a.nch_log2) / E;
+    const int el = (int)(t >> a.nch_log2) % E;
     const int nch = 1 << a.nch_log2;
     const int ch = (int)(t & (nch - 1));
     if (i >= a.N) return;
@@ -284,7 +282,7 @@ __global__ void __launch_bounds__(256) k_pt_adjoint(PtArgs a) {
         }
         const int64_t row = (i * a.S + b) * a.cap;
         const int nb = a.cnt[i * a.S + b];
-        for (int c = el; c < nb; c += kEntryLanes) {
+        for (int c = el; c < nb; c += E) {
             PairGeo p;
             float gx = 0.0f, gy = 0.0f, gz = 0.0f;
             if (pair_geo(a.tab[row + c], a.rc2, p)) {
@@ -449,12 +447,11 @@ __device__ __forceinline__ float sum8(float v) {
 }
 
 // Descriptor tangent along r: forward mode through pair geometry, radial
-// functions, monomials, P and S.  Eight lanes per (atom, chunk) take the
-// row's entries in turn (17,648 atoms, 60 entries each: 28 us; one lane and
-// half the chunk 40: the geometry repeated per chunk, one wave on a SIMD).
-template <int KC, int M>
+// functions, monomials, P and S.  E lanes per (atom, chunk), one or eight, take
+// the row's entries in turn (tangent_lanes).
+template <int KC, int M, int E>
 __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
-    constexpr int E = kTangentLanes;
+    static_assert(E == 1 || E == 8, "sum8");
     constexpr int D = Moments<M>::D;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int el = (int)(t % E);
@@ -514,7 +511,8 @@ __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk)
 #pragma unroll
-            for (int d = 0; d < D; ++d) Pt[kk][d] = sum8(Pt[kk][d]);
+            for (int d = 0; d < D; ++d)
+                if constexpr (E == 8) Pt[kk][d] = sum8(Pt[kk][d]);
         float P[KC][D];
         load_P<KC, D>(a, i, b, ch, P);
 #pragma unroll
@@ -528,7 +526,7 @@ __global__ void __launch_bounds__(256) k_pt_tangent(PtArgs a) {
                 // m = 0: G = |P_k0|, so its tangent is sign(P_k0) times that of P_k0
                 float wv = st;
                 if (m == 0) wv = P[kk][0] > 0.0f ? Pt[kk][0] : (P[kk][0] < 0.0f ? -Pt[kk][0] : 0.0f);
-                if (el == m) a.w[i * a.F + (b * a.K + k) * (M + 1) + m] = wv;
+                if (E == 1 || el == m) a.w[i * a.F + (b * a.K + k) * (M + 1) + m] = wv;
             }
         }
     }
@@ -1157,31 +1155,52 @@ __global__ void __launch_bounds__(1024) k_grad_update(GradArgs a) {
 
 using PtFn = void (*)(PtArgs);
 
-#define TMD_PICK(NAME, KERNEL)                                    \
-    PtFn NAME(int kc, int M) {                                    \
-        switch (kc * 10 + M) {                                    \
-            case 20: return KERNEL<2, 0>;                         \
-            case 21: return KERNEL<2, 1>;                         \
-            case 22: return KERNEL<2, 2>;                         \
-            case 23: return KERNEL<2, 3>;                         \
-            case 40: return KERNEL<4, 0>;                         \
-            case 41: return KERNEL<4, 1>;                         \
-            case 42: return KERNEL<4, 2>;                         \
-            case 43: return KERNEL<4, 3>;                         \
-            case 60: return KERNEL<6, 0>;                         \
-            case 61: return KERNEL<6, 1>;                         \
-            case 62: return KERNEL<6, 2>;                         \
-            case 63: return KERNEL<6, 3>;                         \
-            case 80: return KERNEL<8, 0>;                         \
-            case 81: return KERNEL<8, 1>;                         \
-            case 82: return KERNEL<8, 2>;                         \
-            default: return KERNEL<8, 3>;                         \
-        }                                                         \
+template <template <int, int> class Kernel>
+PtFn pick_pt(int kc, int M) {
+    switch (kc * 10 + M) {
+        case 20: return Kernel<2, 0>::fn;
+        case 21: return Kernel<2, 1>::fn;
+        case 22: return Kernel<2, 2>::fn;
+        case 23: return Kernel<2, 3>::fn;
+        case 40: return Kernel<4, 0>::fn;
+        case 41: return Kernel<4, 1>::fn;
+        case 42: return Kernel<4, 2>::fn;
+        case 43: return Kernel<4, 3>::fn;
+        case 60: return Kernel<6, 0>::fn;
+        case 61: return Kernel<6, 1>::fn;
+        case 62: return Kernel<6, 2>::fn;
+        case 63: return Kernel<6, 3>::fn;
+        case 80: return Kernel<8, 0>::fn;
+        case 81: return Kernel<8, 1>::fn;
+        case 82: return Kernel<8, 2>::fn;
+        default: return Kernel<8, 3>::fn;
     }
-TMD_PICK(pick_forward, k_pt_forward)
-TMD_PICK(pick_adjoint, k_pt_adjoint)
-TMD_PICK(pick_tangent, k_pt_tangent)
-#undef TMD_PICK
+}
+template <int KC, int M>
+struct Forward {
+    static constexpr PtFn fn = k_pt_forward<KC, M>;
+};
+template <int KC, int M>
+struct Adjoint1 {
+    static constexpr PtFn fn = k_pt_adjoint<KC, M, 1>;
+};
+template <int KC, int M>
+struct Adjoint4 {
+    static constexpr PtFn fn = k_pt_adjoint<KC, M, 4>;
+};
+template <int KC, int M>
+struct Tangent1 {
+    static constexpr PtFn fn = k_pt_tangent<KC, M, 1>;
+};
+template <int KC, int M>
+constexpr PtFn tangent8() {  // chunks of two or six (tangent_kc)
+    if constexpr (KC == 2 || KC == 6) return k_pt_tangent<KC, M, 8>;
+    else return nullptr;
+}
+template <int KC, int M>
+struct Tangent8 {
+    static constexpr PtFn fn = tangent8<KC, M>();
+};
 
 unsigned blocks_for(int64_t threads) { return (unsigned)((threads + kBlock - 1) / kBlock); }
 
@@ -1193,10 +1212,42 @@ int batch_kc(int K, int kc, int64_t N) {
     return kc;
 }
 
-// The tangent's chunk: two radial functions (146 registers, three waves on a
-// SIMD) where the model's chunk divides into them; four (276 registers, one
-// wave) took 44 us instead of 29 for 17,648 atoms.
+// Floats of P per atom and radial function, and in the batch: the measure of
+// work in the rules below.
+int moments(const tmd_batch* b) { return b->S * ((b->M + 1) * (b->M + 2) * (b->M + 3) / 6); }
+int64_t moment_floats(const tmd_batch* b) { return b->N * b->K * moments(b); }
+
+// Lanes that share an atom's row in the adjoint: four keep a smaller batch's
+// chip busy and hold a quarter of the dependent chain each, one reads every
+// moment once.  In us with four and with one: 10^4 moments 14 and 41; K = 8 at
+// 17086 atoms (2.7 M) 28 and 47; K = 64 at 4874 (6.2 M) 80 and 83; K = 32 at
+// 17086 (10.9 M) 122 and 96.  An atom of few chunks has few lanes otherwise and
+// gains for longer: four chunks at 21.9 M 127 and 140, at 43.7 M 389 and 320.
+// One of 64 chunks fills its wave: 109 and 100 at 6.2 M.
+int entry_lanes(const tmd_batch* b) {
+    const int nch = b->K / b->kc;
+    const int64_t most = nch <= 4 ? 30000000 : nch <= 32 ? 7000000 : 4000000;
+    return moment_floats(b) <= most ? 4 : 1;
+}
+
+// The same for the tangent, eight lanes or one; eight go with chunks of two
+// radial functions (146 registers and their partial sums in eight lanes, where
+// four took 247), three more chunk lanes than one lane's, and sum every moment's
+// tangent over the eight.  In us with eight and with one: 10^4 moments 10 and
+// 31; K = 8 at 17086 atoms (2.7 M) 28 and 34; K = 4 at 34172 (2.7 M) 30 and 38;
+// K = 16 at 17086 (5.5 M) 52 and 47; K = 32 at 17086 (10.9 M) 101 and 80.  At
+// M = 0 the sums weigh most: 19 and 25 at 0.3 M, 52 and 38 at 1.1 M.  Few atoms
+// of many moments leave the chip idle with one (eight species, K = 32, 1326
+// atoms, 6.8 M: 52 and 71), and 64 chunks of one lane, or 32 of long ones, read
+// a row from as many lanes (K = 128 at 4874 atoms, 12.5 M: 115 and 210; four
+// species, K = 64 at 9076, 46 M: 318 and 388).
 int tangent_kc(int kc) { return kc % 4 == 0 ? 2 : kc; }
+int tangent_lanes(const tmd_batch* b) {
+    const int nch = b->K / b->kc;
+    const int64_t x = moment_floats(b);
+    const bool many = x <= (b->M ? 5000000 : 700000) || (b->M && x <= 7000000 && b->N * nch <= 131072);
+    return many || nch >= 64 || (nch == 32 && moments(b) >= 20) ? 8 : 1;
+}
 
 PtArgs pt_args(const tmd_batch* bt) {
     PtArgs a{};
@@ -1443,7 +1494,7 @@ tmd_status tmd_batch_create(tmd_context* ctx, const tmd_model* m, int32_t n_syst
         a.eta = m->eta;
         a.G = b->G;
         a.P = b->P;
-        pick_forward(b->kc, b->M)<<<blocks_for(N * (b->K / b->kc)), kBlock, 0, ctx->stream>>>(a);
+        pick_pt<Forward>(b->kc, b->M)<<<blocks_for(N * (b->K / b->kc)), kBlock, 0, ctx->stream>>>(a);
         e = hipGetLastError();
         int32_t flag = 0;
         if (e == hipSuccess) e = hipMemcpyAsync(&flag, b->flag, 4, hipMemcpyDeviceToHost, ctx->stream);
@@ -1528,7 +1579,9 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     a.w = b->w;
     {
         ProfScope ps_(ctx, "train_adjoint");
-        pick_adjoint(b->kc, b->M)<<<blocks_for(N * (b->K / b->kc) * kEntryLanes), kBlock, 0, ctx->stream>>>(a);
+        const int E = entry_lanes(b);
+        (E == 1 ? pick_pt<Adjoint1>(b->kc, b->M) : pick_pt<Adjoint4>(b->kc, b->M))
+            <<<blocks_for(N * (b->K / b->kc) * E), kBlock, 0, ctx->stream>>>(a);
     }
     {
         ProfScope ps_(ctx, "train_forces");
@@ -1545,10 +1598,11 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     // 3. descriptor tangent along r
     {
         ProfScope ps_(ctx, "train_tangent");
-        const int kc = tangent_kc(m->kc);
+        const int E = tangent_lanes(b), kc = E == 1 ? b->kc : tangent_kc(m->kc);
         a.nch_log2 = 0;
         while ((kc << a.nch_log2) < m->K) ++a.nch_log2;
-        pick_tangent(kc, b->M)<<<blocks_for(N * (b->K / kc) * kTangentLanes), kBlock, 0, ctx->stream>>>(a);
+        (E == 1 ? pick_pt<Tangent1>(kc, b->M) : pick_pt<Tangent8>(kc, b->M))
+            <<<blocks_for(N * (b->K / kc) * E), kBlock, 0, ctx->stream>>>(a);
     }
     // 4. second-order network pass and gradient
     MlpTrainArgs t{};

@@ -434,3 +434,42 @@ def test_gradient_of_a_repeated_batch_to_the_last_place(tmd, ctx, torch):
     assert np.abs(grads[0]).max() > 0
     assert (d <= np.spacing(np.abs(grads[0]))).all()
     model.close()
+
+
+@pytest.mark.parametrize("S,K,M,rep", [
+    (1, 16, 3, 140), (1, 16, 3, 150),  # the tangent's line, 4.8 and 5.2 M moments
+    (1, 32, 3, 120),  # one lane in the adjoint and in the tangent, chunks of two
+    (1, 6, 3, 400), (1, 12, 3, 220), (2, 4, 1, 1460),  # one lane in the tangent: whole rows, six and four functions
+    (1, 16, 0, 420),  # M = 0 past its own line
+    (1, 128, 3, 21)])  # 64 chunks: one lane in the adjoint, eight in the tangent
+def test_train_lanes_of_large_batches(tmd, ctx, torch, S, K, M, rep):
+    """A 108-atom system repeated, past the sizes where an atom's row has one
+    lane per chunk: every copy's forces and descriptor tangents, and the
+    gradient, are the single system's by the oracle, within the bars above."""
+    _note(f"training lanes: S={S} K={K} M={M}, {rep} copies")
+    teacher = inputs.make_model(S, K, M, [32], 5.0, seed=1051)
+    student = inputs.make_model(S, K, M, [32], 5.0, seed=2051)
+    s = inputs.make_system("fcc", 3.61, (3, 3, 3), 0.1, S, seed=43, masses=[1.0] * S)
+    E, _, F, _ = oracle.energy_forces(teacher, s.pos, s.species, s.box)
+    b = inputs.Batch(pos=np.tile(s.pos, (rep, 1)), species=np.tile(s.species, rep),
+                     sys_off=np.arange(rep + 1, dtype=np.int64) * s.n, boxes=np.tile(s.box, (rep, 1)),
+                     kinds=["fcc3x3x3"] * rep)
+    model = tmd.Model(ctx, student)
+    bt = _device_batch(tmd, ctx, torch, model, b, np.full(rep, E), np.tile(F, (rep, 1)))
+    grad = torch.empty(model.n_params, dtype=torch.float32, device="cuda")
+    loss, le, lf = tmd.train_step(ctx, model, bt, lam=0.1, lr=0.0, grad=grad)
+    loss_r, le_r, lf_r, gr = oracle.train_loss_grad(student, np.array([0, s.n]), s.pos, s.species, s.box[None, :],
+                                                    np.array([E]), F, 0.1)
+    assert abs(le - le_r) <= 1e-3 * le_r + 1e-12
+    assert abs(lf - lf_r) <= 1e-3 * lf_r + 1e-12
+    _grad_close(grad.cpu().numpy().astype(np.float64), gr)
+    Fg = bt.read(tmd.BATCH_FORCES).cpu().numpy().astype(np.float64).reshape(rep, s.n, 3)
+    r = bt.read(tmd.BATCH_RESIDUAL).cpu().numpy().astype(np.float64).reshape(rep, s.n, 3)
+    w = bt.read(tmd.BATCH_TANGENT).cpu().numpy().astype(np.float64).reshape(rep, s.n, -1)
+    _, _, Fr, _ = oracle.energy_forces(student, s.pos, s.species, s.box)
+    assert np.sqrt(np.mean((Fg - Fr) ** 2, axis=(1, 2))).max() <= 1e-4
+    for k in (0, rep // 2, rep - 1):
+        wr = oracle.descriptor_jvp(student, s.pos, s.species, s.box, r[k])
+        assert (np.abs(w[k] - wr) / (np.abs(wr) + np.abs(wr).max())).max() <= 1e-4
+    bt.close()
+    model.close()
