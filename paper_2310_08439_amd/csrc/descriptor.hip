@@ -299,7 +299,7 @@ __device__ __forceinline__ void block_virial(const double (&Wd)[6], double (*red
 }
 
 // Adjoint with the force scatter done by device-scope atomics: lists without a
-// work order (a box edge shorter than two list cutoffs, merged lists) of the
+// work order (a box edge shorter than one list cutoff, merged lists) of the
 // models that the row kernels do not take (M < 3, K = 6 or K > 16).
 template <int KC, int M, int RAD>
 __global__ void __launch_bounds__(256) k_adjoint_atomic(PathArgs a, unsigned long long* F) {
@@ -459,7 +459,7 @@ __global__ void __launch_bounds__(256) k_adjoint_blocked(PathArgs a, BlockGeom b
     __shared__ int32_t h_base[257], h_first[kMaxHaloCells], hoff[kMaxHaloCells];
     __shared__ int32_t wtmp[kBlock / 64], hp_of[kMaxBlockCells];
     __shared__ double red[6][kBlock / 64][2];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int t = threadIdx.x;
     const int blk = blockIdx.x;
     int x0, y0, z0;
     block_halo_cells(bg, hp_of);
@@ -1627,7 +1627,6 @@ int log2_int(int v) {
 // Per halo atom the blocked adjoint keeps its position (3 floats) and its
 // fixed-point force accumulators (3 x 8 bytes) in LDS; capped so that two
 // workgroups fit on a CU.
-constexpr size_t kHaloBytes = 3 * sizeof(float) + 3 * sizeof(unsigned long long);
 constexpr size_t kMaxDynLds = 76 * 1024;
 size_t blocked_lds_bytes(int hmax) { return sizeof(float) * (size_t)((3 * hmax + 1) & ~1) + 24 * (size_t)hmax; }
 
@@ -1840,18 +1839,12 @@ tmd_status launch_adjoint(tmd_context* ctx, const tmd_model* m, const tmd_nlist*
         BlockGeom bg = wo_geom(nl);
         bg.F = Fsorted;
         const unsigned grid = (unsigned)bg.nb[0] * bg.nb[1] * bg.nb[2];
-        // P's layout does not depend on the chunk: for M = 3 and K >= 64 four
-        // radial functions per lane (two waves per SIMD) beat eight (one wave;
-        // measured at K = 128: 0.947 -> 0.908 ms; at K = 32 eight stay faster,
-        // 0.600 against 0.636 ms)
-        const int kca = (m->M == 3 && m->kc == 8 && m->K >= 64) ? 4 : m->kc;
-        a.nch_log2 = log2_int(m->K / kca);
-        const bool pair2 = m->K / kca == 2;  // two chunk lanes per atom share the pair geometry
+        const bool pair2 = m->K / m->kc == 2;  // two chunk lanes per atom share the pair geometry
         const int rad = m->tab ? kRadTab : (m->rec ? kRadRec : kRadDirect);
         const int rad4 = m->tab ? kRadTab : (m->rec4 ? kRadRec : kRadDirect);  // stride-four recurrence
         auto fn = mfma_adjoint(m)     ? select_mfma(rad, m->K / 4)
                   : mfma16_adjoint(m) ? select_mfma16(rad4, m->K / 4)
-                                      : select_blocked(rad, kca, m->M, pair2);
+                                      : select_blocked(rad, m->kc, m->M, pair2);
         {
             ProfScope ps_(ctx, "adjoint");
             fn<<<grid, kBlock, blocked_lds_bytes(bg.hmax), ctx->stream>>>(a, bg);

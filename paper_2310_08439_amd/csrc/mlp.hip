@@ -33,7 +33,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 
 struct MlpArgs {
-    int S, F, Fpad, act;
+    int S, F, Fpad;
     int64_t sp_off[kMaxSpecies + 1];
     int64_t tile_off[kMaxSpecies + 1];
     const int32_t* sp_idx;
@@ -49,7 +49,6 @@ struct MlpArgs {
     const float* bias;  // [S][L][H]
     const float* wout;  // [S][H]
     const float* bout;  // [S]
-    int L;
 };
 
 template <int ACT>
@@ -179,12 +178,6 @@ struct Op<true> {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
     }
 };
-
-// LDS of k_mlp: two buffers of activations, one of the last layer's in FP32.
-template <bool BF16, int H, int CB>
-constexpr int mlp_lds_bytes() {
-    return 16 * CB * ((H + 4) * 4 + 2 * (H + Op<BF16>::kPad) * (int)sizeof(typename Op<BF16>::X));
-}
 
 // One workgroup of four waves takes 16 CB atoms of one species.  Wave w owns a
 // quarter of every layer's output rows (in both directions, so s' stays in its
@@ -616,7 +609,7 @@ __global__ void __launch_bounds__(64 * staged_waves(H), staged_occupancy(H, L, A
 
 // Resident-weight form (BF16, networks whose weights fit in LDS): one
 // workgroup of 16 waves per CU keeps every matrix of one species in LDS
-// (W_1, the hidden W_l, their transposes and W_1^T, padded rows) and its waves
+// (W_1, the hidden W_l, their transposes and W_1^T) and its waves
 // take 16-atom tiles independently, with no barrier between layers.  The
 // weights are staged once per species and workgroup instead of once per
 // 128-atom tile (at 1 M atoms that is ~30 MB of L2 traffic instead of ~0.9 GB).
@@ -892,8 +885,6 @@ tmd_status launch_mlp(tmd_context* ctx, const tmd_model* m, const SpeciesGroups&
     a.S = m->S;
     a.F = m->F;
     a.Fpad = m->Fpad;
-    a.act = m->act;
-    a.L = m->L;
     // 16 atoms per workgroup, 32 beyond 96 per CU: 23,040 atoms of
     // 512-128-128-128-128 in FP32 took 134 with 16, 146 us with 32, 32,000 of
     // 32-64-64 19.1 and 18.1, 24,624 of 96-128-128 49 and 47.

@@ -41,9 +41,10 @@ struct PathArgs {
     const float* dG;
     // P written by the forward pass (if non-null) and read back by the
     // adjoint: [S][K][DR][n] by work slot (VALU kernels); atom by atom,
-    // [n][S][K][4][4] with element (k, set, i) = P[k][kMfmaRow[i][set]] (row
-    // kernels and the 16x16x4 matrix-core adjoint); or, for the matrix-core
-    // pair, one tile per 16-atom group g of the work order,
+    // [n][S][K][16], the components in order (row kernels) or as [4][4] with
+    // element (set, i) = component kMfmaRow[i][set] (16x16x4 matrix-core
+    // adjoint); or, for the matrix-core pair, one tile per 16-atom group g of
+    // the work order,
     // [g][S][K/4][4][16][4][4]: element (kk, set, atom, j, i) =
     // P[4 kk + j][kMfmaRow[i][set]]
     float* Pbuf;
@@ -239,8 +240,7 @@ __device__ __forceinline__ void store_tile(float* dst, int64_t n, const float (&
 __device__ constexpr int kMfmaRow[4][4] = {{0, 1, 2, 3}, {4, 9, 10, 11}, {7, 12, 14, 15}, {5, 6, 8, 13}};
 
 // The same tile (M = 3) in the atom-major layout [n][S][K][4][4] of the
-// row kernels and the large-K matrix-core adjoint: per radial function the
-// four fold sets, each a float4 (kMfmaRow[0..3][g]), so that a lane moves its
+// large-K matrix-core adjoint: per radial function the four fold sets, each a float4 (kMfmaRow[0..3][g]), so that a lane moves its
 // fold set with one instruction.
 template <int KC, int D>
 __device__ __forceinline__ void store_tile_am(float* dst, const float (&P)[KC][D]) {
@@ -252,20 +252,6 @@ __device__ __forceinline__ void store_tile_am(float* dst, const float (&P)[KC][D
             *reinterpret_cast<float4*>(dst + kk * 16 + 4 * g) =
                 make_float4(P[kk][kMfmaRow[0][g]], P[kk][kMfmaRow[1][g]], P[kk][kMfmaRow[2][g]], P[kk][kMfmaRow[3][g]]);
 }
-template <int KC>
-__device__ __forceinline__ void load_tile_am(const float* src, float (&P)[KC][16]) {
-#pragma unroll
-    for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 v = *reinterpret_cast<const float4*>(src + kk * 16 + 4 * g);
-            P[kk][kMfmaRow[0][g]] = v.x;
-            P[kk][kMfmaRow[1][g]] = v.y;
-            P[kk][kMfmaRow[2][g]] = v.z;
-            P[kk][kMfmaRow[3][g]] = v.w;
-        }
-}
-
 template <int KC, int D>
 __device__ __forceinline__ void load_tile(const float* src, int64_t n, float (&P)[KC][D]) {
 #pragma unroll

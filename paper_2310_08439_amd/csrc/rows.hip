@@ -1,6 +1,7 @@
 // Descriptor and adjoint with 16 lanes per atom (M = 3, K = 4, 8, 12 or 16
 // radial functions), for lists without a work order: systems with a box edge
-// below two list cutoffs, and the merged list of several systems.  A wave walks
+// below one list cutoff (or a grid that no block shape fits, or rows of more
+// than ~2,400 entries), and the merged list of several systems.  A wave walks
 // the list rows of its atoms 16 entries at a time.  Every sum (P over the row,
 // the atom's force and its virial over the row) runs in the order of the row
 // with the roundings of the kernels in descriptor.hip that take one lane per

@@ -165,11 +165,6 @@ struct tmd_model {
 };
 
 namespace tmd {
-// Position of an ABI-layout parameter in the padded layout.  Both layouts
-// hold, per species, W_l [out][in] then b_l [out] for each hidden layer, then
-// the output weights [width] and bias; the padded one at the padded sizes.
-// Returns the offset inside the species block and, for a weight, its row o
-// and padded column c (layer l; -1 for the output layer and biases).
 // Element (r, c) of a weight matrix with cols columns in the order its MFMA
 // operand reads it: 16 rows by 16 (FP32) or 32 (BF16) columns are 1 KB, lane
 // (c % 16 / 4, r % 16) holding its 16 bytes in one piece, so that a wave's load
@@ -181,6 +176,11 @@ __host__ __device__ inline int64_t wbf_at(int64_t r, int64_t c, int64_t cols) {
     return ((r / 16 * (cols / 32) + c / 32) * 64 + c % 16 / 4 * 16 + r % 16) * 8 + c % 32 / 16 * 4 + c % 4;
 }
 
+// Position of an ABI-layout parameter in the padded layout.  Both layouts
+// hold, per species, W_l [out][in] then b_l [out] for each hidden layer, then
+// the output weights [width] and bias; the padded one at the padded sizes.
+// Returns the offset inside the species block and, for a weight, its row o
+// and padded column c (layer l; -1 for the output layer and biases).
 struct ParamMap {
     int L, H, F, Fabi, K, Kabi, M1;
     int hid[TMD_MAX_HIDDEN];
@@ -498,7 +498,7 @@ struct BatchSeg {
     const double* pos = nullptr;     // system positions [n][3], original order
     const int32_t* perm = nullptr;   // the system list's sorted -> original index
     const int32_t* shift = nullptr;  // and its wrap shifts
-    const int32_t* nbr = nullptr;    // its rows (unpruned; skin entries are skipped by the kernels)
+    const int32_t* nbr = nullptr;    // its rows, skin entries among them (the merge leaves those out)
     const int32_t* img = nullptr;
     const int32_t* cnt = nullptr;
     const int32_t* sp_idx = nullptr;  // its species grouping

@@ -1230,10 +1230,9 @@ int entry_lanes(const tmd_batch* b) {
     return moment_floats(b) <= most ? 4 : 1;
 }
 
-// The same for the tangent, eight lanes or one; eight go with chunks of two
-// radial functions (146 registers and their partial sums in eight lanes, where
-// four took 247), three more chunk lanes than one lane's, and sum every moment's
-// tangent over the eight.  In us with eight and with one: 10^4 moments 10 and
+// The same for the tangent, eight lanes or one.  Eight go with chunks of two
+// radial functions (146 registers; chunks of four took 247) and sum every
+// moment's tangent over the eight lanes; one goes with the batch's chunk.  In us with eight and with one: 10^4 moments 10 and
 // 31; K = 8 at 17086 atoms (2.7 M) 28 and 34; K = 4 at 34172 (2.7 M) 30 and 38;
 // K = 16 at 17086 (5.5 M) 52 and 47; K = 32 at 17086 (10.9 M) 101 and 80.  At
 // M = 0 the sums weigh most: 19 and 25 at 0.3 M, 52 and 38 at 1.1 M.  Few atoms
