@@ -1663,10 +1663,12 @@ tmd_status tmd_train_step(tmd_context* ctx, tmd_model* m, const tmd_batch* bc, c
     u.update = opts->lr > 0.0 ? 1 : 0;
     if (u.update) {
         u.adam = opts->optimizer == TMD_OPT_ADAM ? 1 : 0;
-        if (u.adam && !m->opt_m) {
-            TMD_HIP(ctx, hipMalloc((void**)&m->opt_m, 4 * (size_t)np));
-            TMD_HIP(ctx, hipMalloc((void**)&m->opt_v, 4 * (size_t)np));
+        if (u.adam && !m->opt_v) {  // set last: a step after a failed allocation tries again
+            float* v = nullptr;
+            if (!m->opt_m) TMD_HIP(ctx, hipMalloc((void**)&m->opt_m, 4 * (size_t)np));
             TMD_HIP(ctx, hipMemsetAsync(m->opt_m, 0, 4 * (size_t)np, ctx->stream));
+            TMD_HIP(ctx, hipMalloc((void**)&v, 4 * (size_t)np));
+            m->opt_v = v;
             TMD_HIP(ctx, hipMemsetAsync(m->opt_v, 0, 4 * (size_t)np, ctx->stream));
             m->opt_t = 0;
         }
