@@ -408,21 +408,20 @@ tmd_status run_batch(tmd_server* sv, tmd_context* ctx, const std::vector<System*
     hipError_t e = hipSuccess;
     // totals [nb][7], then the forces of every system (an MD request recomputes
     // its starting forces, so the resident force arrays need not be written)
-    // Room for the largest request that comes alone, as far as the accounted
-    // bytes go (tmd_serve_create), so that these arrays and the merged list's do
-    // not grow with every larger system: growing waits for the whole device.
+    // Room for all that the accounted bytes allow (tmd_serve_create), so that
+    // these arrays and the merged list's do not grow with every larger system or
+    // batch: growing waits for the whole device.
     int cap = 64;
     for (const System* sys : systems) cap = std::max(cap, sys->nl->cap);
     const int64_t lim = std::min<int64_t>(sv->opts.max_atoms, kServeBatchAtoms);
-    const int64_t lone = std::min<int64_t>((std::min<int64_t>(sv->opts.batch_atoms, lim) + kBlock - 1) / kBlock,
-                                           lim * 64 / cap / kBlock) * kBlock;
+    const int64_t room = lim * 64 / cap / kBlock * kBlock;
     const size_t out = sizeof(double) * 7 * (size_t)nb + 4 * foff[nb];
     double* tot = (double*)ctx->ws.get(
-        "serve.batch_out", std::max(out, sizeof(double) * 7 * (size_t)kServeBatchSystems + 12 * (size_t)lone), &e);
+        "serve.batch_out", std::max(out, sizeof(double) * 7 * (size_t)kServeBatchSystems + 12 * (size_t)room), &e);
     if (e != hipSuccess) return hip_fail(ctx, e, "batch outputs");
     float* fst = reinterpret_cast<float*>(tot + 7 * (size_t)nb);
     tmd_status st;
-    if ((st = reserve_batch_workspace(ctx, m, kServeBatchSystems, lone, cap)) != TMD_OK) return st;
+    if ((st = reserve_batch_workspace(ctx, m, kServeBatchSystems, room, cap)) != TMD_OK) return st;
     for (int i = 0; i < nb; ++i) {
         System* sys = systems[i];
         if (!sys->nl_valid && (st = build_list(sv, ctx, sys, &rebuilds[i])) != TMD_OK) return st;
