@@ -792,9 +792,11 @@ MlpFn pick_staged_L(int L) {
         case 1: return k_mlp_staged<BF16, H, 1, ACT>;
         case 2: return k_mlp_staged<BF16, H, 2, ACT>;
         case 3: return k_mlp_staged<BF16, H, 3, ACT>;
-        default:  // (FP32 with 128 units: k_mlp at any size)
-            if constexpr (!BF16 && H == 128) return nullptr;
+        default: {  // (k_mlp at any size: take_staged's table)
+            constexpr bool sp = ACT == TMD_ACT_SQUAREPLUS;
+            if constexpr ((H == 128 && (!BF16 || sp)) || (H == 64 && !BF16 && sp)) return nullptr;
             else return k_mlp_staged<BF16, H, 4, ACT>;
+        }
     }
 }
 template <bool BF16, int ACT>
